@@ -861,17 +861,17 @@ def main():
                         avg_launch_ms=avg_ms, launches_per_step=n_sw / nprof,
                         alu_tflops=tflops, alu_frac=tflops / PEAK_FP32_TFLOPS)
         # the whole backward (parent recompute, child lists, level walk, gradients)
-        # against its algorithmic bytes; the level launches are latency-bound
+        # against its algorithmic bytes; the walk of all levels is latency-bound
         bwd_fams = ("parent", "child_lists", "adj_level", "grad")
         bwd_ms = sum(prof[f][1] for f in bwd_fams if f in prof) / nprof
         ab = adjoint_bytes(prob.n_v, prob.n_e)
         n_lv, ms_lv = prof["adj_level"]
         lv_ms = ms_lv / max(n_lv, 1)
-        lv_bytes = stored_traffic("k_adj_level")
+        lv_bytes = stored_traffic("k_adj_walk_team")
         detail["adjoint"] = dict(
             kernels="+".join(bwd_fams), ms_per_step=bwd_ms, algorithmic_bytes=ab,
             achieved_GBps=ab / (bwd_ms * 1e-3) / 1e9, frac=ab / (bwd_ms * 1e-3) / 1e9 / PEAK_HBM_GBS,
-            level_kernel="k_adj_level", level_avg_launch_ms=lv_ms, level_launches_per_step=n_lv / nprof,
+            level_kernel="k_adj_walk_team", level_avg_launch_ms=lv_ms, level_launches_per_step=n_lv / nprof,
             level_traffic_per_launch=lv_bytes,
             level_traffic_per_backward=None if lv_bytes is None else lv_bytes * n_lv / nprof)
         # ECG contraction on the matrix cores: executed bf16 MFMA flops (counters)

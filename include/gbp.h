@@ -153,7 +153,7 @@ int gbp_eikonal_backward(gbp_plan plan, const float *D, const float *vscale,
  * host synchronisation (graph-capturable; the same kernels and results):
  *   round_budget  relaxation rounds (>= 1); rounds after convergence return at once
  *   level_budget  adjoint levels (>= 1); gs_budget Gauss-Seidel sweeps (>= 0) for
- *                 vertices on or above parent-graph cycles
+ *                 vertices on or above parent-graph cycles and beyond the level budget
  * Whether the budgets sufficed and the input errors the kernels found (root ids
  * out of range, non-finite inputs, D not positive definite) are kept on the
  * device: gbp_plan_status reads them (it synchronises), gbp_plan_forward_work the
@@ -524,9 +524,9 @@ int gbp_plan_forward_work(gbp_plan plan, int64_t *face_solves, int64_t *node_upd
  * relaxation rounds and adjoint levels (chosen by an autotuner):
  *   lanes        lanes per vertex in a relaxation round: 8, 16 or 32
  *   sweep_blocks grid of a relaxation round, 64..2048
- *   level_blocks grid of an adjoint level (a scan of all vertices, at most 8 per
- *                thread, so at least n_v / 2048 blocks are used), 16..2048
- *   sync_batch   launches between convergence checks in synchronous calls, 1..64
+ *   level_blocks most blocks that walk the adjoint's levels, 16..2048 (at most 256 are
+ *                used, and one on small meshes)
+ *   sync_batch   rounds between convergence checks in synchronous calls, 1..64
  * Results do not depend on the configuration beyond rounding order.
  * Errors: GBP_ERR_ARG for values outside those ranges.
  */

@@ -11,14 +11,15 @@
 // upper bound of the solution and the update is monotone.
 //
 // Adjoint.  lambda = g + P^T lambda with P the parent weights.  The parent graph
-// is walked leaves-first in levels (Kahn order): a vertex is finished once all of
-// its children are, and then pulls their contributions in a fixed order, so the
-// result is deterministic.  Vertices left over by a cycle in the (non-causal)
-// anisotropic parent graph are finished with in-place (Gauss-Seidel) sweeps.
+// is walked leaves-first (walk.h): a vertex is finished once all of its children
+// are, and then sums their contributions in a fixed order, so the result is
+// deterministic.  Vertices left over by a cycle in the (non-causal) anisotropic
+// parent graph are finished with in-place (Gauss-Seidel) sweeps.
 #include <math.h>
 
 #include <algorithm>
 #include <climits>
+#include <cstddef>
 #include <cstring>
 
 #include <vector>
@@ -27,6 +28,7 @@
 #include "local_solve.h"
 #include "fista.h"
 #include "profile.h"
+#include "walk.h"
 
 namespace {
 
@@ -66,18 +68,6 @@ __device__ __forceinline__ void block_sum2_u64(unsigned long long& a, unsigned l
             b += red2[1][w];
         }
     }
-}
-
-__device__ __forceinline__ float block_max_f(float v) {
-    __shared__ float red[TPB / 64];
-    for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o));
-    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
-    __syncthreads();
-    float t = 0.f;
-    if (threadIdx.x == 0)
-        for (int w = 0; w < TPB / 64; ++w) t = fmaxf(t, red[w]);
-    __syncthreads();
-    return t;
 }
 
 // Capacity of a block's LDS push buffer (entries, all sub-queue sections): cold
@@ -202,14 +192,16 @@ __global__ void k_reduce_stats(const unsigned long long* __restrict__ blk, GbpCt
 // the queue marks are cleared when the control reset restarted the stamps.
 // only_T: T alone (the scales and onsets of the last preparation are kept).
 // G_init non-null: copied (NaN read as +inf) into guess, the hold-back's ordering key.
+// ccnt non-null: the child counts that k_parent adds to, cleared.
 __global__ void k_vertex_in(const float* __restrict__ vs_user, const float* __restrict__ T_init,
                             const int* __restrict__ node_user, float* __restrict__ vs,
                             float* __restrict__ troot, float* __restrict__ T,
                             int* __restrict__ mark, int n_v, int only_T, GbpCtl* ctl,
                             int* __restrict__ hold, const float* __restrict__ G_init,
-                            float* __restrict__ guess) {
+                            float* __restrict__ guess, int* __restrict__ ccnt) {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n_v) return;
+    if (ccnt) ccnt[i] = 0;
     if (ctl->marks_stale) mark[i] = 0;   // the stamps restarted from 1
     if (hold) hold[i] = INT_MIN;          // held in no bucket
     const int u = node_user[i];
@@ -372,7 +364,9 @@ __global__ void k_queue_all(int* __restrict__ q, int* __restrict__ mark, int n_v
 // Control-block reset at the start of a call.  The queue stamp base survives;
 // so does the forward's status bit when a backward starts (keep_fwd), so that one
 // status read after a captured iteration reports both passes.
-__global__ void k_ctl_reset(GbpCtl* ctl, int keep_fwd) {
+__global__ void k_ctl_reset(GbpCtl* ctl, int keep_fwd, TeamCtl* team) {
+    for (int k = threadIdx.x; k < (int)(sizeof(TeamCtl) / sizeof(int)); k += blockDim.x)
+        reinterpret_cast<int*>(team)[k] = 0;
     if (threadIdx.x == 0) {
         const int stamp = ctl->stamp;
         const int st = keep_fwd ? (ctl->status & 1) : 0;
@@ -841,6 +835,15 @@ __global__ void k_count_inf(const float* __restrict__ T, int n_v, GbpCtl* ctl) {
     if (threadIdx.x == 0 && t) atomicAdd(&ctl->unreached, (int)t);
 }
 
+__device__ __forceinline__ void face_nodes_rt(const int4 v, int K, int& a, int& b, int& c) {
+    switch (K) {
+        case 0: a = v.y; b = v.z; c = v.w; break;
+        case 1: a = v.x; b = v.z; c = v.w; break;
+        case 2: a = v.x; b = v.y; c = v.w; break;
+        default: a = v.x; b = v.y; c = v.z; break;
+    }
+}
+
 // ------------------------------------------------------------------ parents
 // The parent of a vertex is an argmin over its local problems: a decision taken
 // by floating point.  It is taken here in FP64 from the raw inputs (coordinates,
@@ -904,6 +907,8 @@ __device__ __forceinline__ double parent_face64(int t, int K, int self, const in
 // for the whole FP64 solve.  A candidate that finds the list full is solved in
 // its own lane.  Same values, same tie rule: the result does not depend on where
 // a candidate was solved.
+// The group's first lane also names the parents that carry weight and counts this
+// vertex among their children, which the adjoint's child lists start from.
 constexpr int kParCands = 512;   // FP64 candidates per block held in LDS
 constexpr int kParLanes = 8;     // lanes per vertex: 3 passes cover a 24-element patch
 
@@ -914,7 +919,8 @@ __global__ void __launch_bounds__(TPB)
              const int* __restrict__ tet_user, const float* __restrict__ D,
              const float* __restrict__ vs, const float4* __restrict__ xyz,
              const float* __restrict__ T, const float* __restrict__ troot, int n_v,
-             int* __restrict__ par, float4* __restrict__ pa) {
+             int* __restrict__ par, float4* __restrict__ pa, int4* __restrict__ pnode,
+             int* __restrict__ ccnt) {
     constexpr int VPB = TPB / L;                    // vertices per block
     __shared__ int cand_key[kParCands];             // vertex slot << 16 | entry position
     __shared__ double cand_val[kParCands];
@@ -1038,428 +1044,24 @@ __global__ void __launch_bounds__(TPB)
     }
     par[i] = bpar;
     pa[i] = make_float4((float)b0, (float)b1, (float)b2, (float)best);
-}
-
-__device__ __forceinline__ void face_nodes_rt(const int4 v, int K, int& a, int& b, int& c) {
-    switch (K) {
-        case 0: a = v.y; b = v.z; c = v.w; break;
-        case 1: a = v.x; b = v.z; c = v.w; break;
-        case 2: a = v.x; b = v.y; c = v.w; break;
-        default: a = v.x; b = v.y; c = v.z; break;
+    int4 pn = make_int4(-1, -1, -1, -1);
+    if (bpar >= 0) {
+        int f[3];
+        face_nodes_rt(tetv[bpar >> 2], bpar & 3, f[0], f[1], f[2]);
+        pn.x = (float)b0 > 0.f ? f[0] : -1;
+        pn.y = (float)b1 > 0.f ? f[1] : -1;
+        pn.z = (float)b2 > 0.f ? f[2] : -1;
+        if (pn.x >= 0) atomicAdd(&ccnt[pn.x], 1);
+        if (pn.y >= 0) atomicAdd(&ccnt[pn.y], 1);
+        if (pn.z >= 0) atomicAdd(&ccnt[pn.z], 1);
     }
+    pnode[i] = pn;
 }
 
 // ------------------------------------------------------------------ adjoint
-// Parent face vertices carrying weight, and two-cycle detection: a and c are
-// partners when each is a weighted parent of the other (the anisotropic scheme
-// is not causal).  The mutual edges are left out of the readiness counts; the
-// pair is solved jointly once both members' other children are finished.
-// (Also clears the child counters and fill cursors the next kernels accumulate into,
-// and the entry slots k_child_sort fills.)
-__global__ void k_pnodes(const int* __restrict__ par, const float4* __restrict__ pa,
-                         const int4* __restrict__ tetv, int n_v, int4* __restrict__ pnode,
-                         int* __restrict__ cnt, int* __restrict__ cfill, int4* __restrict__ cslot) {
-    const int c = blockIdx.x * blockDim.x + threadIdx.x;
-    if (c >= n_v) return;
-    cnt[c] = 0;
-    cfill[c] = 0;
-    cslot[c] = make_int4(-1, -1, -1, -1);
-    const int pr = par[c];
-    int4 out = make_int4(-1, -1, -1, -1);
-    if (pr >= 0) {
-        int f[3];
-        face_nodes_rt(tetv[pr >> 2], pr & 3, f[0], f[1], f[2]);
-        const float4 w = pa[c];
-        out.x = w.x > 0.f ? f[0] : -1;
-        out.y = w.y > 0.f ? f[1] : -1;
-        out.z = w.z > 0.f ? f[2] : -1;
-    }
-    pnode[c] = out;
-}
-
-__device__ __forceinline__ bool has_parent(int4 pn, int x) {
-    return pn.x == x || pn.y == x || pn.z == x;
-}
-
-__global__ void k_partner(const int4* __restrict__ pnode, int n_v, int* __restrict__ partner) {
-    const int a = blockIdx.x * blockDim.x + threadIdx.x;
-    if (a >= n_v) return;
-    const int4 pn = pnode[a];
-    const int cand[3] = {pn.x, pn.y, pn.z};
-    int best = -1;
-    for (int k = 0; k < 3; ++k)
-        if (cand[k] >= 0 && has_parent(pnode[cand[k]], a) && (best < 0 || cand[k] < best))
-            best = cand[k];
-    partner[a] = best;
-}
-
-// keep a pair only if both members chose each other; prime the pair counter
-// (pairrem: 2 at the smaller member of a pair, -1 at the larger, 0 elsewhere)
-__global__ void k_partner_sym(const int* __restrict__ partner, int n_v, int* __restrict__ pairrem) {
-    const int a = blockIdx.x * blockDim.x + threadIdx.x;
-    if (a >= n_v) return;
-    const int c = partner[a];
-    const bool ok = c >= 0 && partner[c] == a;
-    pairrem[a] = ok ? (a < c ? 2 : -1) : 0;
-}
-
-__global__ void k_partner_fix(int* __restrict__ partner, int* __restrict__ pairrem, int n_v) {
-    const int a = blockIdx.x * blockDim.x + threadIdx.x;
-    if (a >= n_v) return;
-    const int r = pairrem[a];
-    if (r == 0) partner[a] = -1;
-    if (r < 0) pairrem[a] = 0;
-}
-
-// Children per vertex.  (A vertex waits for all of them but its two-cycle
-// partner, which is always among them: see k_adj_init.)
-__global__ void k_child_count(const int4* __restrict__ pnode, int n_v, int* __restrict__ cnt) {
-    const int c = blockIdx.x * blockDim.x + threadIdx.x;
-    if (c >= n_v) return;
-    const int4 pn = pnode[c];
-    const int f[3] = {pn.x, pn.y, pn.z};
-    for (int k = 0; k < 3; ++k)
-        if (f[k] >= 0) atomicAdd(&cnt[f[k]], 1);
-}
-
-__global__ void k_child_fill(const int4* __restrict__ pnode, const float4* __restrict__ pa,
-                             int n_v, const int* __restrict__ cptr, int* __restrict__ cfill,
-                             int* __restrict__ cchild, float* __restrict__ calpha) {
-    const int c = blockIdx.x * blockDim.x + threadIdx.x;
-    if (c >= n_v) return;
-    const int4 pn = pnode[c];
-    const int f[3] = {pn.x, pn.y, pn.z};
-    const float4 w = pa[c];
-    const float al[3] = {w.x, w.y, w.z};
-    for (int k = 0; k < 3; ++k)
-        if (f[k] >= 0) {
-            const int pos = cptr[f[k]] + atomicAdd(&cfill[f[k]], 1);
-            cchild[pos] = (c << 2) | k;     // unpacked by k_child_sort
-            calpha[pos] = al[k];
-        }
-}
-
-// Position of entry k (rank r in x's sorted child list) in the entry array.
-__device__ __forceinline__ int centry(int x, int r, int k, int n_v) {
-    return r < kChildSlots ? x * kChildSlots + r : n_v * kChildSlots + k;
-}
-
-// Sort each child list by child id (fixed summation order -> deterministic), then
-// tell each child where its entry sits (the component of its cslot for this
-// parent).  The entries arrive as (child << 2 | which of the child's parents this
-// is) from k_child_fill; child ids are distinct within a list, so the packed keys
-// sort in child order, and the ids are written back unpacked.
-constexpr int kSortRegs = 16;   // child lists up to this long are sorted in registers
-
-__global__ void __launch_bounds__(TPB) k_child_sort(const int* __restrict__ cptr, int* __restrict__ cchild,
-                                                    float* __restrict__ calpha, int n_v,
-                                                    int4* __restrict__ cslot) {
-    const int p = blockIdx.x * blockDim.x + threadIdx.x;
-    if (p >= n_v) return;
-    const int b = cptr[p], e = cptr[p + 1];
-    if (e - b <= kSortRegs) {
-        // the list in registers (padded with INT_MAX) through a bitonic network
-        int ch[kSortRegs];
-        float al[kSortRegs];
-#pragma unroll
-        for (int k = 0; k < kSortRegs; ++k) {
-            ch[k] = b + k < e ? cchild[b + k] : INT_MAX;
-            al[k] = b + k < e ? calpha[b + k] : 0.f;
-        }
-#pragma unroll
-        for (int k = 2; k <= kSortRegs; k <<= 1)
-#pragma unroll
-            for (int j = k >> 1; j > 0; j >>= 1)
-#pragma unroll
-                for (int i = 0; i < kSortRegs; ++i) {
-                    const int l = i ^ j;
-                    if (l > i) {
-                        const int u = ch[i], v = ch[l];
-                        const float fu = al[i], fv = al[l];
-                        const bool sw = (u > v) == ((i & k) == 0);
-                        ch[i] = sw ? v : u;
-                        ch[l] = sw ? u : v;
-                        al[i] = sw ? fv : fu;
-                        al[l] = sw ? fu : fv;
-                    }
-                }
-#pragma unroll
-        for (int k = 0; k < kSortRegs; ++k)
-            if (b + k < e) {
-                const int c = ch[k] >> 2;
-                cchild[b + k] = c;
-                calpha[b + k] = al[k];
-                reinterpret_cast<int*>(&cslot[c])[ch[k] & 3] = centry(p, k, b + k, n_v);
-            }
-        return;
-    }
-    for (int x = b + 1; x < e; ++x) {
-        const int kc = cchild[x];
-        const float ka = calpha[x];
-        int y = x - 1;
-        while (y >= b && cchild[y] > kc) {
-            cchild[y + 1] = cchild[y];
-            calpha[y + 1] = calpha[y];
-            --y;
-        }
-        cchild[y + 1] = kc;
-        calpha[y + 1] = ka;
-    }
-    for (int x = b; x < e; ++x) {
-        const int v = cchild[x];
-        const int c = v >> 2;
-        cchild[x] = c;
-        reinterpret_cast<int*>(&cslot[c])[v & 3] = centry(p, x - b, x, n_v);
-    }
-}
-
-// Readiness stamps of the level walk: the launch from which a vertex may be
-// finished (0 for leaves), or one of the markers below.
-constexpr int kRdyNever = 0x7fffffff;   // waiting for children (or unreached)
-constexpr int kRdyWait = 0x7ffffffe;    // first member of a two-cycle, partner not ready
-constexpr int kRdyDone = 0x7ffffffd;    // finished
-constexpr int kLevelPer = 8;            // vertices per thread in a level scan (grid >= n_v / (8 TPB))
-
-// rem: the children a vertex waits for, all of them (the CSR range) but its
-// two-cycle partner, which is one of them (partners are parents of each other).
-__global__ void k_adj_init(const float* __restrict__ dLdT_user, const int* __restrict__ node_user,
-                           const float* __restrict__ T, const int* __restrict__ cptr,
-                           const int* __restrict__ partner, int* __restrict__ rem, int n_v,
-                           float* __restrict__ g, float* __restrict__ lam, int* __restrict__ done,
-                           int* __restrict__ rdy, float* __restrict__ contrib, GbpCtl* ctl) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n_v) return;
-    // fixed entry slots start at zero: a vertex sums all of them, used or not
-    float4* z = reinterpret_cast<float4*>(contrib + (size_t)i * kChildSlots);
-#pragma unroll
-    for (int k = 0; k < kChildSlots / 4; ++k) z[k] = make_float4(0.f, 0.f, 0.f, 0.f);
-    const bool reached = T[i] < GBP_INF;
-    float gi = reached ? dLdT_user[node_user[i]] : 0.f;
-    if (gi != gi) gi = 0.f;
-    g[i] = gi;
-    lam[i] = gi;
-    done[i] = reached ? 0 : 1;
-    const int wait = cptr[i + 1] - cptr[i] - (partner[i] >= 0 ? 1 : 0);
-    rem[i] = wait;
-    const bool leaf = reached && wait == 0;
-    rdy[i] = leaf ? 0 : kRdyNever;
-    if (leaf) ctl->count[0] = 1;   // flag: the first launch has work
-}
-
-// Fixed entry slot r (0..7) of a vertex from its two loaded float4s.
-__device__ __forceinline__ float slot_of(float4 s0, float4 s1, int r) {
-    const float4 h = r < 4 ? s0 : s1;
-    const int k = r & 3;
-    return k == 0 ? h.x : k == 1 ? h.y : k == 2 ? h.z : h.w;
-}
-
-// A finished vertex hands alpha * lambda to its entries in its parents' child
-// lists (read only in later launches, after this one has ended).
-__device__ __forceinline__ void publish_to(float l, int4 cs, float4 w, float* __restrict__ contrib) {
-    if (cs.x >= 0) contrib[cs.x] = w.x * l;
-    if (cs.y >= 0) contrib[cs.y] = w.y * l;
-    if (cs.z >= 0) contrib[cs.z] = w.z * l;
-}
-
-__device__ __forceinline__ void publish(int x, float l, const float4* __restrict__ pa,
-                                        const int4* __restrict__ cslot, float* __restrict__ contrib) {
-    publish_to(l, cslot[x], pa[x], contrib);
-}
-
-// A finished vertex releases its parents; a parent whose last child this was
-// becomes ready for the next launch (stamped with a plain store: it is only
-// read after this launch ends).
-__device__ __forceinline__ bool release_from(int4 pn, int skip, int self, int* __restrict__ rem,
-                                             int* __restrict__ rdy, int next) {
-    const int f[3] = {pn.x, pn.y, pn.z};
-    // the three releases in flight together, with no branch between them: a slot
-    // without a parent subtracts 0 from the finished vertex's own count (no longer
-    // read by anyone), and its result is ignored
-    bool v[3];
-    int r[3];
-#pragma unroll
-    for (int k = 0; k < 3; ++k) {
-        v[k] = f[k] >= 0 && f[k] != skip;
-        r[k] = atomicSub(&rem[v[k] ? f[k] : self], v[k] ? 1 : 0);
-    }
-#pragma unroll
-    for (int k = 0; k < 3; ++k) r[k] = v[k] ? r[k] : 0;
-    bool any = false;
-#pragma unroll
-    for (int k = 0; k < 3; ++k)
-        if (r[k] == 1) {
-            rdy[f[k]] = next;
-            any = true;
-        }
-    return any;
-}
-
-__device__ __forceinline__ bool release_parents(int x, int skip, const int4* __restrict__ pnode,
-                                                int* __restrict__ rem, int* __restrict__ rdy,
-                                                int next) {
-    return release_from(pnode[x], skip, x, rem, rdy, next);
-}
-
-// One leaves-first level, as a scan over all vertices (one thread per vertex):
-// every vertex stamped ready for this launch has all (non-partner) children
-// finished in earlier launches, so their contributions are visible.  It sums
-// lambda = g + sum alpha_c lambda_c over its child entries in a fixed order
-// (deterministic; each child wrote its alpha_c lambda_c there), then writes its
-// own contributions to its parents' entries; the second
-// member of a two-cycle to become ready solves the pair
-//   lam_a = S_a + w_ca lam_c,  lam_c = S_c + w_ac lam_a.
-__global__ void __launch_bounds__(TPB)
-    k_adj_level(int* __restrict__ rdy, const int* __restrict__ cptr,
-                const int* __restrict__ cchild, const float* __restrict__ calpha,
-                const float* __restrict__ g, float* lam, int* __restrict__ done,
-                const int4* __restrict__ pnode, const float4* __restrict__ pa,
-                const int4* __restrict__ cslot, float* __restrict__ contrib,
-                const int* __restrict__ partner, int* __restrict__ pairrem, int* __restrict__ rem,
-                int n_v, GbpCtl* ctl, int s, int* __restrict__ st) {
-    // up to kLevelPer vertices per thread: their stamps are loaded together, and
-    // before the work flag, so that all these loads are in flight at once
-    const int stride = gridDim.x * blockDim.x;
-    const int xb = blockIdx.x * blockDim.x + threadIdx.x;
-    int rv[kLevelPer];
-#pragma unroll
-    for (int k = 0; k < kLevelPer; ++k) {
-        const int x = xb + k * stride;
-        rv[k] = x < n_v ? rdy[x] : kRdyNever;
-    }
-    const int flag = ctl->count[s % 3];
-    if (blockIdx.x == 0 && threadIdx.x == 0) {
-        ctl->count[(s + 2) % 3] = 0;
-        if (flag != 0) atomicMax(&ctl->levels, s + 1);
-        if (st) {   // status for the host: this level's work flag, error bits, level index
-            st[0] = flag;
-            st[8] = ctl->err;
-            st[9] = s;
-        }
-    }
-    if (flag == 0) return;
-    __shared__ int any_sh;
-    if (threadIdx.x == 0) any_sh = 0;
-    __syncthreads();
-    bool any = false;
-#pragma unroll
-    for (int k = 0; k < kLevelPer; ++k) {
-        if (rv[k] > s) continue;                    // not ready yet, waiting or finished
-        const int x = xb + k * stride;
-        // everything this vertex needs, its first child entries included, loaded together:
-        // one memory round trip instead of a chain (partner, entry range, entries)
-        const int q = partner[x];
-        const float gx = g[x];
-        const int cb = cptr[x], ce = cptr[x + 1];
-        const int4 csx = cslot[x];
-        const float4 wx = pa[x];
-        const int4 pnx = pnode[x];
-        const float4* sl = reinterpret_cast<const float4*>(contrib + (size_t)x * kChildSlots);
-        const float4 s0 = sl[0], s1 = sl[1];
-        static_assert(kChildSlots == 8, "two float4 slot loads");
-        if (q < 0) {
-            // entries in child order: the fixed slots (zero where unused), then the rest
-            float l = gx;
-            l += s0.x; l += s0.y; l += s0.z; l += s0.w;
-            l += s1.x; l += s1.y; l += s1.z; l += s1.w;
-            for (int k = cb + kChildSlots; k < ce; ++k) l += contrib[n_v * kChildSlots + k];
-            lam[x] = l;
-            done[x] = 1;
-            rdy[x] = kRdyDone;
-            publish_to(l, csx, wx, contrib);
-            any |= release_from(pnx, -1, x, rem, rdy, s + 1);
-            continue;
-        }
-        if (atomicSub(&pairrem[min(x, q)], 1) != 1) {   // partner not ready yet
-            rdy[x] = kRdyWait;
-            continue;
-        }
-        // x's own g, entry range and fixed slots come from the registers loaded above
-        // (no child of x other than q finishes in this launch, and q's entry is
-        // skipped); using them on this path too keeps the compiler from moving those
-        // loads behind the partner test, which would add a round trip to every level
-        float S[2], w[2];
-        const int pr[2] = {x, q};
-        for (int m = 0; m < 2; ++m) {
-            const int a = pr[m], o = pr[1 - m];
-            float l = m == 0 ? gx : g[a], wo = 0.f;
-            const int b = m == 0 ? cb : cptr[a];
-            const int e = m == 0 ? ce : cptr[a + 1];
-            for (int k = b; k < e; ++k) {
-                const int ch = cchild[k];
-                if (ch == o) {
-                    wo = calpha[k];
-                } else {
-                    const int r = k - b;
-                    l += (m == 0 && r < kChildSlots) ? slot_of(s0, s1, r) : contrib[centry(a, r, k, n_v)];
-                }
-            }
-            S[m] = l;
-            w[m] = wo;     // weight of a in o's parent face
-        }
-        const float lx = (S[0] + w[0] * S[1]) / (1.f - w[0] * w[1]);
-        const float lq = S[1] + w[1] * lx;
-        lam[x] = lx;
-        lam[q] = lq;
-        done[x] = 1;
-        done[q] = 1;
-        rdy[x] = kRdyDone;
-        rdy[q] = kRdyDone;
-        publish_to(lx, csx, wx, contrib);
-        publish(q, lq, pa, cslot, contrib);
-        any |= release_from(pnx, q, x, rem, rdy, s + 1);
-        any |= release_parents(q, x, pnode, rem, rdy, s + 1);
-    }
-    if (any) any_sh = 1;
-    __syncthreads();
-    if (threadIdx.x == 0 && any_sh) ctl->count[(s + 1) % 3] = 1;
-}
-
-__global__ void k_adj_remaining(const int* __restrict__ done, int n_v, int* __restrict__ list,
-                                GbpCtl* ctl) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n_v && !done[i]) list[atomicAdd(&ctl->remaining, 1)] = i;
-}
-
-// Gauss-Seidel sweep (in place) over the vertices the level walk could not
-// finish because of a cycle in the parent graph.  Every cycle leaks weight to
-// parents outside it, so the sweeps contract to the unique solution.  Records
-// the largest |change| and the largest |lambda| of the sweep (as float bits).
-__global__ void k_adj_gs(const int* __restrict__ list, const int* __restrict__ cptr,
-                         const int* __restrict__ cchild, const float* __restrict__ calpha,
-                         const float* __restrict__ g, float* lam, GbpCtl* ctl, int slot) {
-    // change of this sweep goes to slot (slot&1); the other slot is cleared for the next
-    int* md = reinterpret_cast<int*>(slot & 1 ? &ctl->maxdiff2 : &ctl->maxdiff);
-    int* md_next = reinterpret_cast<int*>(slot & 1 ? &ctl->maxdiff : &ctl->maxdiff2);
-    if (blockIdx.x == 0 && threadIdx.x == 0) *md_next = 0;
-    const int n_list = ctl->remaining;
-    // a block with no listed vertex has nothing to add (in a budgeted backward most
-    // sweeps find the list empty: they must cost a launch, not 2 contended atomics
-    // per block)
-    if ((int)(blockIdx.x * blockDim.x) >= n_list) return;
-    float d = 0.f, a = 0.f;
-    for (int q = blockIdx.x * blockDim.x + threadIdx.x; q < n_list; q += gridDim.x * blockDim.x) {
-        const int i = list[q];
-        float l = g[i];
-        for (int x = cptr[i]; x < cptr[i + 1]; ++x) l += calpha[x] * lam[cchild[x]];
-        d = fmaxf(d, fabsf(l - lam[i]));
-        a = fmaxf(a, fabsf(l));
-        lam[i] = l;
-    }
-    d = block_max_f(d);
-    a = block_max_f(a);
-    if (threadIdx.x == 0) {   // both are >= 0 and start at 0: a zero changes no maximum
-        if (d > 0.f) atomicMax(md, __float_as_int(d));
-        if (a > 0.f) atomicMax(&ctl->lmax_bits, __float_as_int(a));
-    }
-}
-
-// Adjoint status after `sweeps` Gauss-Seidel sweeps: unsettled if the last
-// sweep still moved lambda by more than 1e-6 of its largest magnitude.
-__global__ void k_backward_end(GbpCtl* ctl, int sweeps) {
-    if (threadIdx.x != 0 || ctl->remaining == 0) return;
-    const float md = ((sweeps - 1) & 1) ? ctl->maxdiff2 : ctl->maxdiff;
-    const float lmax = __int_as_float(ctl->lmax_bits);
-    if (sweeps == 0 || !(md <= 1e-6f * lmax)) ctl->status |= 2;
+// Adjoint status after the Gauss-Seidel sweeps of a budgeted backward.
+__global__ void k_backward_end(GbpCtl* ctl) {
+    if (threadIdx.x == 0 && ctl->adj.remaining != 0 && !ctl->adj.settled) ctl->status |= 2;
 }
 
 // ------------------------------------------------------------------ gradients
@@ -1610,75 +1212,7 @@ __global__ void k_parent_out(const int* __restrict__ par, const float4* __restri
     }
 }
 
-// ------------------------------------------------------------------ scan
-__global__ void k_scan_block(const int* __restrict__ in, int* __restrict__ out, int n,
-                             int* __restrict__ bsum) {
-    __shared__ int sh[1024];
-    const int base = blockIdx.x * 1024;
-    int v[4], s = 0;
-    for (int k = 0; k < 4; ++k) {
-        const int idx = base + threadIdx.x * 4 + k;
-        v[k] = idx < n ? in[idx] : 0;
-        s += v[k];
-    }
-    sh[threadIdx.x] = s;
-    __syncthreads();
-    for (int off = 1; off < 256; off <<= 1) {
-        const int t = (int)threadIdx.x >= off ? sh[threadIdx.x - off] : 0;
-        __syncthreads();
-        sh[threadIdx.x] += t;
-        __syncthreads();
-    }
-    int run = sh[threadIdx.x] - s;  // exclusive prefix of this thread
-    for (int k = 0; k < 4; ++k) {
-        const int idx = base + threadIdx.x * 4 + k;
-        if (idx < n) out[idx] = run;
-        run += v[k];
-    }
-    if (threadIdx.x == 255) bsum[blockIdx.x] = sh[255];
-}
-
-// Exclusive scan of the block sums by one block of 1024 threads (chunks of 1024).
-__global__ void __launch_bounds__(1024) k_scan_top(int* __restrict__ bsum, int nb,
-                                                   int* __restrict__ total_out) {
-    __shared__ int sh[1024];
-    __shared__ int carry;
-    if (threadIdx.x == 0) carry = 0;
-    __syncthreads();
-    for (int base = 0; base < nb; base += 1024) {
-        const int idx = base + threadIdx.x;
-        const int v = idx < nb ? bsum[idx] : 0;
-        sh[threadIdx.x] = v;
-        __syncthreads();
-        for (int off = 1; off < 1024; off <<= 1) {
-            const int t = (int)threadIdx.x >= off ? sh[threadIdx.x - off] : 0;
-            __syncthreads();
-            sh[threadIdx.x] += t;
-            __syncthreads();
-        }
-        if (idx < nb) bsum[idx] = carry + sh[threadIdx.x] - v;
-        __syncthreads();
-        if (threadIdx.x == 1023) carry += sh[1023];
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) *total_out = carry;
-}
-
-__global__ void k_scan_add(int* __restrict__ out, int n, const int* __restrict__ bsum) {
-    const int idx = blockIdx.x * blockDim.x + threadIdx.x;
-    if (idx < n) out[idx] += bsum[idx / 1024];
-}
-
 }  // namespace
-
-int gbp_scan_exclusive(const int* in, int* out, int n, int* tmp, hipStream_t s) {
-    const int nb = (n + 1023) / 1024;
-    k_scan_block<<<nb, 256, 0, s>>>(in, out, n, tmp);
-    k_scan_top<<<1, 1024, 0, s>>>(tmp, nb, out + n);
-    k_scan_add<<<gbp_blocks(n, TPB), TPB, 0, s>>>(out, n, tmp);
-    GBP_LAUNCH_CHECK();
-    return GBP_OK;
-}
 
 // ====================================================================== host
 static int read_ctl(gbp_plan p, hipStream_t s) {
@@ -1704,18 +1238,16 @@ static int status_wait(gbp_plan p, int slot) {
     return GBP_OK;
 }
 
-// Runs launch(k, st) for k = 0, 1, ... in growing batches until the status
-// after a batch ending at k_end shows no work left, or `cap` launches.  The
+// Runs the rounds launch(k, st), k = 0, 1, ..., in growing batches until the status
+// after a batch ending at k_end shows empty queues, or `cap` launches.  The
 // first launch of the next batch (launch k_end) writes that status into the
 // pinned words st (the work it finds, the error bits, its index) and an event
 // follows it; the host waits for that event while the rest of the batch is
 // queued.  Only when no launch is left (cap) is the control block copied.
-// fwd: the status counts are the 8 sub-queue lengths (forward), else one work
-// flag (adjoint level).  Returns GBP_OK, or the device error bits' code;
-// `launched` and `finished` out.
+// Returns GBP_OK, or the device error bits' code; `launched` and `finished` out.
 template <class Launch>
-static int run_pipelined(gbp_plan p, hipStream_t s, int cap, bool fwd, Launch launch,
-                         int& launched, bool& finished) {
+static int run_pipelined(gbp_plan p, hipStream_t s, int cap, Launch launch, int& launched,
+                         bool& finished) {
     int r = 0, slot = 0, batch = 4, rc;
     finished = false;
     const int nb = std::min(batch, cap);
@@ -1744,14 +1276,11 @@ static int run_pipelined(gbp_plan p, hipStream_t s, int cap, bool fwd, Launch la
                 gbp_set_error("loop status out of order (launch %d reported, %d expected)", w[9], k_end);
                 return GBP_ERR_HIP;
             }
-            for (int x = 0; x < (fwd ? 8 : 1); ++x) left += w[x];
+            for (int x = 0; x < 8; ++x) left += w[x];
             err = w[8];
         } else {
             const GbpCtl& c = p->ctl_host[1 + slot];
-            if (fwd)
-                for (int x = 0; x < 8; ++x) left += c.qcnt[k_end % 3][x];
-            else
-                left = c.count[k_end % 3];
+            for (int x = 0; x < 8; ++x) left += c.qcnt[k_end % 3][x];
             err = c.err;
         }
         if (err) return gbp_err_from_bits(err);
@@ -1815,13 +1344,13 @@ static int prepare(gbp_plan p, const float* D, const float* vscale, const int32_
     const bool keep = cold == 2 && p->reuse_inputs && p->prep_valid && p->prep_D == D &&
                       p->prep_vs == vscale && p->prep_rn == root_node && p->prep_rt == root_t &&
                       p->prep_nroots == n_roots;
-    k_ctl_reset<<<1, 64, 0, s>>>(p->ctl, keep ? 2 : (cold == 2 ? 1 : 0));
+    k_ctl_reset<<<1, 256, 0, s>>>(p->ctl, keep ? 2 : (cold == 2 ? 1 : 0), p->team);
     k_vertex_in<<<gbp_blocks(n_v, TPB), TPB, 0, s>>>(vscale, cold == 1 ? nullptr : T_init,
                                                      p->node_user, p->vs, p->troot, p->T, p->mark,
                                                      n_v, keep ? 1 : 0, p->ctl,
                                                      cold == 1 && p->hold_delta > 0.f ? p->hold
                                                                                       : nullptr,
-                                                     G_init, p->guess);
+                                                     G_init, p->guess, cold == 2 ? p->done : nullptr);
     if (keep) {
         GBP_LAUNCH_CHECK();
         return GBP_OK;
@@ -1911,7 +1440,7 @@ int gbp_forward_impl(gbp_plan p, const float* D, const float* vscale, const int3
         for (; r < budget; ++r) launch_round(p, cold, ordered, r, s);
     } else {
         rc = run_pipelined(
-            p, s, p->max_rounds, true, [&](int k, int* st) { launch_round(p, cold, ordered, k, s, st); },
+            p, s, p->max_rounds, [&](int k, int* st) { launch_round(p, cold, ordered, k, s, st); },
             r, converged);
         if (rc) {
             k_forward_end<<<1, 64, 0, s>>>(p->ctl, r);   // stamps used so far stay retired
@@ -1961,7 +1490,7 @@ static int run_parents(gbp_plan p, const float* D_in, hipStream_t s) {
     ProfScope ps(GBP_PROF_PARENT, s);
     k_parent<kParLanes><<<gbp_blocks((long long)kParLanes * n_v, TPB), TPB, 0, s>>>(
         p->nptr, p->nent, p->tetv, p->tetg, p->tet_user, D_in, p->vs, p->xyz, p->T, p->troot, n_v,
-        p->par, p->pa);
+        p->par, p->pa, p->pnode, p->done);
     GBP_LAUNCH_CHECK();
     return GBP_OK;
 }
@@ -1999,26 +1528,13 @@ extern "C" int gbp_backward_info(gbp_plan p, int* levels, int* cyclic, int* gs_s
     return GBP_OK;
 }
 
-static void launch_level(gbp_plan p, int level, hipStream_t s, int* st = nullptr) {
-    ProfScope ps(GBP_PROF_ADJ_LEVEL, s);
-    const int need = gbp_blocks(p->n_v, TPB);
-    const int grid = std::max(std::max(1, gbp_blocks(p->n_v, (long long)TPB * kLevelPer)),
-                              std::min(need, p->level_blocks));
-    k_adj_level<<<grid, TPB, 0, s>>>(
-        p->rdy, p->ccnt, p->cchild, p->calpha, p->g, p->lam, p->done, p->pnode, p->pa, p->cslot,
-        p->contrib, p->partner, p->pairrem, p->rem, p->n_v, p->ctl, level, st);
-}
+// Meshes whose adjoint levels are narrow enough for one block (walk.hip): the backward
+// of 5k vertices takes 217 us by one block and 280-305 by a team, of 12k 297 and 256-275.
+constexpr int kWalkBlockVerts = 8192;
 
-static void launch_gs(gbp_plan p, int it, hipStream_t s) {
-    ProfScope ps(GBP_PROF_AUX, s);
-    k_adj_gs<<<std::max(1, std::min(gbp_blocks(p->n_v, TPB), 1024)), TPB, 0, s>>>(
-        p->cfill, p->ccnt, p->cchild, p->calpha, p->g, p->lam, p->ctl, it);
-}
-
-// Backward.  level_budget <= 0: synchronous (levels until the frontier empties,
-// Gauss-Seidel on what cycles leave until settled).  level_budget > 0: exactly
-// that many levels then gs_budget sweeps, no host synchronisation; status bit 1
-// reports an unsettled remainder.
+// Backward.  level_budget <= 0: synchronous (every level, Gauss-Seidel on what cycles
+// leave until settled).  level_budget > 0: at most that many levels then gs_budget
+// sweeps, no host synchronisation; status bit 1 reports an unsettled remainder.
 int gbp_backward_impl(gbp_plan p, const float* D, const float* vscale, const int32_t* root_node,
                       const float* root_t, int n_roots, const float* T, const float* dL_dT,
                       float* dL_dD, float* dL_dvscale, float* dL_droot_t, hipStream_t s,
@@ -2029,71 +1545,52 @@ int gbp_backward_impl(gbp_plan p, const float* D, const float* vscale, const int
     const int n_v = p->n_v, n_e = p->n_e;
     const bool sync = level_budget <= 0;
     if ((rc = prepare(p, D, vscale, root_node, root_t, n_roots, 2, T, s))) return rc;
-    if ((rc = run_parents(p, D, s))) return rc;   // input errors surface at the first status read
-    // parent lists, two-cycle partners, children lists
-    {
-        ProfScope ps_child(GBP_PROF_CHILD, s);
-        const int nb = gbp_blocks(n_v, TPB);
-        // p->done holds the child counts until the scan
-        k_pnodes<<<nb, TPB, 0, s>>>(p->par, p->pa, p->tetv, n_v, p->pnode, p->done, p->cfill,
-                                    p->cslot);
-        k_partner<<<nb, TPB, 0, s>>>(p->pnode, n_v, p->partner);
-        k_partner_sym<<<nb, TPB, 0, s>>>(p->partner, n_v, p->pairrem);
-        k_partner_fix<<<nb, TPB, 0, s>>>(p->partner, p->pairrem, n_v);
-        k_child_count<<<nb, TPB, 0, s>>>(p->pnode, n_v, p->done);
-        GBP_LAUNCH_CHECK();
-        if ((rc = gbp_scan_exclusive(p->done, p->ccnt, n_v, p->scan_tmp, s))) return rc;
-        k_child_fill<<<nb, TPB, 0, s>>>(p->pnode, p->pa, n_v, p->ccnt, p->cfill, p->cchild,
-                                        p->calpha);
-        k_child_sort<<<nb, TPB, 0, s>>>(p->ccnt, p->cchild, p->calpha, n_v, p->cslot);
-        GBP_LAUNCH_CHECK();
-    }
-    // leaves-first level walk
-    k_ctl_reset<<<1, 64, 0, s>>>(p->ctl, 2);
-    k_adj_init<<<gbp_blocks(n_v, TPB), TPB, 0, s>>>(dL_dT, p->node_user, p->T, p->ccnt, p->partner,
-                                                    p->rem, n_v, p->g, p->lam, p->done, p->rdy,
-                                                    p->contrib, p->ctl);
-    GBP_LAUNCH_CHECK();
-    int level = 0;
-    if (!sync) {
-        for (; level < level_budget; ++level) launch_level(p, level, s);
-    } else {
-        bool empty = false;
-        rc = run_pipelined(
-            p, s, p->max_rounds + n_v, false, [&](int k, int* st) { launch_level(p, k, s, st); },
-            level, empty);
-        if (rc) return rc;
-    }
+    if ((rc = run_parents(p, D, s))) return rc;   // input errors surface at the status read
+    AdjGraph a{};
+    a.n_v = n_v;
+    a.pnode = p->pnode;
+    a.pa = p->pa;
+    a.T = p->T;
+    a.cnt = p->done;
+    a.crange = p->crange;
+    a.cfill = p->cfill;
+    a.cchild = p->cchild;
+    a.calpha = p->calpha;
+    a.rec = p->rec;
+    a.over = p->over;
+    a.leaf = p->q[0];
+    a.ready[0] = p->ready[0];
+    a.ready[1] = p->ready[1];
+    a.team = p->team;
+    a.done = p->done;
+    a.g = p->g;
+    a.lam = p->lam;
+    a.ctl = reinterpret_cast<AdjCtl*>(reinterpret_cast<char*>(p->ctl) + offsetof(GbpCtl, adj));
+    if ((rc = gbp_adj_lists(a, dL_dT, p->node_user, s))) return rc;
+    if ((rc = gbp_adj_walk(a, sync ? INT_MAX : level_budget, n_v <= kWalkBlockVerts, p->level_blocks, s))) return rc;
     // vertices on or above cycles longer than two: Gauss-Seidel on the remainder
-    k_adj_remaining<<<gbp_blocks(n_v, TPB), TPB, 0, s>>>(p->done, n_v, p->cfill, p->ctl);
-    GBP_LAUNCH_CHECK();
-    int it = 0;
+    const int batch = gbp_adj_sweep_batch(a);
+    if ((rc = gbp_adj_sweeps(a, p->cfill, true, 0, sync ? (batch > 16 ? batch : 0) : gs_budget, 1e-6f, !sync, s)))
+        return rc;
     if (!sync) {
-        for (; it < gs_budget; ++it) launch_gs(p, it, s);
-        k_backward_end<<<1, 64, 0, s>>>(p->ctl, it);
+        k_backward_end<<<1, 64, 0, s>>>(p->ctl);
     } else {
+        const AdjCtl& c = p->ctl_host->adj;
         if ((rc = read_ctl(p, s))) return rc;
-        p->bwd_levels = p->ctl_host->levels;
-        p->last_levels = p->ctl_host->levels;
-        p->bwd_cyclic = p->ctl_host->remaining;
-        if (p->ctl_host->remaining > 0) {
-            bool ok = false;
-            const int cap = 4 * p->max_rounds + 1000;
-            while (!ok && it < cap) {
-                for (int b = 0; b < 16; ++b, ++it) launch_gs(p, it, s);
-                GBP_LAUNCH_CHECK();
-                if ((rc = read_ctl(p, s))) return rc;
-                const float lmax = __builtin_bit_cast(float, p->ctl_host->lmax_bits);
-                const float md = ((it - 1) & 1) ? p->ctl_host->maxdiff2 : p->ctl_host->maxdiff;
-                ok = md <= 1e-6f * lmax;
-            }
-            if (!ok) {
-                gbp_set_error("adjoint did not settle on %d vertices left by parent-graph cycles",
-                              p->bwd_cyclic);
-                return GBP_ERR_NOT_CONVERGED;
-            }
+        if (p->ctl_host->err) return gbp_err_from_bits(p->ctl_host->err);
+        const int cap = 4 * p->max_rounds + 1000;
+        while (c.remaining > 0 && !c.settled && c.sweeps < cap) {
+            if ((rc = gbp_adj_sweeps(a, p->cfill, false, c.sweeps, batch, 1e-6f, false, s))) return rc;
+            if ((rc = read_ctl(p, s))) return rc;
         }
-        p->bwd_gs_sweeps = it;
+        p->bwd_levels = p->last_levels = c.levels;
+        p->bwd_cyclic = c.remaining;
+        p->bwd_gs_sweeps = c.sweeps;
+        if (c.remaining > 0 && !c.settled) {
+            gbp_set_error("adjoint did not settle on %d vertices left by parent-graph cycles",
+                          p->bwd_cyclic);
+            return GBP_ERR_NOT_CONVERGED;
+        }
     }
     // gradients
     ProfScope ps_grad(GBP_PROF_GRAD, s);
@@ -2182,6 +1679,6 @@ extern "C" int gbp_plan_status(gbp_plan p, int* err_code, int* forward_converged
     if (forward_converged) *forward_converged = (c.status & 1) ? 0 : 1;
     if (backward_settled) *backward_settled = (c.status & 2) ? 0 : 1;
     if (rounds) *rounds = c.rounds;
-    if (levels) *levels = c.levels;
+    if (levels) *levels = c.adj.levels;
     return GBP_OK;
 }

@@ -4,6 +4,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <cstddef>
 #include <string>
 
 #include "gbp.h"
@@ -41,21 +42,37 @@ enum : int {
     ERRBIT_SPIN = 32,
 };
 
+// State of a launch's team of blocks (team.h), zeroed before the launch.
+constexpr int kTeamMax = 256;          // blocks
+struct TeamCtl {
+    int home;      // 1 + the XCD whose blocks may join
+    int joined;    // blocks that asked to join, marked once the team is closed
+    int size;      // blocks in the team (0: open)
+    int pad;
+    unsigned long long flag[2][kTeamMax];   // per round parity and block: round << 32 | the block's count
+};
+
+// State of one adjoint walk (walk.h), zeroed before it.
+struct AdjCtl {
+    int nleaf;     // vertices that wait for no child
+    int levels;    // last level with work + 1
+    int nchild;    // child-list entries handed out
+    int remaining; // reached vertices the walk did not finish
+    int sweeps;    // Gauss-Seidel sweeps over those
+    int settled;   // 1: the last of them moved lambda by no more than the tolerance
+    int diff[3], lmax[3];   // largest |change| and |lambda| of a checked sweep (float bits), in turn
+};
+
 // Control block of the relaxation loops (device memory, mirrored to pinned host).
 struct GbpCtl {
-    int count[3];                  // rotating queue lengths
     int err;                       // ERRBIT_* flags
     unsigned long long solves;     // local problems evaluated
     unsigned long long updates;    // nodes that changed
     int unreached;
-    int remaining;                 // adjoint: vertices the level walk did not finish
-    float maxdiff;                 // adjoint fallback: largest change of an even sweep
-    float maxdiff2;                // ... of an odd sweep
     int rounds;                    // forward: last round with work + 1
-    int lmax_bits;                 // adjoint fallback: largest |lambda| (float bits)
     int stamp;                     // queue stamp base, kept across calls
     int status;                    // bit 0: forward not converged, bit 1: adjoint not settled
-    int levels;                    // adjoint: last level with work + 1
+    AdjCtl adj;                    // adjoint walk
     int marks_stale;               // set by a reset that restarted the stamps: clear the marks
     int qcnt[3][8];                // forward: rotating lengths of the 8 sub-queues
     // bucketed hold-back of the cold forward (Delta-stepping): changed vertices whose
@@ -78,6 +95,37 @@ struct XcdQueues {
     int nq;                        // 8 (split) or 1 (one queue: R = n_v, every block serves it)
 };
 void gbp_set_queue_layout(gbp_plan p, int split);
+
+// Adjoint: a vertex's record, one 128-byte line in pieces of 16 bytes.  Its children
+// hand over their alpha * lambda in the entries (child k of the sorted list in entry
+// k, later ones in an array beside the records).
+constexpr int kAdjEntries = 8;
+struct AdjParent {
+    int vertex;        // a weighted parent or -1
+    int rank;          // the entry in its list (from kAdjEntries on: child-list position + kAdjEntries)
+    float w;           // its weight
+    union {
+        float g;       // [0] right-hand side
+        int nchild;    // [1] children
+        int partner;   // [2] two-cycle partner or -1
+    };
+};
+struct alignas(128) AdjRec {
+    AdjParent up[3];
+    int rem;           // children it still waits for (not its partner)
+    int pair;          // members of the two-cycle not yet ready (at the smaller one)
+    int first;         // its child list's first position
+    int pad;
+    float entry[kAdjEntries];
+};
+// A member's list of the vertices it made ready in a level holds at most 4 for each
+// vertex of its share of the level (a pair's two members release up to 2 each).
+constexpr int kWalkGroups = 128;   // vertices a block takes at a time
+__host__ __device__ inline size_t walk_list_cap(int n_v, int size) {
+    return 4 * ((size_t)n_v / size + kWalkGroups);
+}
+inline size_t walk_list_size(int n_v) { return 4 * ((size_t)n_v + (size_t)kWalkGroups * kTeamMax); }
+static_assert(sizeof(AdjParent) == 16 && offsetof(AdjRec, entry) == 64, "pieces 0-2 parents, 4 and 5 entries");
 
 struct gbp_plan_s {
     int device = 0;
@@ -131,10 +179,11 @@ struct gbp_plan_s {
     const void *prep_D = nullptr, *prep_vs = nullptr, *prep_rn = nullptr, *prep_rt = nullptr;
     int prep_nroots = 0;
     float* lip = nullptr;         // [4 n_e] FISTA step constant per face (allocated on use)
-    int level_blocks = 2048;      // grid of an adjoint level (scan; at least n_v / (8 * 256))
+    int level_blocks = 2048;      // grid of the adjoint walk
     int sync_batch = 16;          // launches between convergence checks (synchronous mode)
     int last_rounds = 0, last_levels = 0;   // of the last synchronous calls
     GbpCtl* ctl = nullptr;        // device control block
+    TeamCtl* team = nullptr;      // state of a launch's team of blocks
     unsigned long long* blk = nullptr;  // [2 * kStatBlocks] per-block (solves, updates)
     GbpCtl* ctl_host = nullptr;   // pinned mirror [3]: [0] status reads, [1..2] pipelined checks
     int* st_host = nullptr;       // pinned, device-mapped [2][kStWords]: loop status written by
@@ -146,22 +195,18 @@ struct gbp_plan_s {
     int bwd_levels = 0, bwd_cyclic = 0, bwd_gs_sweeps = 0;   // last backward
     int* par = nullptr;           // [n_v] (element << 2 | local slot) or -1
     float4* pa = nullptr;         // [n_v] (alpha0, alpha1, alpha2, best)
-    int* ccnt = nullptr;          // [n_v+1] children per node, then exclusive scan
-    int* cfill = nullptr;         // [n_v]
-    int* rem = nullptr;           // [n_v]
+    int2* crange = nullptr;       // [n_v] child list [begin, end)
+    int* cfill = nullptr;         // [n_v] fill cursors, then the vertices the walk left
     int* cchild = nullptr;        // [3 n_v]
     float* calpha = nullptr;      // [3 n_v]
     float* lam = nullptr;         // [n_v]
-    float* contrib = nullptr;     // [(kChildSlots + 3) n_v] alpha * lambda of each child entry, written by the child
-    int4* cslot = nullptr;        // [n_v] position of a vertex in each weighted parent's child list
+    AdjRec* rec = nullptr;        // [n_v] adjoint records
+    float* over = nullptr;        // [3 n_v] entries past a record's
+    int* ready[2] = {nullptr, nullptr};   // [walk_list_size] adjoint: the next level's vertices
     float* g = nullptr;           // [n_v]
     float* dsbar = nullptr;       // [n_e]
-    int* done = nullptr;          // [n_v] adjoint finished flag
-    int* rdy = nullptr;           // [n_v] adjoint readiness stamp (launch index or marker)
+    int* done = nullptr;          // [n_v] child counts, then adjoint finished flag
     int4* pnode = nullptr;        // [n_v] parent face vertices with alpha > 0 (-1 otherwise)
-    int* partner = nullptr;       // [n_v] mutual parent (two-cycle partner) or -1
-    int* pairrem = nullptr;       // [n_v] members of a two-cycle not yet ready (at min id)
-    int* scan_tmp = nullptr;      // block sums
 };
 
 constexpr int kStatBlocks = 2048;   // max grid of the relaxation kernels
@@ -171,11 +216,6 @@ constexpr int kStatBlocks = 2048;   // max grid of the relaxation kernels
 // in coherent pinned host memory: the host reads them after an event that follows
 // the writing launch, when the launch's writes have completed.
 constexpr int kStWords = 16;
-// Adjoint entries: the first kChildSlots children of vertex x hand over their
-// alpha * lambda in fixed slots contrib[x * kChildSlots + r] (rank r in the
-// sorted child list), further ones at contrib[n_v * kChildSlots + k] (k = the
-// CSR index), so a finished vertex reads its first entries without its CSR range.
-constexpr int kChildSlots = 8;
 
 int gbp_plan_check(gbp_plan p);
 int gbp_err_from_bits(int bits);
@@ -188,9 +228,6 @@ int gbp_backward_impl(gbp_plan p, const float* D, const float* vscale, const int
                       float* dL_dD, float* dL_dvscale, float* dL_droot_t, hipStream_t s,
                       int level_budget, int gs_budget);
 int gbp_alloc_backward(gbp_plan p);
-
-// exclusive scan of n ints in place into out[0..n] (out[n] = total); device
-int gbp_scan_exclusive(const int* in, int* out, int n, int* tmp, hipStream_t s);
 
 static inline int gbp_blocks(long long n, int threads) {
     long long b = (n + threads - 1) / threads;

@@ -75,9 +75,9 @@ static void plan_free(gbp_plan p) {
     if (!p) return;
     void* ptrs[] = {p->xyz, p->tetv, p->tet_user, p->tet_int, p->node_user, p->node_int, p->nptr, p->nent,
                     p->adj_ptr, p->adj, p->tetg, p->vs, p->T, p->troot, p->q[0], p->q[1],
-                    p->mark, p->ctl, p->blk, p->par, p->pa, p->ccnt, p->cfill, p->rem, p->cchild,
-                    p->calpha, p->lam, p->contrib, p->cslot, p->g, p->dsbar, p->done, p->rdy, p->scan_tmp, p->lip,
-                    p->pnode, p->partner, p->pairrem, p->hold, p->blist, p->guess, p->comp,
+                    p->mark, p->ctl, p->team, p->blk, p->par, p->pa, p->crange, p->cfill, p->rec, p->cchild,
+                    p->calpha, p->lam, p->over, p->ready[0], p->ready[1], p->g, p->dsbar, p->done, p->lip,
+                    p->pnode, p->hold, p->blist, p->guess, p->comp,
                     p->comp_root};
     for (void* q : ptrs)
         if (q) (void)hipFree(q);
@@ -336,6 +336,7 @@ extern "C" int gbp_plan_create(const float* xyz, int n_v, const int32_t* tets, i
     TRY(dalloc(&p->q[1], n_v));
     TRY(dalloc(&p->mark, n_v));
     TRY(dalloc(&p->ctl, 1));
+    TRY(dalloc(&p->team, 1));
     TRY(dalloc(&p->blk, 2 * (size_t)kStatBlocks));
 #undef TRY
     GbpCtl c0{};
@@ -369,22 +370,19 @@ extern "C" int gbp_plan_create(const float* xyz, int n_v, const int32_t* tets, i
 int gbp_alloc_backward(gbp_plan p) {
     if (p->bwd_ready) return GBP_OK;
     const int n_v = p->n_v, n_e = p->n_e;
-    if ((long long)(kChildSlots + 3) * n_v > INT_MAX) {
+    if ((long long)(kAdjEntries + 3) * n_v > INT_MAX) {
         gbp_set_error("adjoint: %d vertices exceed the entry layout (at most %d)", n_v,
-                      INT_MAX / (kChildSlots + 3));
+                      INT_MAX / (kAdjEntries + 3));
         return GBP_ERR_ARG;
     }
     int rc;
-    if ((rc = dalloc(&p->par, n_v)) || (rc = dalloc(&p->pa, n_v)) ||
-        (rc = dalloc(&p->ccnt, n_v + 1)) || (rc = dalloc(&p->cfill, n_v)) ||
-        (rc = dalloc(&p->rem, n_v)) || (rc = dalloc(&p->cchild, (size_t)3 * n_v)) ||
-        (rc = dalloc(&p->calpha, (size_t)3 * n_v)) || (rc = dalloc(&p->lam, n_v)) ||
-        (rc = dalloc(&p->contrib, (size_t)(kChildSlots + 3) * n_v)) || (rc = dalloc(&p->cslot, n_v)) ||
-        (rc = dalloc(&p->g, n_v)) ||
-        (rc = dalloc(&p->dsbar, n_e)) || (rc = dalloc(&p->done, n_v)) || (rc = dalloc(&p->rdy, n_v)) ||
-        (rc = dalloc(&p->pnode, n_v)) || (rc = dalloc(&p->partner, n_v)) ||
-        (rc = dalloc(&p->pairrem, n_v)) ||
-        (rc = dalloc(&p->scan_tmp, (size_t)(n_v / 256 + 2))))
+    if ((rc = dalloc(&p->par, n_v)) || (rc = dalloc(&p->pa, n_v)) || (rc = dalloc(&p->pnode, n_v)) ||
+        (rc = dalloc(&p->crange, n_v)) || (rc = dalloc(&p->cfill, n_v)) ||
+        (rc = dalloc(&p->cchild, (size_t)3 * n_v)) || (rc = dalloc(&p->calpha, (size_t)3 * n_v)) ||
+        (rc = dalloc(&p->rec, n_v)) || (rc = dalloc(&p->over, (size_t)3 * n_v)) ||
+        (rc = dalloc(&p->ready[0], walk_list_size(n_v))) || (rc = dalloc(&p->ready[1], walk_list_size(n_v))) ||
+        (rc = dalloc(&p->lam, n_v)) || (rc = dalloc(&p->g, n_v)) || (rc = dalloc(&p->done, n_v)) ||
+        (rc = dalloc(&p->dsbar, n_e)))
         return rc;
     p->bwd_ready = true;
     return GBP_OK;

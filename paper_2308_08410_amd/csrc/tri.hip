@@ -8,35 +8,33 @@
 // * backward: geodesic parents in FP64 (the argmin is a decision taken by
 //   floating point: same precision as the reference), the adjoint
 //   lambda = g + P^T lambda (Sec. 2.3 Eq. (dto_grad)) as a leaves-first walk
-//   over device-built child lists in a fixed order (a vertex finished once all
-//   its children are, two-cycles solved as pairs; the whole walk in one
-//   work-group, since these parent graphs are deep and narrow), Gauss-Seidel
-//   sweeps over just the vertices that longer cycles leave unfinished (geometric
-//   convergence there), and the gradients w.r.t. the triangle tensors, nodal
-//   velocity scales and root onsets.
+//   over device-built child lists in a fixed order (walk.h, the tetrahedral path's:
+//   a vertex finished once all its children are, two-cycles solved as pairs),
+//   Gauss-Seidel sweeps over just the vertices that longer cycles leave unfinished
+//   (geometric convergence there), and the gradients w.r.t. the triangle tensors,
+//   nodal velocity scales and root onsets.
 //
 // Meshes of the 2-D study are small (thousands of vertices); the kernels keep
-// the tetrahedral path's structure (queue, level walk, block-aggregated
-// counters) without its XCD and LDS-gather refinements.
+// the tetrahedral path's structure (queue, block-aggregated counters) without its
+// XCD and LDS-gather refinements.
 #include <math.h>
 
 #include <algorithm>
+#include <climits>
 #include <cmath>
+#include <cstddef>
 #include <vector>
 
 #include "gbp_internal.h"
 #include "local_solve.h"
+#include "walk.h"
 
 struct TriCtl {
     int count[3];
     int err;
     unsigned long long solves, updates;
     int unreached;
-    int diff_bits[2];    // adjoint sweeps: largest |change| (float bits), by parity
-    int lmax_bits[2];    // ... and largest |lambda|
-    int levels;          // adjoint: last level with work + 1
-    int remaining;       // adjoint: reached vertices the level walk has not finished
-    int nlist;           // adjoint: length of the list of those vertices
+    AdjCtl adj;          // adjoint walk
     int rounds;          // forward: last round with work + 1
 };
 
@@ -59,19 +57,20 @@ struct gbp_tri_plan_s {
     TriCtl* ctl_pipe = nullptr;   // pinned [2]: control block after each batch of rounds
     hipEvent_t ev[2] = {nullptr, nullptr};
     int* par = nullptr;
-    int2* pnode = nullptr;
+    int4* pnode = nullptr;        // weighted parents a, b (-1: none)
     float4* pa = nullptr;         // alpha_a, alpha_b, best, root_self
-    int* ccnt = nullptr;          // [n_v+1]
-    int* cfill = nullptr;         // child fill cursors, then the level walk's remaining-children counts
-    int* rdy = nullptr;           // [n_v] adjoint walk: finished flags
-    int* partner = nullptr;       // [n_v] two-cycle partner or -1
-    int* pairrem = nullptr;       // [n_v] members of a two-cycle not yet ready (at the smaller one)
+    int2* crange = nullptr;       // child lists and walk state: see AdjGraph
+    int* cfill = nullptr;         // fill cursors, then the vertices the walk left
+    int* done = nullptr;          // child counts, then finished flags
+    AdjRec* rec = nullptr;
+    float* over = nullptr;        // [2 n_v]
+    int* ready[2] = {nullptr, nullptr};
+    TeamCtl* team = nullptr;
     int* cchild = nullptr;        // [2 n_v]
     float* calpha = nullptr;
-    float* lam[2] = {nullptr, nullptr};
+    float* lam = nullptr;
     float* g = nullptr;
     float* dsbar = nullptr;
-    int* scan_tmp = nullptr;
     int stamp = 1;
     int last_levels = 0, last_cyclic = 0, last_sweeps = 0;   // of the last backward
     int max_rounds = 20000;
@@ -81,6 +80,10 @@ struct gbp_tri_plan_s {
 namespace {
 
 constexpr int TPB = 256;
+// Meshes whose adjoint levels (fronts of a planar mesh: some sqrt(n_v) / 2 vertices)
+// are narrow enough for one block: an iteration at 250k vertices takes 10.3 ms by one
+// block and 10.4-11.1 by a team, at 2M 98.7 and 83.0.
+constexpr int kTriWalkBlockVerts = 1 << 20;
 
 template <typename T>
 int tri_alloc(T** p, size_t n) {
@@ -96,8 +99,9 @@ void tri_free(gbp_tri_plan p) {
     if (!p) return;
     void* ptrs[] = {p->xy,    p->tri,   p->vptr,   p->vent,   p->nbp,    p->nb,     p->minv,
                     p->T,     p->troot, p->q[0],   p->q[1],   p->mark,   p->ctl,    p->par,
-                    p->pnode, p->pa,    p->ccnt,   p->cfill,  p->cchild, p->calpha, p->lam[0],
-                    p->lam[1], p->g,    p->dsbar,  p->scan_tmp, p->rdy, p->partner, p->pairrem};
+                    p->pnode, p->pa,    p->crange, p->cfill,  p->cchild, p->calpha, p->lam,
+                    p->g,     p->dsbar, p->done,   p->rec,    p->over,
+                    p->ready[0], p->ready[1], p->team};
     for (void* q : ptrs)
         if (q) (void)hipFree(q);
     if (p->ctl_host) (void)hipHostFree(p->ctl_host);
@@ -118,17 +122,6 @@ __device__ __forceinline__ unsigned long long tri_block_sum(unsigned long long v
     __syncthreads();
     unsigned long long t = 0;
     for (int w = 0; w < TPB / 64; ++w) t += part[w];
-    return t;
-}
-
-__device__ __forceinline__ float tri_block_max(float v) {
-    __shared__ float part[TPB / 64];
-    for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o));
-    __syncthreads();
-    if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = v;
-    __syncthreads();
-    float t = 0.f;
-    for (int w = 0; w < TPB / 64; ++w) t = fmaxf(t, part[w]);
     return t;
 }
 
@@ -307,7 +300,9 @@ __global__ void __launch_bounds__(TPB)
     }
 }
 
-__global__ void k_tri_ctl_reset(TriCtl* ctl) {
+__global__ void k_tri_ctl_reset(TriCtl* ctl, TeamCtl* team) {
+    for (int k = threadIdx.x; k < (int)(sizeof(TeamCtl) / sizeof(int)); k += blockDim.x)
+        reinterpret_cast<int*>(team)[k] = 0;
     if (threadIdx.x == 0) *ctl = TriCtl{};
 }
 
@@ -328,17 +323,18 @@ __global__ void k_tri_count_inf(const float* __restrict__ T, int n_v, TriCtl* ct
 
 // FP64 geodesic parent of every vertex: lowest triangle among local values
 // within 1e-12 max(1, |T|) of the minimum; a vertex whose smallest onset does
-// not exceed that minimum is a root (its own parent).
+// not exceed that minimum is a root (its own parent).  The parents that carry weight
+// go to pnode and count the vertex among their children (ccnt, cleared before).
 __global__ void k_tri_parent(const float2* __restrict__ xy, const int4* __restrict__ tri,
                              const float* __restrict__ D, const float* __restrict__ vscale,
                              const int* __restrict__ vptr, const int* __restrict__ vent,
                              const float* __restrict__ T, const float* __restrict__ troot, int n_v,
-                             int* __restrict__ par, int2* __restrict__ pnode,
-                             float4* __restrict__ pa) {
+                             int* __restrict__ par, int4* __restrict__ pnode,
+                             float4* __restrict__ pa, int* __restrict__ ccnt) {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n_v) return;
     par[i] = -1;
-    pnode[i] = make_int2(-1, -1);
+    pnode[i] = make_int4(-1, -1, -1, -1);
     pa[i] = make_float4(0.f, 0.f, GBP_INF, 0.f);
     const double Ti = T[i];
     if (!(T[i] < GBP_INF)) return;
@@ -372,8 +368,11 @@ __global__ void k_tri_parent(const float2* __restrict__ xy, const int4* __restri
                     pa[i] = make_float4(0.f, 0.f, (float)best, 1.f);
                 } else {
                     par[i] = t;
-                    pnode[i] = make_int2(a, b);
-                    pa[i] = make_float4((float)al, (float)(1.0 - al), (float)best, 0.f);
+                    const float wa = (float)al, wb = (float)(1.0 - al);
+                    pnode[i] = make_int4(wa > 0.f ? a : -1, wb > 0.f ? b : -1, -1, -1);
+                    pa[i] = make_float4(wa, wb, (float)best, 0.f);
+                    if (wa > 0.f) atomicAdd(&ccnt[a], 1);
+                    if (wb > 0.f) atomicAdd(&ccnt[b], 1);
                 }
                 return;
             }
@@ -383,287 +382,9 @@ __global__ void k_tri_parent(const float2* __restrict__ xy, const int4* __restri
     if (troot[i] < GBP_INF) pa[i] = make_float4(0.f, 0.f, (float)best, 1.f);   // root
 }
 
-__global__ void k_tri_child_count(const int* __restrict__ par, const int2* __restrict__ pnode,
-                                  const float4* __restrict__ pa, int n_v, int* __restrict__ cnt) {
-    const int c = blockIdx.x * blockDim.x + threadIdx.x;
-    if (c >= n_v || par[c] < 0) return;
-    const int2 p = pnode[c];
-    const float4 w = pa[c];
-    if (w.x > 0.f) atomicAdd(&cnt[p.x], 1);
-    if (w.y > 0.f) atomicAdd(&cnt[p.y], 1);
-}
-
-__global__ void k_tri_child_fill(const int* __restrict__ par, const int2* __restrict__ pnode,
-                                 const float4* __restrict__ pa, int n_v, const int* __restrict__ cptr,
-                                 int* __restrict__ cfill, int* __restrict__ cchild,
-                                 float* __restrict__ calpha) {
-    const int c = blockIdx.x * blockDim.x + threadIdx.x;
-    if (c >= n_v || par[c] < 0) return;
-    const int2 p = pnode[c];
-    const float4 w = pa[c];
-    if (w.x > 0.f) {
-        const int k = cptr[p.x] + atomicAdd(&cfill[p.x], 1);
-        cchild[k] = c;
-        calpha[k] = w.x;
-    }
-    if (w.y > 0.f) {
-        const int k = cptr[p.y] + atomicAdd(&cfill[p.y], 1);
-        cchild[k] = c;
-        calpha[k] = w.y;
-    }
-}
-
-// child lists sorted by child id: a fixed summation order (deterministic)
-__global__ void k_tri_child_sort(const int* __restrict__ cptr, int* __restrict__ cchild,
-                                 float* __restrict__ calpha, int n_v) {
-    const int p = blockIdx.x * blockDim.x + threadIdx.x;
-    if (p >= n_v) return;
-    const int b = cptr[p], e = cptr[p + 1];
-    for (int x = b + 1; x < e; ++x) {
-        const int kc = cchild[x];
-        const float ka = calpha[x];
-        int y = x - 1;
-        while (y >= b && cchild[y] > kc) {
-            cchild[y + 1] = cchild[y];
-            calpha[y + 1] = calpha[y];
-            --y;
-        }
-        cchild[y + 1] = kc;
-        calpha[y + 1] = ka;
-    }
-}
-
-__global__ void k_tri_adj_init(const float* __restrict__ dLdT, const float* __restrict__ T, int n_v,
-                               float* __restrict__ g, float* __restrict__ lam) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n_v) return;
-    float v = T[i] < GBP_INF ? dLdT[i] : 0.f;
-    if (v != v) v = 0.f;
-    g[i] = v;
-    lam[i] = v;
-}
-
-// Gauss-Seidel sweep (in place) over the vertices the level walk left unfinished
-// (on or above parent-graph cycles; every cycle leaks weight to parents outside
-// it, so the sweeps contract); records the largest |change| and |lambda|.
-__global__ void k_tri_adj_gs(const int* __restrict__ list, const int* __restrict__ cptr,
-                             const int* __restrict__ cchild, const float* __restrict__ calpha,
-                             const float* __restrict__ g, float* lam, TriCtl* ctl, int it) {
-    if (blockIdx.x == 0 && threadIdx.x == 0) {
-        ctl->diff_bits[(it + 1) & 1] = 0;
-        ctl->lmax_bits[(it + 1) & 1] = 0;
-    }
-    const int n = ctl->nlist;
-    float d = 0.f, a = 0.f;
-    for (int q = blockIdx.x * blockDim.x + threadIdx.x; q < n; q += gridDim.x * blockDim.x) {
-        const int i = list[q];
-        float l = g[i];
-        for (int k = cptr[i]; k < cptr[i + 1]; ++k) l += calpha[k] * lam[cchild[k]];
-        d = fmaxf(d, fabsf(l - lam[i]));
-        a = fmaxf(a, fabsf(l));
-        lam[i] = l;
-    }
-    d = tri_block_max(d);
-    a = tri_block_max(a);
-    if (threadIdx.x == 0) {
-        if (d > 0.f) atomicMax(&ctl->diff_bits[it & 1], __float_as_int(d));
-        if (a > 0.f) atomicMax(&ctl->lmax_bits[it & 1], __float_as_int(a));
-    }
-}
-
-// Two-cycles of the parent graph: a and c are partners when each is a weighted
-// parent of the other (the anisotropic scheme is not causal).  The walk leaves the
-// mutual edge out of both readiness counts and solves the pair jointly once both
-// members' other children are finished.  A vertex picks its smallest mutual
-// parent; a pair is kept only if both picked each other (pairrem: 2 at the
-// smaller member, -1 at the larger until k_tri_partner_fix, 0 elsewhere).
-__device__ __forceinline__ bool tri_weighted_parent(int2 pn, float4 w, int x) {
-    return (pn.x == x && w.x > 0.f) || (pn.y == x && w.y > 0.f);
-}
-
-__global__ void k_tri_partner(const int* __restrict__ par, const int2* __restrict__ pnode,
-                              const float4* __restrict__ pa, int n_v, int* __restrict__ partner) {
-    const int a = blockIdx.x * blockDim.x + threadIdx.x;
-    if (a >= n_v) return;
-    int best = -1;
-    if (par[a] >= 0) {
-        const int2 pn = pnode[a];
-        const float4 w = pa[a];
-        const int cand[2] = {w.x > 0.f ? pn.x : -1, w.y > 0.f ? pn.y : -1};
-        for (int k = 0; k < 2; ++k) {
-            const int c = cand[k];
-            if (c >= 0 && par[c] >= 0 && tri_weighted_parent(pnode[c], pa[c], a) && (best < 0 || c < best))
-                best = c;
-        }
-    }
-    partner[a] = best;
-}
-
-__global__ void k_tri_partner_sym(const int* __restrict__ partner, int n_v, int* __restrict__ pairrem) {
-    const int a = blockIdx.x * blockDim.x + threadIdx.x;
-    if (a >= n_v) return;
-    const int c = partner[a];
-    const bool ok = c >= 0 && partner[c] == a;
-    pairrem[a] = ok ? (a < c ? 2 : -1) : 0;
-}
-
-__global__ void k_tri_partner_fix(int* __restrict__ partner, int* __restrict__ pairrem, int n_v) {
-    const int a = blockIdx.x * blockDim.x + threadIdx.x;
-    if (a >= n_v) return;
-    const int r = pairrem[a];
-    if (r == 0) partner[a] = -1;
-    if (r < 0) pairrem[a] = 0;
-}
-
-// rem: the children a vertex waits for (its sorted CSR range but its partner);
-// done: 1 for unreached vertices; ctl->remaining: the reached vertices (the walk
-// subtracts those it finishes)
-__global__ void k_tri_walk_init(const int* __restrict__ cptr, const int* __restrict__ partner,
-                                const float* __restrict__ T, int n_v, int* __restrict__ rem,
-                                int* __restrict__ done, TriCtl* ctl) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    bool reached = false;
-    if (i < n_v) {
-        rem[i] = cptr[i + 1] - cptr[i] - (partner[i] >= 0 ? 1 : 0);
-        reached = T[i] < GBP_INF;
-        done[i] = reached ? 0 : 1;
-    }
-    const unsigned long long r = tri_block_sum(reached ? 1ull : 0ull);
-    if (threadIdx.x == 0 && r) atomicAdd(&ctl->remaining, (int)r);
-}
-
-constexpr int kWalkThreads = 1024;
-
-// A finished vertex releases its weighted parents (but `skip`); a parent whose
-// last awaited child this was joins the next frontier.
-__device__ __forceinline__ void tri_release(int px, int2 pn, float4 w, int skip, int self,
-                                            int* __restrict__ rem, int* __restrict__ next, int* n_next) {
-    if (px < 0) return;
-    // both releases in flight together, with no branch between them: a parent that
-    // is not released takes 0 off the finished vertex's own count instead (no
-    // longer read by anyone), and its result is ignored
-    const bool va = w.x > 0.f && pn.x != skip, vb = w.y > 0.f && pn.y != skip;
-    const int ra = atomicSub(&rem[va ? pn.x : self], va ? 1 : 0);
-    const int rb = atomicSub(&rem[vb ? pn.y : self], vb ? 1 : 0);
-    if (va && ra == 1) next[atomicAdd(n_next, 1)] = pn.x;
-    if (vb && rb == 1) next[atomicAdd(n_next, 1)] = pn.y;
-}
-
-// The whole leaves-first walk in one work-group: the 2-D study's parent graphs are
-// deep and narrow (~2,000 levels of ~100 vertices at 250k vertices), so a launch
-// (and a convergence read) per level would cost more than the level's work.
-// Each level's frontier lives in global memory (qa / qb, each vertex enters once);
-// block barriers order the levels, which makes every earlier level's lambdas
-// visible to the next.  A vertex sums lambda = g + sum alpha_c lambda_c over its
-// children in child order (the value a sweep of lambda = g + P^T lambda gives);
-// the second member of a two-cycle to become ready solves the pair
-//   lam_a = S_a + w_ca lam_c,  lam_c = S_c + w_ac lam_a.
-// Ends when a frontier is empty (each vertex enters at most once, so after at
-// most n_v levels).
-__global__ void __launch_bounds__(kWalkThreads)
-    k_tri_walk(const int* __restrict__ cptr, const int* __restrict__ cchild,
-               const float* __restrict__ calpha, const float* __restrict__ g, float* lam,
-               const int* __restrict__ par, const int2* __restrict__ pnode,
-               const float4* __restrict__ pa, const int* __restrict__ partner,
-               int* __restrict__ rem, int* __restrict__ pairrem, int* __restrict__ done,
-               const float* __restrict__ T, int* qa, int* qb, int n_v, TriCtl* ctl) {
-    __shared__ int n_cur, n_next, n_fin;
-    if (threadIdx.x == 0) {
-        n_cur = 0;
-        n_fin = 0;
-    }
-    __syncthreads();
-    for (int i = threadIdx.x; i < n_v; i += blockDim.x)
-        if (T[i] < GBP_INF && rem[i] == 0) qa[atomicAdd(&n_cur, 1)] = i;
-    __syncthreads();
-    int* cur = qa;
-    int* nxt = qb;
-    int level = 0;
-    while (n_cur > 0) {
-        const int n = n_cur;
-        __syncthreads();                    // everyone has read n_cur
-        if (threadIdx.x == 0) n_next = 0;
-        __syncthreads();
-        for (int k = threadIdx.x; k < n; k += blockDim.x) {
-            const int x = cur[k];
-            // what depends on x alone, in one round trip
-            const int q = partner[x];
-            const int e0 = cptr[x], e1 = cptr[x + 1];
-            const float gx = g[x];
-            const int px = par[x];
-            const int2 pn = pnode[x];
-            const float4 pw = pa[x];
-            if (q < 0) {
-                // children four at a time: their ids and weights, then their lambdas,
-                // summed in child order
-                float l = gx;
-                for (int e = e0; e < e1; e += 4) {
-                    int c[4];
-                    float a[4], lc[4];
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) {
-                        c[j] = e + j < e1 ? cchild[e + j] : -1;
-                        a[j] = e + j < e1 ? calpha[e + j] : 0.f;
-                    }
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) lc[j] = c[j] >= 0 ? lam[c[j]] : 0.f;
-#pragma unroll
-                    for (int j = 0; j < 4; ++j)
-                        if (e + j < e1) l += a[j] * lc[j];
-                }
-                lam[x] = l;
-                done[x] = 1;
-                atomicAdd(&n_fin, 1);
-                tri_release(px, pn, pw, -1, x, rem, nxt, &n_next);
-                continue;
-            }
-            if (atomicSub(&pairrem[min(x, q)], 1) != 1) continue;   // partner not ready yet
-            float S[2], w[2];
-            const int pr[2] = {x, q};
-            for (int m = 0; m < 2; ++m) {
-                const int a = pr[m], o = pr[1 - m];
-                float l = g[a], wo = 0.f;
-                for (int e = cptr[a]; e < cptr[a + 1]; ++e) {
-                    const int c = cchild[e];
-                    if (c == o) wo = calpha[e];
-                    else l += calpha[e] * lam[c];
-                }
-                S[m] = l;
-                w[m] = wo;                  // weight of a in o's parent face
-            }
-            const float lx = (S[0] + w[0] * S[1]) / (1.f - w[0] * w[1]);
-            lam[x] = lx;
-            lam[q] = S[1] + w[1] * lx;
-            done[x] = 1;
-            done[q] = 1;
-            atomicAdd(&n_fin, 2);
-            tri_release(px, pn, pw, q, x, rem, nxt, &n_next);
-            tri_release(par[q], pnode[q], pa[q], x, q, rem, nxt, &n_next);
-        }
-        __syncthreads();                    // the level's lambdas, releases and n_next
-        if (threadIdx.x == 0) n_cur = n_next;
-        int* t = cur;
-        cur = nxt;
-        nxt = t;
-        ++level;
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) {
-        ctl->levels = level;
-        atomicSub(&ctl->remaining, n_fin);
-    }
-}
-
-// the reached vertices the walk left unfinished (on or above longer cycles), as a list
-__global__ void k_tri_walk_list(const int* __restrict__ done, int n_v, int* __restrict__ list,
-                                TriCtl* ctl) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n_v && !done[i]) list[atomicAdd(&ctl->nlist, 1)] = i;
-}
-
 __global__ void k_tri_grad_tri(const float2* __restrict__ xy, const int4* __restrict__ tri,
                                const float* __restrict__ D, const float* __restrict__ vscale,
-                               const int* __restrict__ par, const int2* __restrict__ pnode,
+                               const int* __restrict__ par, const int4* __restrict__ pnode,
                                const float4* __restrict__ pa, const float* __restrict__ lam, int n_v,
                                float* __restrict__ dD, float* __restrict__ dsbar) {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
@@ -671,7 +392,9 @@ __global__ void k_tri_grad_tri(const float2* __restrict__ xy, const int4* __rest
     const int t = par[i];
     const float l = lam[i];
     if (t < 0 || l == 0.f) return;
-    const int2 p = pnode[i];
+    int4 p = pnode[i];
+    if (p.x < 0) p.x = i;   // no weight: any vertex does
+    if (p.y < 0) p.y = i;
     const float4 w = pa[i];
     const int4 tv = tri[t];
     double sbar = 1.0;
@@ -747,7 +470,7 @@ int tri_read(gbp_tri_plan p, hipStream_t s) {
 int tri_prepare(gbp_tri_plan p, const float* D, const float* vscale, const int32_t* root_node,
                 const float* root_t, int n_roots, bool cold, hipStream_t s) {
     const int n_v = p->n_v;
-    k_tri_ctl_reset<<<1, 64, 0, s>>>(p->ctl);
+    k_tri_ctl_reset<<<1, 256, 0, s>>>(p->ctl, p->team);
     if (p->stamp > (1 << 30)) {
         k_tri_fill_i<<<gbp_blocks(n_v, TPB), TPB, 0, s>>>(p->mark, 0, n_v);
         p->stamp = 1;
@@ -859,17 +582,19 @@ extern "C" int gbp_tri_plan_create(const float* xy, int n_v, const int32_t* tris
     TRI_TRY(tri_alloc(&p->par, n_v));
     TRI_TRY(tri_alloc(&p->pnode, n_v));
     TRI_TRY(tri_alloc(&p->pa, n_v));
-    TRI_TRY(tri_alloc(&p->ccnt, (size_t)n_v + 1));
+    TRI_TRY(tri_alloc(&p->crange, n_v));
     TRI_TRY(tri_alloc(&p->cfill, n_v));
-    TRI_TRY(tri_alloc(&p->rdy, n_v));
-    TRI_TRY(tri_alloc(&p->partner, n_v));
-    TRI_TRY(tri_alloc(&p->pairrem, n_v));
+    TRI_TRY(tri_alloc(&p->done, n_v));
+    TRI_TRY(tri_alloc(&p->rec, n_v));
+    TRI_TRY(tri_alloc(&p->over, (size_t)2 * n_v));
+    TRI_TRY(tri_alloc(&p->ready[0], walk_list_size(n_v)));
+    TRI_TRY(tri_alloc(&p->ready[1], walk_list_size(n_v)));
+    TRI_TRY(tri_alloc(&p->team, 1));
     TRI_TRY(tri_alloc(&p->cchild, (size_t)2 * n_v));
     TRI_TRY(tri_alloc(&p->calpha, (size_t)2 * n_v));
-    TRI_TRY(tri_alloc(&p->lam[0], n_v));
+    TRI_TRY(tri_alloc(&p->lam, n_v));
     TRI_TRY(tri_alloc(&p->g, n_v));
     TRI_TRY(tri_alloc(&p->dsbar, n_t));
-    TRI_TRY(tri_alloc(&p->scan_tmp, (size_t)(n_v / 256 + 2)));
 #undef TRI_UP
 #undef TRI_TRY
     if (hipHostMalloc((void**)&p->ctl_host, sizeof(TriCtl)) != hipSuccess ||
@@ -975,61 +700,52 @@ extern "C" int gbp_tri_backward(gbp_tri_plan p, const float* D, const float* vsc
     const int nb = gbp_blocks(n_v, TPB);
     GBP_HIP(hipMemcpyAsync(p->T, T, (size_t)n_v * sizeof(float), hipMemcpyDeviceToDevice, s));
     if ((rc = tri_prepare(p, D, vscale, root_node, root_t, n_roots, false, s))) return rc;
+    k_tri_fill_i<<<nb, TPB, 0, s>>>(p->done, 0, n_v);
     k_tri_parent<<<nb, TPB, 0, s>>>(p->xy, p->tri, D, vscale, p->vptr, p->vent, p->T, p->troot, n_v,
-                                    p->par, p->pnode, p->pa);
-    // child lists in a fixed order
-    k_tri_fill_i<<<gbp_blocks(n_v + 1, TPB), TPB, 0, s>>>(p->cfill, 0, n_v);
-    k_tri_child_count<<<nb, TPB, 0, s>>>(p->par, p->pnode, p->pa, n_v, p->cfill);
+                                    p->par, p->pnode, p->pa, p->done);
     GBP_LAUNCH_CHECK();
-    if ((rc = gbp_scan_exclusive(p->cfill, p->ccnt, n_v, p->scan_tmp, s))) return rc;
-    k_tri_fill_i<<<nb, TPB, 0, s>>>(p->cfill, 0, n_v);
-    k_tri_child_fill<<<nb, TPB, 0, s>>>(p->par, p->pnode, p->pa, n_v, p->ccnt, p->cfill, p->cchild,
-                                        p->calpha);
-    k_tri_child_sort<<<nb, TPB, 0, s>>>(p->ccnt, p->cchild, p->calpha, n_v);
-    k_tri_adj_init<<<nb, TPB, 0, s>>>(dL_dT, p->T, n_v, p->g, p->lam[0]);
-    // two-cycles, then the leaves-first walk in one work-group (cfill: the children
-    // each vertex still waits for; rdy: finished flags; the forward's queues hold
-    // the frontiers)
-    k_tri_partner<<<nb, TPB, 0, s>>>(p->par, p->pnode, p->pa, n_v, p->partner);
-    k_tri_partner_sym<<<nb, TPB, 0, s>>>(p->partner, n_v, p->pairrem);
-    k_tri_partner_fix<<<nb, TPB, 0, s>>>(p->partner, p->pairrem, n_v);
-    k_tri_walk_init<<<nb, TPB, 0, s>>>(p->ccnt, p->partner, p->T, n_v, p->cfill, p->rdy, p->ctl);
-    k_tri_walk<<<1, kWalkThreads, 0, s>>>(p->ccnt, p->cchild, p->calpha, p->g, p->lam[0], p->par, p->pnode,
-                                          p->pa, p->partner, p->cfill, p->pairrem, p->rdy, p->T, p->q[0],
-                                          p->q[1], n_v, p->ctl);
-    GBP_LAUNCH_CHECK();
+    AdjGraph a{};
+    a.n_v = n_v;
+    a.pnode = p->pnode;
+    a.pa = p->pa;
+    a.T = p->T;
+    a.cnt = p->done;
+    a.crange = p->crange;
+    a.cfill = p->cfill;
+    a.cchild = p->cchild;
+    a.calpha = p->calpha;
+    a.rec = p->rec;
+    a.over = p->over;
+    a.leaf = p->q[0];
+    a.ready[0] = p->ready[0];
+    a.ready[1] = p->ready[1];
+    a.team = p->team;
+    a.done = p->done;
+    a.g = p->g;
+    a.lam = p->lam;
+    a.ctl = reinterpret_cast<AdjCtl*>(reinterpret_cast<char*>(p->ctl) + offsetof(TriCtl, adj));
+    if ((rc = gbp_adj_lists(a, dL_dT, nullptr, s))) return rc;
+    if ((rc = gbp_adj_walk(a, INT_MAX, n_v <= kTriWalkBlockVerts, kTeamMax, s))) return rc;
+    // vertices on or above parent-graph cycles: Gauss-Seidel sweeps over just those
+    // (their children outside the list are final)
+    const int batch = gbp_adj_sweep_batch(a);
+    if ((rc = gbp_adj_sweeps(a, p->cfill, true, 0, batch > 16 ? batch : 0, 1e-7f, false, s))) return rc;
     if ((rc = tri_read(p, s))) return rc;
     if (p->ctl_host->err) return gbp_err_from_bits(p->ctl_host->err);
-    p->last_levels = p->ctl_host->levels;
-    p->last_cyclic = p->ctl_host->remaining;
-    // vertices on or above parent-graph cycles: Gauss-Seidel sweeps over just
-    // those (their children outside the list are final), checked every 16
-    int it = 0;
-    if (p->ctl_host->remaining > 0) {
-        k_tri_walk_list<<<nb, TPB, 0, s>>>(p->rdy, n_v, p->cfill, p->ctl);   // rem is no longer needed
-        const int gs_grid = std::max(1, std::min(gbp_blocks(p->ctl_host->remaining, TPB), 1024));
-        const int cap = 8 * n_v + 64;
-        bool settled = false;
-        while (it < cap) {
-            for (int b = 0; b < 16; ++b, ++it)
-                k_tri_adj_gs<<<gs_grid, TPB, 0, s>>>(p->cfill, p->ccnt, p->cchild, p->calpha, p->g,
-                                                     p->lam[0], p->ctl, it);
-            GBP_LAUNCH_CHECK();
-            if ((rc = tri_read(p, s))) return rc;
-            const float d = __builtin_bit_cast(float, p->ctl_host->diff_bits[(it - 1) & 1]);
-            const float a = __builtin_bit_cast(float, p->ctl_host->lmax_bits[(it - 1) & 1]);
-            if (d <= 1e-7f * a) {
-                settled = true;
-                break;
-            }
-        }
-        if (!settled) {
-            gbp_set_error("triangle adjoint did not settle in %d sweeps", it);
-            return GBP_ERR_NOT_CONVERGED;
-        }
+    const AdjCtl& c = p->ctl_host->adj;
+    const int cap = 8 * n_v + 64;
+    while (c.remaining > 0 && !c.settled && c.sweeps < cap) {
+        if ((rc = gbp_adj_sweeps(a, p->cfill, false, c.sweeps, batch, 1e-7f, false, s))) return rc;
+        if ((rc = tri_read(p, s))) return rc;
     }
-    p->last_sweeps = it;
-    const float* lam = p->lam[0];
+    p->last_levels = c.levels;
+    p->last_cyclic = c.remaining;
+    if (c.remaining > 0 && !c.settled) {
+        gbp_set_error("triangle adjoint did not settle in %d sweeps", c.sweeps);
+        return GBP_ERR_NOT_CONVERGED;
+    }
+    p->last_sweeps = c.sweeps;
+    const float* lam = p->lam;
     k_tri_fill<<<gbp_blocks(n_t, TPB), TPB, 0, s>>>(p->dsbar, 0.f, n_t);
     if (dL_dD) k_tri_fill<<<gbp_blocks(3LL * n_t, TPB), TPB, 0, s>>>(dL_dD, 0.f, 3 * n_t);
     k_tri_grad_tri<<<nb, TPB, 0, s>>>(p->xy, p->tri, D, vscale, p->par, p->pnode, p->pa, lam, n_v,
