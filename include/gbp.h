@@ -431,8 +431,8 @@ typedef struct {
  *   sum_n W[n*L + l] * U(t_s - T[n]).  W is the discretised lead-field operator
  *   B (one column per lead).  Vertices with T = +inf stay at rest (U = K0).
  *   T   device float [n_v];  W device float [n_v*L];  ecg device float [n_steps*L]
- *   1 <= L <= 256, 1 <= n_steps <= 2^20 (the kernels take tiles of 16 leads and
- *   chunks of 992 steps; the paper's 31 leads are two tiles).  Uses a
+ *   1 <= L <= 256, 1 <= n_steps <= 2^20 (a launch takes up to 32 leads and
+ *   8032 steps, or 16 leads and 16096).  Uses a
  *   library-owned scratch buffer per device (grown on demand, which frees the old
  *   one): forward calls that overlap on one device, on different streams or host
  *   threads, race on it, and a captured graph would keep a buffer that a later,
@@ -447,7 +447,7 @@ int gbp_ecg_forward(const float *T, int n_v, const float *W, int L, const gbp_ap
  * device memory (code under HIP graph capture, tight serving loops, harnesses that
  * forbid hipMalloc): the same kernels and results, with the scratch in a
  * fixed-size array that the library holds in each GPU's memory (129 KB, for any
- * call within gbp_ecg_forward's limits: the lead tiles and time chunks reuse it
+ * call within gbp_ecg_forward's limits: the launches reuse it
  * in stream order).  The call allocates and frees nothing.  Every call on one GPU
  * shares that GPU's array (the kernels clear it first): calls that overlap on one
  * GPU, on different streams or host threads, race on it.  Arguments, limits and

@@ -4,31 +4,29 @@
 //
 // The template saturates: for |4 xi / tau| >= 24, sigma equals 1 to FP32
 // precision on the upper side (1 - sigma < 4e-11) and is below 4e-11 on the lower
-// side.  A wavefront owns 64 consecutive vertices; their finite activation times
-// span [Tmin, Tmax], so for t_s < Tmin - 6 tau every term is at rest and for
-// t_s > Tmax + 6 tau every term is at K1.  Only the window in between needs the
-// template; there the contraction (time x vertices) . (vertices x leads) runs on
-// v_mfma_f32_16x16x16_bf16 tiles whose A operand is generated in registers from T.
-// (The K = 32 shape of gfx950 halves the matrix instructions but made both kernels
-// slower, 74 -> 106 us and 63 -> 67 us at 500k: they are bound by the template's
-// vector-ALU work and latency, and the wider operands raised register use.)
+// side.  The time axis is cut into tiles of 16 steps and the vertices into steps of 16:
+// a vertex step's finite activation times span [Tmin, Tmax], so only the time tiles
+// that touch [Tmin - 6 tau, Tmax + 6 tau] need the template; before them every term is
+// at rest, after them at K1.  There the contraction (time x vertices) . (vertices x
+// leads) runs on v_mfma_f32_16x16x16_bf16 tiles whose A operand is generated in
+// registers from T.  (The K = 32 shape of gfx950 halves the matrix instructions, but 32
+// vertices share a longer window, and the template's vector-ALU work is the bound.)
 // Both operands are split into bf16 hi + lo parts (three products, FP32
 // accumulation), since the lead weights sum to ~0 and the ECG is a cancellation.
-// The saturated part is a step function: the window's weight sum is added once at
-// the first saturated step and prefix-summed over time at the end.
 //
 // Backward:  dT_n = -sum_s U'(t_s - T_n) sum_l G[s,l] W[n,l], with U' zero outside
 // the same window; R = U' G runs on MFMA (vertices x time) . (time x leads) and the
 // row-wise dot with W finishes in registers.  No atomics: deterministic.
 //
-// One launch covers a tile of at most 16 leads and a chunk of at most kMaxChunk
-// time steps (the window and G tiles live in LDS); the host walks the tiles and
-// chunks.  A chunk is an independent ECG on its own time grid; the backward adds
-// the contributions of later tiles and chunks to dT in launch order.
+// A launch covers up to 32 leads (two MFMA column tiles share the template) and all
+// time steps, as long as the scratch holds a row per time tile.
 //
 // MFMA 16x16x16 lane layout: lane l holds A[l % 16][4 (l / 16) + q] and
 // B[4 (l / 16) + q][l % 16], q = 0..3, and returns D[4 (l / 16) + r][l % 16], r = 0..3.
 #include <math.h>
+
+#include <algorithm>
+#include <climits>
 #include <mutex>
 
 #include "gbp_internal.h"
@@ -37,23 +35,28 @@
 namespace {
 
 typedef short bf16x4_t __attribute__((ext_vector_type(4)));
+typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
+typedef float floatx2 __attribute__((ext_vector_type(2)));
 typedef float floatx4 __attribute__((ext_vector_type(4)));
 
 constexpr float kSat = 24.f;          // |4 xi / tau| beyond which sigma is saturated
 constexpr float kLog2e = 1.4426950408889634f;
-constexpr int kMaxChunk = 992;        // time steps per launch: keeps the LDS of both kernels within 64 KB
 constexpr int kMaxSteps = 1 << 20;    // time steps per call
 constexpr int kMaxLeads = 256;
 
-__device__ __forceinline__ unsigned bf16_rne(float x) {
-    const unsigned u = __float_as_uint(x);
-    return (u + 0x7FFFu + ((u >> 16) & 1u)) >> 16;
+// x = hi + lo in bf16, both rounded to nearest even (v_cvt_pk_bf16_f32)
+__device__ __forceinline__ void split_bf16(float x, float y, unsigned& hi, unsigned& lo) {
+    hi = __builtin_bit_cast(unsigned, __builtin_convertvector(floatx2{x, y}, bf16x2_t));
+    const floatx2 rest{x - __uint_as_float(hi << 16), y - __uint_as_float(hi & 0xffff0000u)};
+    lo = __builtin_bit_cast(unsigned, __builtin_convertvector(rest, bf16x2_t));
 }
 
-__device__ __forceinline__ void split_bf16(float x, short& hi, short& lo) {
-    const unsigned h = bf16_rne(x);
-    hi = (short)h;
-    lo = (short)bf16_rne(x - __uint_as_float(h << 16));
+__device__ __forceinline__ void split4(const float (&a)[4], bf16x4_t& hi, bf16x4_t& lo) {
+    uint2 h, l;
+    split_bf16(a[0], a[1], h.x, l.x);
+    split_bf16(a[2], a[3], h.y, l.y);
+    hi = __builtin_bit_cast(bf16x4_t, h);
+    lo = __builtin_bit_cast(bf16x4_t, l);
 }
 
 __device__ __forceinline__ floatx4 mfma3(bf16x4_t ah, bf16x4_t al, bf16x4_t bh, bf16x4_t bl,
@@ -64,281 +67,330 @@ __device__ __forceinline__ floatx4 mfma3(bf16x4_t ah, bf16x4_t al, bf16x4_t bh, 
     return acc;
 }
 
-__device__ __forceinline__ float wave_min(float v) {
-    for (int o = 32; o > 0; o >>= 1) v = fminf(v, __shfl_xor(v, o));
-    return v;
-}
-__device__ __forceinline__ float wave_max(float v) {
-    for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o));
-    return v;
-}
-
 struct ApDev {
     float K0, amp, c4, dudx, t0, dt, halfw;  // c4 = 4 log2(e)/tau, dudx = amp*4/tau, halfw = 6 tau
-    int S;                                    // time steps of this chunk
+    int S;                                    // time steps of this launch
 };
 
-// Tile of the lead and time axes a launch works on: columns [0, Lt) of arrays
-// whose rows are Ls floats long (W, and ecg / G per time step), the latter
-// `istride` floats apart from one instance to the next.
+// Lead columns [0, Lt) of arrays whose rows are Ls floats long (W, and ecg / G per time
+// step), the latter `istride` floats apart from one instance to the next.
 struct LeadTile {
     int Ls, Lt;
     long long istride;
 };
 
-// window [s_lo, s_hi) of a wave's finite activation times; empty if none finite
-__device__ __forceinline__ void wave_window(float Tv, const ApDev& ap, int& s_lo, int& s_hi,
-                                            bool& any) {
+// Window of 16 vertices, one per lane of a group of 16, in time tiles: [lo, hi), empty
+// and past the end if none is finite.  From hi on they are saturated.
+__device__ __forceinline__ void step_window(float Tv, const ApDev& ap, int& lo, int& hi) {
     const bool fin = Tv < __builtin_huge_valf();
-    const float tmin = wave_min(fin ? Tv : __builtin_huge_valf());
-    const float tmax = wave_max(fin ? Tv : -__builtin_huge_valf());
-    any = tmin < __builtin_huge_valf();
-    if (!any) {
-        s_lo = s_hi = ap.S;
-        return;
+    float tmin = fin ? Tv : __builtin_huge_valf(), tmax = fin ? Tv : -__builtin_huge_valf();
+#pragma unroll
+    for (int o = 1; o < 16; o <<= 1) {
+        tmin = fminf(tmin, __shfl_xor(tmin, o));
+        tmax = fmaxf(tmax, __shfl_xor(tmax, o));
     }
-    const float lo = ceilf((tmin - ap.halfw - ap.t0) / ap.dt);
-    const float hi = floorf((tmax + ap.halfw - ap.t0) / ap.dt) + 1.f;
-    s_lo = (int)fminf(fmaxf(lo, 0.f), (float)ap.S);
-    s_hi = (int)fminf(fmaxf(hi, 0.f), (float)ap.S);
-    if (s_hi < s_lo) s_hi = s_lo;
+    const int nt = (ap.S + 15) / 16;
+    lo = hi = nt;
+    if (!(tmin < __builtin_huge_valf())) return;
+    const float S = (float)ap.S;
+    const int s_lo = (int)fminf(fmaxf(ceilf((tmin - ap.halfw - ap.t0) / ap.dt), 0.f), S);
+    const int s_hi = (int)fminf(fmaxf(floorf((tmax + ap.halfw - ap.t0) / ap.dt) + 1.f, 0.f), S);
+    hi = (max(s_hi, s_lo) + 15) / 16;
+    lo = min(s_lo / 16, hi);
 }
 
 // ------------------------------------------------------------------ forward
-// Block: 4 waves; each wave takes 64-vertex groups of the block's range (two
-// K-steps of 32 vertices: lane (col, kq) holds vertices 8 kq .. 8 kq + 7).
-// Dynamic LDS: win[S_pad*16] floats.  The step histogram goes to global memory
-// directly (one 16-wide add per 64-vertex group).
+// A block of 16 waves takes `vb` vertices (vb / 16 steps, at most 32): their weights go to
+// LDS once, split, as B operands.  The waves share out the time tiles of the block's
+// window (and, where there are fewer than 16, the vertex steps of a tile); a tile is
+// contracted over the steps whose window it touches and added to the ECG once.
+// A step's weights' sums go to the row of g_hist of the tile from which it is saturated;
+// the rows are summed over time at the end.
+//
+// Bound by the template (exp2, rcp and the splits, ~13 vector-ALU operations a term) and, in
+// a fifth of the time, by the atomic adds.  143,564 vertices, 31 leads, 2000 steps of
+// 0.1 tau: 55 us; 500,103 vertices, 12 leads, 500 steps of tau: 40 us.  With launches of 16
+// leads and 992 steps, groups of 64 vertices and the window in LDS, where each group's
+// tiles were added with LDS atomics: 408 us (6 launches) and 49 us.
+constexpr int kFwdThreads = 1024;
+constexpr int kFwdSteps = 32;         // most vertex steps of a block
+constexpr int kFwdTiles = kFwdThreads / 64;         // time tiles at a time: one per wave
+constexpr int kBufRow = 20;           // floats per lead of a wave's tile sums: 16 steps, padded over the banks
+
+// Dynamic LDS: B operands, tile sums, saturated sums, times.
+__host__ __device__ constexpr size_t fwd_lds(int nt, int vb) {
+    return (size_t)vb * nt * 64 + (size_t)kFwdTiles * 16 * nt * kBufRow * 4 + (size_t)vb * nt * 4 + (size_t)vb * 4;
+}
+
 // Grid (blocks per instance, instances); instance i owns vertices
 // [off[i], off[i+1]) (off == nullptr: one instance of n_v vertices).
-__global__ void __launch_bounds__(256)
+template <int NT>
+__global__ void __launch_bounds__(kFwdThreads)
     k_ecg_fwd(const float* __restrict__ T, const float* __restrict__ W, int n_v, LeadTile lt,
-              ApDev ap, int S_pad, int groups_per_block, const int* __restrict__ off,
-              float* __restrict__ g_win_all, float* __restrict__ g_hist_all,
-              float* __restrict__ g_wsum_all) {
-    extern __shared__ float win[];
+              ApDev ap, int vb, const int* __restrict__ off, double* __restrict__ g_hist_all,
+              double* __restrict__ g_wsum_all, float* __restrict__ ecg_all) {
+    constexpr int NL = 16 * NT;
+    extern __shared__ char lds[];
+    short* wf = reinterpret_cast<short*>(lds);                                  // [vb/16][NT][2][16 leads][16]
+    float* buf = reinterpret_cast<float*>(lds + (size_t)vb * NT * 64);          // [waves][NL][kBufRow]
+    float* ws = buf + kFwdTiles * NL * kBufRow;                                      // [vb/16][NL]
+    float* Tsh = ws + (size_t)vb * NT;                                          // [vb]
+    __shared__ int lo_sh[kFwdSteps], hi_sh[kFwdSteps];
+    __shared__ float wtot[NL];
     const int inst = blockIdx.y;
     const int vbeg = off ? off[inst] : 0, vend = off ? off[inst + 1] : n_v;
-    const int Ls = lt.Ls, Lt = lt.Lt;
-    float* g_win = g_win_all + (size_t)inst * S_pad * 16;
-    float* g_hist = g_hist_all + (size_t)inst * S_pad * 16;
-    float* g_wsum = g_wsum_all + (size_t)inst * 16;
-    __shared__ int blo, bhi;
-    __shared__ float wsum_sh[4][16];
-    for (int x = threadIdx.x; x < S_pad * 16; x += blockDim.x) win[x] = 0.f;
-    if (threadIdx.x == 0) {
-        blo = ap.S;
-        bhi = 0;
-    }
-    __syncthreads();
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    const int col = lane & 15, kq = lane >> 4;
-    float wsum_all = 0.f;   // lane: lead col, vertices 4kq+r of each K-step
-    for (int gi = wave; gi < groups_per_block; gi += 4) {
-        const int g0 = vbeg + (blockIdx.x * groups_per_block + gi) * 64;
-        if (g0 >= vend) break;
-        const int nl = g0 + lane;
-        const float Tl = nl < vend ? T[nl] : __builtin_huge_valf();
-        int s_lo, s_hi;
-        bool any;
-        wave_window(Tl, ap, s_lo, s_hi, any);
-        float wsum_fin = 0.f;
-        // W fragments and sums (4 K-steps of 16 vertices)
-        for (int ks = 0; ks < 4; ++ks) {
-            for (int r = 0; r < 4; ++r) {
-                const int n = g0 + ks * 16 + kq * 4 + r;
-                const float w = (n < vend && col < Lt) ? W[(size_t)n * Ls + col] : 0.f;
-                const float t = n < vend ? T[n] : __builtin_huge_valf();
-                wsum_all += w;
-                if (t < __builtin_huge_valf()) wsum_fin += w;
-            }
-        }
-        if (!any) continue;
-        // window contraction, up to 4 time tiles per pass
-        for (int s0 = s_lo; s0 < s_hi; s0 += 64) {
-            floatx4 acc[4];
-            for (int m = 0; m < 4; ++m) acc[m] = floatx4{0.f, 0.f, 0.f, 0.f};
-            const int ntile = min(4, (s_hi - s0 + 15) / 16);
-            for (int ks = 0; ks < 4; ++ks) {
-                float tv[4];
-                bf16x4_t bh, bl;
-                for (int r = 0; r < 4; ++r) {
-                    const int n = g0 + ks * 16 + kq * 4 + r;
-                    const float w = (n < vend && col < Lt) ? W[(size_t)n * Ls + col] : 0.f;
-                    tv[r] = n < vend ? T[n] : __builtin_huge_valf();
-                    short h, l;
-                    split_bf16(w, h, l);
-                    bh[r] = h;
-                    bl[r] = l;
-                }
-                for (int m = 0; m < 4; ++m) {
-                    if (m >= ntile) break;
-                    const float t = ap.t0 + (float)(s0 + 16 * m + col) * ap.dt;
-                    bf16x4_t ah, al;
-                    for (int r = 0; r < 4; ++r) {
-                        const float e = __builtin_amdgcn_exp2f((tv[r] - t) * ap.c4);
-                        const float a = ap.amp * __builtin_amdgcn_rcpf(1.f + e);
-                        short h, l;
-                        split_bf16(a, h, l);
-                        ah[r] = h;
-                        al[r] = l;
-                    }
-                    acc[m] = mfma3(ah, al, bh, bl, acc[m]);
-                }
-            }
-            for (int m = 0; m < ntile; ++m)
-                for (int r = 0; r < 4; ++r) {
-                    const int s = s0 + 16 * m + kq * 4 + r;
-                    if (s < s_hi && col < Lt) atomicAdd(&win[s * 16 + col], acc[m][r]);
-                }
-        }
-        // saturated part: step at s_hi
-        float hsum = wsum_fin;
-        hsum += __shfl_xor(hsum, 16);
-        hsum += __shfl_xor(hsum, 32);
-        if (s_hi < ap.S && kq == 0 && col < Lt) atomicAdd(&g_hist[s_hi * 16 + col], ap.amp * hsum);
-        if (lane == 0) {
-            atomicMin(&blo, s_lo);
-            atomicMax(&bhi, s_hi);
-        }
-    }
-    wsum_all += __shfl_xor(wsum_all, 16);
-    wsum_all += __shfl_xor(wsum_all, 32);
-    if (kq == 0) wsum_sh[wave][col] = wsum_all;
-    __syncthreads();
-    if (threadIdx.x < 16 && (int)threadIdx.x < Lt) {
-        const float v = wsum_sh[0][threadIdx.x] + wsum_sh[1][threadIdx.x] +
-                        wsum_sh[2][threadIdx.x] + wsum_sh[3][threadIdx.x];
-        atomicAdd(&g_wsum[threadIdx.x], v);
-    }
-    const int lo = blo, hi = min(bhi, ap.S);
-    for (int x = lo * 16 + threadIdx.x; x < hi * 16; x += blockDim.x) {
-        if ((x & 15) >= Lt) continue;
-        const float a = win[x];
-        if (a != 0.f) atomicAdd(&g_win[x], a);
-    }
-}
-
-__global__ void k_ecg_zero(float* __restrict__ p, int n) {
-    for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x)
-        p[i] = 0.f;
-}
-
-// ecg[s,l] = K0 * sum W + prefix_s(hist) + win.  One block of 1024 threads:
-// thread (c, l) owns lead l and the c-th of 64 contiguous chunks of time steps.
-__global__ void __launch_bounds__(1024)
-    k_ecg_finish(const float* __restrict__ g_win_all, const float* __restrict__ g_hist_all,
-                 const float* __restrict__ g_wsum_all, int S, int S_pad, LeadTile lt, float K0,
-                 float* __restrict__ ecg_all) {
-    __shared__ float part[64][17];
-    const int inst = blockIdx.x;
-    const float* g_win = g_win_all + (size_t)inst * S_pad * 16;
-    const float* g_hist = g_hist_all + (size_t)inst * S_pad * 16;
-    const float* g_wsum = g_wsum_all + (size_t)inst * 16;
+    const int g0 = vbeg + blockIdx.x * vb;
+    if (g0 >= vend) return;
+    const int Ls = lt.Ls, Lt = lt.Lt, nt_all = (ap.S + 15) / 16, nk = vb / 16;
+    double* g_hist = g_hist_all + (size_t)inst * (nt_all + 1) * NL;
     float* ecg = ecg_all + (size_t)inst * lt.istride;
-    const int l = threadIdx.x & 15, c = threadIdx.x >> 4;
-    const int len = (S + 63) / 64;
-    const int s0 = c * len, s1 = min(S, s0 + len);
-    float run = 0.f;
-    for (int s = s0; s < s1; ++s) run += g_hist[s * 16 + l];
+    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+    if (tid < NL) wtot[tid] = 0.f;
+    if (tid < vb) {
+        const float t = g0 + tid < vend ? T[g0 + tid] : __builtin_huge_valf();
+        Tsh[tid] = t;
+        int lo, hi;
+        step_window(t, ap, lo, hi);
+        if ((tid & 15) == 0) {
+            lo_sh[tid >> 4] = lo;
+            hi_sh[tid >> 4] = hi;
+        }
+    }
+    for (int e = tid; e < nk * NL; e += kFwdThreads) ws[e] = 0.f;
+    __syncthreads();
+    // weights: two vertices a thread, split and stored as the B operand reads them, and
+    // summed: over a step's finite times (saturation), over all of them (rest)
+    float all = 0.f;
+#pragma unroll 4
+    for (int e = tid; e < vb / 2 * NL; e += kFwdThreads) {   // whole waves
+        const int l = e % NL, n = 2 * (e / NL);
+        const float* w = W + min(l, Lt - 1);
+        float a = w[(size_t)min(g0 + n, vend - 1) * Ls], b = w[(size_t)min(g0 + n + 1, vend - 1) * Ls];
+        a = l < Lt && g0 + n < vend ? a : 0.f;
+        b = l < Lt && g0 + n + 1 < vend ? b : 0.f;
+        unsigned h, r;
+        split_bf16(ap.amp * a, ap.amp * b, h, r);
+        short* q = wf + ((size_t)((n >> 4) * NT + (l >> 4)) * 2 * 16 + (l & 15)) * 16 + (n & 15);
+        *reinterpret_cast<unsigned*>(q) = h;
+        *reinterpret_cast<unsigned*>(q + 256) = r;
+        const float2 t = *reinterpret_cast<const float2*>(Tsh + n);
+        float fin = (t.x < __builtin_huge_valf() ? a : 0.f) + (t.y < __builtin_huge_valf() ? b : 0.f);
+        all += a + b;
+#pragma unroll
+        for (int o = NL; o < 64; o <<= 1) fin += __shfl_xor(fin, o);   // a wave's vertices are of one step
+        if (lane < NL) atomicAdd(&ws[(n >> 4) * NL + l], ap.amp * fin);
+    }
+#pragma unroll
+    for (int o = NL; o < 64; o <<= 1) all += __shfl_xor(all, o);
+    if (lane < NL) atomicAdd(&wtot[lane], all);
+    __syncthreads();
+    if (tid < Lt) atomicAdd(&g_wsum_all[(size_t)inst * NL + tid], (double)wtot[tid]);
+    // the block's window
+    const int klo = lane < nk ? lo_sh[lane] : nt_all, khi = lane < nk ? hi_sh[lane] : 0;
+    int blo = klo, bhi = lane < nk && klo < nt_all ? khi : 0;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        blo = min(blo, __shfl_xor(blo, o));
+        bhi = max(bhi, __shfl_xor(bhi, o));
+    }
+    const int col = lane & 15, kq = lane >> 4;
+    // what saturates at tile t goes to its row (one wave)
+    auto saturate = [&](int t) {
+        unsigned long long m = __ballot(klo < nt_all && khi == t);
+        if (!m || lane >= Lt) return;
+        float s = 0.f;
+        for (; m; m &= m - 1) s += ws[(__ffsll(m) - 1) * NL + lane];
+        atomicAdd(&g_hist[(size_t)t * NL + lane], (double)s);
+    };
+    for (int b0 = blo; b0 < bhi; b0 += kFwdTiles) {
+        const int ntb = min(kFwdTiles, bhi - b0);
+        const int parts = kFwdThreads / 64 / ntb, kpp = (nk + parts - 1) / parts;
+        if (wave < ntb) saturate(b0 + wave);
+        if (wave < ntb * parts) {
+            const int tile = b0 + wave % ntb, part = wave / ntb;
+            const float t = ap.t0 + (float)(tile * 16 + col) * ap.dt;
+            floatx4 acc[NT];
+#pragma unroll
+            for (int z = 0; z < NT; ++z) acc[z] = floatx4{0.f, 0.f, 0.f, 0.f};
+            unsigned long long m = __ballot(klo <= tile && tile < khi && lane / kpp == part);
+            while (m) {
+                const int k = __ffsll(m) - 1;
+                m &= m - 1;
+                const float4 tv = *reinterpret_cast<const float4*>(Tsh + 16 * k + 4 * kq);
+                const float tr[4] = {tv.x, tv.y, tv.z, tv.w};
+                float a[4];
+#pragma unroll
+                for (int r = 0; r < 4; ++r)
+                    a[r] = __builtin_amdgcn_rcpf(1.f + __builtin_amdgcn_exp2f((tr[r] - t) * ap.c4));
+                bf16x4_t ah, al;
+                split4(a, ah, al);
+#pragma unroll
+                for (int z = 0; z < NT; ++z) {
+                    const short* q = wf + ((size_t)(k * NT + z) * 2 * 16 + col) * 16 + 4 * kq;
+                    acc[z] = mfma3(ah, al, *reinterpret_cast<const bf16x4_t*>(q),
+                                   *reinterpret_cast<const bf16x4_t*>(q + 256), acc[z]);
+                }
+            }
+#pragma unroll
+            for (int z = 0; z < NT; ++z)
+                *reinterpret_cast<floatx4*>(buf + (wave * NL + z * 16 + col) * kBufRow + 4 * kq) = acc[z];
+        }
+        __syncthreads();
+        for (int e = tid; e < ntb * 16 * NL; e += kFwdThreads) {
+            const int l = e % NL, s = e / NL;
+            const float* b = buf + ((s >> 4) * NL + l) * kBufRow + (s & 15);
+            float v = 0.f;
+            for (int p = 0; p < parts; ++p) v += b[p * ntb * NL * kBufRow];
+            if (l < Lt && b0 * 16 + s < ap.S && v != 0.f) atomicAdd(&ecg[(size_t)(b0 * 16 + s) * Ls + l], v);
+        }
+        __syncthreads();
+    }
+    // and behind the last tile (nothing past the end)
+    if (bhi < nt_all && wave == 0) saturate(bhi);
+}
+
+// ecg (columns [0, Lt)), the rows of g_hist and g_wsum cleared
+__global__ void k_ecg_zero(float* __restrict__ work, int n_work, float* __restrict__ ecg_all, LeadTile lt, int S) {
+    const int step = gridDim.x * blockDim.x, at = blockIdx.x * blockDim.x + threadIdx.x;
+    if (blockIdx.y == 0)
+        for (int i = at; i < n_work; i += step) work[i] = 0.f;
+    float* ecg = ecg_all + (size_t)blockIdx.y * lt.istride;
+    const int n = S * lt.Lt;   // at most 2^20 * 32
+    for (int i = at; i < n; i += step) ecg[(size_t)(i / lt.Lt) * lt.Ls + i % lt.Lt] = 0.f;
+}
+
+// ecg[s,l] += K0 * sum W + the rows of hist up to the step's tile.  Grid (blocks of
+// `tpb` tiles, instances); thread (c, l) sums every (1024 / NL)-th row before the
+// block's first.
+template <int NL>
+__global__ void __launch_bounds__(1024)
+    k_ecg_finish(const double* __restrict__ g_hist_all, const double* __restrict__ g_wsum_all, int S, LeadTile lt,
+                 float K0, int tpb, float* __restrict__ ecg_all) {
+    constexpr int NC = 1024 / NL;
+    __shared__ double part[NC][NL + 1];
+    const int inst = blockIdx.y, nt = (S + 15) / 16;
+    const double* g_hist = g_hist_all + (size_t)inst * (nt + 1) * NL;
+    float* ecg = ecg_all + (size_t)inst * lt.istride;
+    const int l = threadIdx.x % NL, c = threadIdx.x / NL;
+    const int t0 = blockIdx.x * tpb, t1 = min(nt, t0 + tpb);
+    double run = 0.;
+    for (int t = c; t <= t0; t += NC) run += g_hist[(size_t)t * NL + l];
     part[c][l] = run;
     __syncthreads();
-    float off = 0.f;
-    for (int k = 0; k < c; ++k) off += part[k][l];
-    if (l < lt.Lt) {
-        const float base = K0 * g_wsum[l];
-        float r = off;
-        for (int s = s0; s < s1; ++s) {
-            r += g_hist[s * 16 + l];
-            ecg[(size_t)s * lt.Ls + l] = base + r + g_win[s * 16 + l];
-        }
+    if (c == 0) {
+        double s = K0 * g_wsum_all[(size_t)inst * NL + l];
+        for (int k = 0; k < NC; ++k) s += part[k][l];
+        part[0][l] = s;
+    }
+    __syncthreads();
+    if (l >= lt.Lt) return;
+    double r = part[0][l];
+    for (int t = t0; t < t1; ++t) {
+        if (t > t0) r += g_hist[(size_t)t * NL + l];
+        for (int s = 16 * t + c; s < min(16 * t + 16, S); s += NC) ecg[(size_t)s * lt.Ls + l] += (float)r;
     }
 }
 
 // ------------------------------------------------------------------ backward
-// accumulate: add this tile's / chunk's contribution to dT instead of writing it.
-__global__ void __launch_bounds__(256)
+// A block of 8 waves takes 8 steps of 16 vertices; the time tiles of the block's window
+// pass through LDS as B operands, kBwdTiles at a time, and each wave contracts those of
+// its own step's window.
+// Bound by the template's derivative (~19 vector-ALU operations a term).  143,564 vertices,
+// 31 leads, 2000 steps of 0.1 tau: 40 us (two steps a wave: 49 us); 500,103 vertices, 12
+// leads, 500 steps of tau: 27 us.  With all of G in every block's LDS as rows of leads,
+// windows of 64 vertices and launches of 16 leads and 992 steps: 312 us (6 launches) and 47 us.
+// accumulate: add this launch's contribution to dT instead of writing it.
+constexpr int kBwdThreads = 512;
+constexpr int kBwdVerts = kBwdThreads / 4;
+constexpr int kBwdTiles = 16;
+
+template <int NT>
+__global__ void __launch_bounds__(kBwdThreads)
     k_ecg_bwd(const float* __restrict__ T, const float* __restrict__ W,
-              const float* __restrict__ G_all, int n_v, LeadTile lt, ApDev ap, int S_pad,
+              const float* __restrict__ G_all, int n_v, LeadTile lt, ApDev ap,
               const int* __restrict__ off, int accumulate, float* __restrict__ dT) {
-    extern __shared__ short gl[];  // [S_pad*16] hi, then [S_pad*16] lo
+    constexpr int NL = 16 * NT;
+    __shared__ __align__(16) short gf[kBwdTiles][NT][2][16][16];   // tile, lead tile, hi / lo, lead, step
+    __shared__ int blo_sh, bhi_sh;
     const int inst = blockIdx.y;
     const int vbeg = off ? off[inst] : 0, vend = off ? off[inst + 1] : n_v;
+    const int g0 = vbeg + blockIdx.x * kBwdVerts;
+    if (g0 >= vend) return;
     const int Ls = lt.Ls, Lt = lt.Lt;
     const float* G = G_all + (size_t)inst * lt.istride;
-    short* gh = gl;
-    short* glo = gl + S_pad * 16;
-    for (int x = threadIdx.x; x < S_pad * 16; x += blockDim.x) {
-        const int s = x >> 4, l = x & 15;
-        const float v = (s < ap.S && l < Lt) ? G[(size_t)s * Ls + l] : 0.f;
-        short h, lo;
-        split_bf16(v, h, lo);
-        gh[x] = h;
-        glo[x] = lo;
+    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, col = lane & 15, kq = lane >> 4;
+    if (tid == 0) {
+        blo_sh = INT_MAX;
+        bhi_sh = 0;
     }
     __syncthreads();
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    const int col = lane & 15, kq = lane >> 4;
-    const int nwaves = gridDim.x * 4;
-    for (int grp = blockIdx.x * 4 + wave; vbeg + grp * 64 < vend; grp += nwaves) {
-        const int g0 = vbeg + grp * 64;
-        const int nl = g0 + lane;
-        const float Tl = nl < vend ? T[nl] : __builtin_huge_valf();
-        int s_lo, s_hi;
-        bool any;
-        wave_window(Tl, ap, s_lo, s_hi, any);
-        // 4 vertex tiles of 16
-        for (int mt = 0; mt < 4; ++mt) {
-            const int nrow = g0 + mt * 16 + col;   // A row: vertex
-            const float tn = nrow < vend ? T[nrow] : __builtin_huge_valf();
-            floatx4 acc = floatx4{0.f, 0.f, 0.f, 0.f};
-            if (any) {
-                for (int s0 = s_lo; s0 < s_hi; s0 += 16) {
-                    bf16x4_t ah, al, bh, bl;
-                    for (int r = 0; r < 4; ++r) {
-                        const int s = s0 + kq * 4 + r;
-                        const float t = ap.t0 + (float)s * ap.dt;
-                        const float e = __builtin_amdgcn_exp2f((tn - t) * ap.c4);
-                        const float q = __builtin_amdgcn_rcpf(1.f + e);
-                        const float omq = e < 1.f ? e * q : 1.f - q;
-                        const float a = (s < ap.S) ? ap.dudx * q * omq : 0.f;
-                        short h, l;
-                        split_bf16(a, h, l);
-                        ah[r] = h;
-                        al[r] = l;
-                        const int sc = s < S_pad ? s : S_pad - 1;
-                        bh[r] = (s < ap.S) ? gh[sc * 16 + col] : (short)0;
-                        bl[r] = (s < ap.S) ? glo[sc * 16 + col] : (short)0;
-                    }
-                    acc = mfma3(ah, al, bh, bl, acc);
-                }
-            }
-            // acc[r]: R[vertex g0+mt*16+kq*4+r][lead col]
-            float out[4];
-            for (int r = 0; r < 4; ++r) {
-                const int n = g0 + mt * 16 + kq * 4 + r;
-                const float w = (n < vend && col < Lt) ? W[(size_t)n * Ls + col] : 0.f;
-                float v = acc[r] * w;
-                v += __shfl_xor(v, 1);
-                v += __shfl_xor(v, 2);
-                v += __shfl_xor(v, 4);
-                v += __shfl_xor(v, 8);
-                out[r] = v;
-            }
-            if (col == 0)
-                for (int r = 0; r < 4; ++r) {
-                    const int n = g0 + mt * 16 + kq * 4 + r;
-                    if (n < vend) dT[n] = accumulate ? dT[n] - out[r] : -out[r];
-                }
+    const int n0 = g0 + wave * 16;
+    const float tn = n0 + col < vend ? T[n0 + col] : __builtin_huge_valf();   // A row: vertex
+    int lo, hi;
+    step_window(tn, ap, lo, hi);
+    lo = __builtin_amdgcn_readfirstlane(lo);
+    hi = __builtin_amdgcn_readfirstlane(hi);
+    if (lane == 0 && lo < hi) {
+        atomicMin(&blo_sh, lo);
+        atomicMax(&bhi_sh, hi);
+    }
+    floatx4 acc[NT];
+#pragma unroll
+    for (int z = 0; z < NT; ++z) acc[z] = floatx4{0.f, 0.f, 0.f, 0.f};
+    __syncthreads();
+    const int blo = blo_sh, bhi = bhi_sh;
+    for (int b0 = blo; b0 < bhi; b0 += kBwdTiles) {
+        const int ntb = min(kBwdTiles, bhi - b0);
+        for (int e = tid; e < ntb * 8 * NL; e += kBwdThreads) {
+            const int l = e % NL, s2 = 2 * (e / NL), s = b0 * 16 + s2;
+            const float* g = G + (size_t)s * Ls + l;
+            const float a = l < Lt && s < ap.S ? g[0] : 0.f;
+            const float b = l < Lt && s + 1 < ap.S ? g[Ls] : 0.f;
+            unsigned h, r;
+            split_bf16(a, b, h, r);
+            *reinterpret_cast<unsigned*>(&gf[s2 >> 4][l >> 4][0][l & 15][s2 & 15]) = h;
+            *reinterpret_cast<unsigned*>(&gf[s2 >> 4][l >> 4][1][l & 15][s2 & 15]) = r;
         }
+        __syncthreads();
+        for (int t = max(lo, b0); t < min(hi, b0 + ntb); ++t) {
+            float a[4];
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const float ts = ap.t0 + (float)(t * 16 + kq * 4 + r) * ap.dt;
+                const float e = __builtin_amdgcn_exp2f((tn - ts) * ap.c4);
+                const float q = __builtin_amdgcn_rcpf(1.f + e);
+                a[r] = q * (e < 1.f ? e * q : 1.f - q);
+            }
+            bf16x4_t ah, al;
+            split4(a, ah, al);
+#pragma unroll
+            for (int z = 0; z < NT; ++z)
+                acc[z] = mfma3(ah, al, *reinterpret_cast<const bf16x4_t*>(&gf[t - b0][z][0][col][4 * kq]),
+                               *reinterpret_cast<const bf16x4_t*>(&gf[t - b0][z][1][col][4 * kq]), acc[z]);
+        }
+        __syncthreads();
+    }
+    // acc[z][r]: R[vertex 4 kq + r of the step][lead 16 z + col]
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        const int n = n0 + kq * 4 + r;
+        float s = 0.f;
+#pragma unroll
+        for (int z = 0; z < NT; ++z)
+            if (n < vend && z * 16 + col < Lt) s += acc[z][r] * W[(size_t)n * Ls + z * 16 + col];
+        s += __shfl_xor(s, 1);
+        s += __shfl_xor(s, 2);
+        s += __shfl_xor(s, 4);
+        s += __shfl_xor(s, 8);
+        if (col == 0 && n < vend) dT[n] = (accumulate ? dT[n] : 0.f) - ap.dudx * s;
     }
 }
 
 // ------------------------------------------------------------------ workspace
-// Scratch of gbp_ecg_forward_noalloc: one chunk's window, histogram and weight
-// sums for one instance (every chunk and lead tile reuses it in stream order),
+// Scratch of gbp_ecg_forward_noalloc: the rows per time tile and the weight sums of one
+// launch for one instance (every launch of a call reuses it in stream order),
 // file-scope device memory that each GPU holds until the process ends.
-constexpr int kNoAllocFloats = 2 * ((kMaxChunk + 15) / 16 * 16 + 16) * 16 + 16;
+constexpr int kNoAllocFloats = 2 * 1008 * 16 + 16;
 __device__ __align__(256) float scratch[kNoAllocFloats];
 
 // The array's device address on the current device, looked up once per device
@@ -407,7 +459,7 @@ int check_ap(const float* T, int n_v, const float* W, int L, const gbp_ap* ap) {
     return GBP_OK;
 }
 
-// the template constants for the chunk of `len` steps starting at step s0
+// the template constants for the `len` steps starting at step s0
 ApDev make_ap(const gbp_ap* a, int s0, int len) {
     ApDev d;
     d.K0 = a->K0;
@@ -421,50 +473,93 @@ ApDev make_ap(const gbp_ap* a, int s0, int len) {
     return d;
 }
 
-int chunk_pad(int len) { return (len + 15) / 16 * 16 + 16; }
+// Leads of a launch: the two column tiles that share the template, or one.
+int lead_tiles(int left) { return left > 16 ? 2 : 1; }
 
-// floats of forward scratch per instance: window and histogram of one chunk, weight sums
+// Floats of forward scratch per instance.  A launch of `len` steps takes
+// (tiles + 1) * NL doubles for the rows per time tile and NL for the weight sums; what
+// does not fit goes in several launches.
+constexpr size_t kWorkFloats = 2 * 1008 * 16 + 16;
 size_t ecg_work_floats(int n_steps) {
-    const int S_pad = chunk_pad(std::min(n_steps, kMaxChunk));
-    return (size_t)2 * S_pad * 16 + 16;
+    return std::min<size_t>(kWorkFloats, ((size_t)(n_steps + 15) / 16 + 2) * 64);
 }
+int max_len(size_t work_floats, int nl) { return ((int)(work_floats / 2 / nl) - 2) * 16; }
 
 struct EcgLaunch {
     const int* off;       // device offsets or nullptr
     int n_inst;
     int max_verts;        // largest instance
-    float* work;          // n_inst * ecg_work_floats(n_steps) floats
+    float* work;          // n_inst * work_floats floats
+    size_t work_floats;   // per instance
 };
 
-// Every (lead tile, time chunk) of the call: a forward chunk is an ECG on its own
-// time grid (the instance's rows of ecg are n_steps * L floats apart).
+// Vertices per block of the forward: two blocks to each of the 256 CUs at a time, as the
+// LDS allows, and one such round where 512 vertices a block suffice (143,564 vertices:
+// 320 a block 55 us, 256 63 us, 576 66 us; 500,103: 512 a block 40 us, 256 63 us).
+int fwd_verts(long long verts) {
+    return (int)std::min<long long>((verts + 512 * 64 - 1) / (512 * 64) * 64, 16 * kFwdSteps);
+}
+
+template <int NT>
+int ecg_forward_part(const EcgLaunch& el, const float* T, int n_v, const float* W, const LeadTile& lt, const ApDev& d,
+                     float* ecg, hipStream_t s) {
+    constexpr int NL = 16 * NT;
+    const int tiles = (d.S + 15) / 16;
+    double* g_hist = reinterpret_cast<double*>(el.work);
+    double* g_wsum = g_hist + (size_t)el.n_inst * (tiles + 1) * NL;
+    const int n_work = el.n_inst * (tiles + 2) * NL * 2;
+    const int zb = std::min((std::max(n_work, d.S * lt.Lt) + 1023) / 1024, 512);
+    k_ecg_zero<<<dim3(zb, el.n_inst), 256, 0, s>>>(el.work, n_work, ecg, lt, d.S);
+    const int vb = fwd_verts((long long)el.max_verts * el.n_inst);
+    {
+        ProfScope ps(GBP_PROF_ECG_FWD, s);
+        k_ecg_fwd<NT><<<dim3((el.max_verts + vb - 1) / vb, el.n_inst), kFwdThreads, fwd_lds(NT, vb), s>>>(
+            T, W, n_v, lt, d, vb, el.off, g_hist, g_wsum, ecg);
+    }
+    const int tpb = std::max(8, (tiles + 63) / 64);
+    k_ecg_finish<NL><<<dim3((tiles + tpb - 1) / tpb, el.n_inst), 1024, 0, s>>>(g_hist, g_wsum, d.S, lt, d.K0, tpb, ecg);
+    GBP_LAUNCH_CHECK();
+    return GBP_OK;
+}
+
+// More LDS than the default limit of 64 KB, once per device.
+int fwd_lds_limit() {
+    static std::mutex mu;
+    static bool set[64] = {};
+    int dev = 0;
+    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) {
+        gbp_set_error("no HIP device");
+        return GBP_ERR_HIP;
+    }
+    std::lock_guard<std::mutex> lk(mu);
+    if (set[dev]) return GBP_OK;
+    const int most = (int)fwd_lds(2, 16 * kFwdSteps);
+    GBP_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(&k_ecg_fwd<1>),
+                                hipFuncAttributeMaxDynamicSharedMemorySize, most));
+    GBP_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(&k_ecg_fwd<2>),
+                                hipFuncAttributeMaxDynamicSharedMemorySize, most));
+    set[dev] = true;
+    return GBP_OK;
+}
+
+// Every (leads, steps) part of the call: a part is an ECG on its own time grid (the
+// instance's rows of ecg are n_steps * L floats apart).
 int ecg_forward_launch(const EcgLaunch& el, const float* T, int n_v, const float* W, int L,
                        const gbp_ap* ap, float* ecg, hipStream_t s) {
     const int S = ap->n_steps;
-    for (int c0 = 0; c0 < L; c0 += 16) {
-        for (int s0 = 0; s0 < S; s0 += kMaxChunk) {
-            const int len = std::min(kMaxChunk, S - s0);
-            const ApDev d = make_ap(ap, s0, len);
-            const LeadTile lt{L, std::min(16, L - c0), (long long)S * L};
-            const int S_pad = chunk_pad(len);
-            float* g_win = el.work;
-            float* g_hist = el.work + (size_t)el.n_inst * S_pad * 16;
-            float* g_wsum = el.work + (size_t)2 * el.n_inst * S_pad * 16;
-            const int total = el.n_inst * (2 * S_pad * 16 + 16);
-            k_ecg_zero<<<std::min((total + 255) / 256, 1024), 256, 0, s>>>(el.work, total);
-            const int groups = (el.max_verts + 63) / 64;
-            const int gpb = 8;    // 64-vertex groups per block (2 per wave; 16 measured slower: fewer resident waves)
-            const dim3 grid((groups + gpb - 1) / gpb, el.n_inst);
-            const size_t lds = (size_t)S_pad * 16 * sizeof(float);
-            {
-                ProfScope ps(GBP_PROF_ECG_FWD, s);
-                k_ecg_fwd<<<grid, 256, lds, s>>>(T, W + c0, n_v, lt, d, S_pad, gpb, el.off, g_win,
-                                                 g_hist, g_wsum);
-            }
-            k_ecg_finish<<<el.n_inst, 1024, 0, s>>>(g_win, g_hist, g_wsum, len, S_pad, lt, d.K0,
-                                                    ecg + (size_t)s0 * L + c0);
-            GBP_LAUNCH_CHECK();
+    int rc = fwd_lds_limit();
+    if (rc) return rc;
+    for (int c0 = 0; c0 < L;) {
+        const int nt = lead_tiles(L - c0), most = max_len(el.work_floats, 16 * nt);
+        const LeadTile lt{L, std::min(16 * nt, L - c0), (long long)S * L};
+        for (int s0 = 0; s0 < S; s0 += most) {
+            const ApDev d = make_ap(ap, s0, std::min(most, S - s0));
+            float* out = ecg + (size_t)s0 * L + c0;
+            rc = nt == 2 ? ecg_forward_part<2>(el, T, n_v, W + c0, lt, d, out, s)
+                         : ecg_forward_part<1>(el, T, n_v, W + c0, lt, d, out, s);
+            if (rc) return rc;
         }
+        c0 += 16 * nt;
     }
     return GBP_OK;
 }
@@ -472,23 +567,16 @@ int ecg_forward_launch(const EcgLaunch& el, const float* T, int n_v, const float
 int ecg_backward_launch(const EcgLaunch& el, const float* T, int n_v, const float* W, int L,
                         const gbp_ap* ap, const float* G, float* dT, hipStream_t s) {
     const int S = ap->n_steps;
-    int first = 1;
-    for (int c0 = 0; c0 < L; c0 += 16) {
-        for (int s0 = 0; s0 < S; s0 += kMaxChunk) {
-            const int len = std::min(kMaxChunk, S - s0);
-            const ApDev d = make_ap(ap, s0, len);
-            const LeadTile lt{L, std::min(16, L - c0), (long long)S * L};
-            const int S_pad = chunk_pad(len);
-            const int groups = (el.max_verts + 63) / 64;
-            const dim3 grid(std::max(1, std::min((groups + 3) / 4, 2048 / std::max(1, el.n_inst) + 1)),
-                            el.n_inst);
-            const size_t lds = (size_t)2 * S_pad * 16 * sizeof(short);
-            ProfScope ps(GBP_PROF_ECG_BWD, s);
-            k_ecg_bwd<<<grid, 256, lds, s>>>(T, W + c0, G + (size_t)s0 * L + c0, n_v, lt, d, S_pad,
-                                             el.off, first ? 0 : 1, dT);
-            GBP_LAUNCH_CHECK();
-            first = 0;
-        }
+    const ApDev d = make_ap(ap, 0, S);
+    for (int c0 = 0; c0 < L;) {
+        const int nt = lead_tiles(L - c0);
+        const LeadTile lt{L, std::min(16 * nt, L - c0), (long long)S * L};
+        const dim3 grid((el.max_verts + kBwdVerts - 1) / kBwdVerts, el.n_inst);
+        ProfScope ps(GBP_PROF_ECG_BWD, s);
+        (nt == 2 ? k_ecg_bwd<2> : k_ecg_bwd<1>)<<<grid, kBwdThreads, 0, s>>>(T, W + c0, G + c0, n_v, lt, d, el.off,
+                                                                            c0 > 0, dT);
+        GBP_LAUNCH_CHECK();
+        c0 += 16 * nt;
     }
     return GBP_OK;
 }
@@ -581,7 +669,7 @@ extern "C" int gbp_ecg_forward(const float* T, int n_v, const float* W, int L, c
     }
     float* work;
     if ((rc = ecg_workspace(ecg_work_floats(ap->n_steps), &work))) return rc;
-    return ecg_forward_launch(EcgLaunch{nullptr, 1, n_v, work}, T, n_v, W, L, ap, ecg,
+    return ecg_forward_launch(EcgLaunch{nullptr, 1, n_v, work, ecg_work_floats(ap->n_steps)}, T, n_v, W, L, ap, ecg,
                               (hipStream_t)stream);
 }
 
@@ -593,15 +681,9 @@ extern "C" int gbp_ecg_forward_noalloc(const float* T, int n_v, const float* W, 
         gbp_set_error("ecg is NULL");
         return GBP_ERR_ARG;
     }
-    const size_t need = ecg_work_floats(ap->n_steps);
-    if (need > (size_t)kNoAllocFloats) {
-        gbp_set_error("ECG (no allocation): needs %zu scratch floats, the library holds %d", need,
-                      kNoAllocFloats);
-        return GBP_ERR_ARG;
-    }
     float* work;
     if ((rc = noalloc_scratch(&work))) return rc;
-    return ecg_forward_launch(EcgLaunch{nullptr, 1, n_v, work}, T, n_v, W, L, ap, ecg,
+    return ecg_forward_launch(EcgLaunch{nullptr, 1, n_v, work, kNoAllocFloats}, T, n_v, W, L, ap, ecg,
                               (hipStream_t)stream);
 }
 
@@ -613,7 +695,7 @@ extern "C" int gbp_ecg_backward(const float* T, int n_v, const float* W, int L, 
         gbp_set_error("dL_decg and dL_dT are required");
         return GBP_ERR_ARG;
     }
-    return ecg_backward_launch(EcgLaunch{nullptr, 1, n_v, nullptr}, T, n_v, W, L, ap, dL_decg, dL_dT,
+    return ecg_backward_launch(EcgLaunch{nullptr, 1, n_v, nullptr, 0}, T, n_v, W, L, ap, dL_decg, dL_dT,
                                (hipStream_t)stream);
 }
 
@@ -626,7 +708,7 @@ extern "C" int gbp_ecg_forward_batched(gbp_batch b, const float* T, const float*
         gbp_set_error("ecg is NULL");
         return GBP_ERR_ARG;
     }
-    return ecg_forward_launch(EcgLaunch{b->off, b->n_inst, b->max_verts, b->work}, T, b->total, W,
+    return ecg_forward_launch(EcgLaunch{b->off, b->n_inst, b->max_verts, b->work, ecg_work_floats(b->max_steps)}, T, b->total, W,
                               L, ap, ecg, (hipStream_t)stream);
 }
 
@@ -640,6 +722,6 @@ extern "C" int gbp_ecg_backward_batched(gbp_batch b, const float* T, const float
         gbp_set_error("dL_decg and dL_dT are required");
         return GBP_ERR_ARG;
     }
-    return ecg_backward_launch(EcgLaunch{b->off, b->n_inst, b->max_verts, nullptr}, T, b->total, W,
+    return ecg_backward_launch(EcgLaunch{b->off, b->n_inst, b->max_verts, nullptr, 0}, T, b->total, W,
                                L, ap, dL_decg, dL_dT, (hipStream_t)stream);
 }
