@@ -161,7 +161,6 @@ __global__ void __launch_bounds__(kFwdThreads)
     // weights: two vertices a thread, split and stored as the B operand reads them, and
     // summed: over a step's finite times (saturation), over all of them (rest)
     float all = 0.f;
-#pragma unroll 4
     for (int e = tid; e < vb / 2 * NL; e += kFwdThreads) {   // whole waves
         const int l = e % NL, n = 2 * (e / NL);
         const float* w = W + min(l, Lt - 1);

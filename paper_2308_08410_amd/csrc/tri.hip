@@ -14,9 +14,8 @@
 //   (geometric convergence there), and the gradients w.r.t. the triangle tensors,
 //   nodal velocity scales and root onsets.
 //
-// Meshes of the 2-D study are small (thousands of vertices); the kernels keep
-// the tetrahedral path's structure (queue, block-aggregated counters) without its
-// XCD and LDS-gather refinements.
+// Meshes of the 2-D study are small (thousands of vertices) and their fronts narrow, so the
+// forward's rounds run inside one launch.
 #include <math.h>
 
 #include <algorithm>
@@ -27,15 +26,25 @@
 
 #include "gbp_internal.h"
 #include "local_solve.h"
+#include "team.h"
 #include "walk.h"
 
 struct TriCtl {
-    int count[3];
+    int count;           // forward: vertices around the roots
     int err;
     unsigned long long solves, updates;
     int unreached;
     AdjCtl adj;          // adjoint walk
-    int rounds;          // forward: last round with work + 1
+    int rounds;          // forward: rounds with work
+    int left;            // forward: queued vertices after the last
+};
+
+// Incidence of a vertex: the triangle's other two (in increasing local order) and the Q of
+// the edges to them with the roots of its diagonal.
+struct __align__(32) TriInc {
+    int a, b;
+    float qaa, qbb, qab, sa, sb;
+    int pad;
 };
 
 struct gbp_tri_plan_s {
@@ -48,14 +57,19 @@ struct gbp_tri_plan_s {
     int* nbp = nullptr;           // [n_v+1] unique neighbours
     int* nb = nullptr;
     float4* minv = nullptr;       // [n_t] D_eff^-1 (xx, yy, xy) and sbar
+    int4* info = nullptr;         // incidence and neighbour ranges of a vertex
+    int* tpos = nullptr;          // [3 n_t] position of a triangle's incidences
+    TriInc* inc = nullptr;        // [3 n_t] as vent; of the forward's metric
+    int max_deg = 0;              // most neighbours of a vertex
     float* T = nullptr;
+    int* now[2] = {nullptr, nullptr};   // a team's times, and each round's improvements
+    unsigned long long* gain[2] = {nullptr, nullptr};
     float* troot = nullptr;
-    int* q[2] = {nullptr, nullptr};
+    int* q0 = nullptr;            // first queue of the forward, leaves of the adjoint
+    int* q[2] = {nullptr, nullptr};   // a team's lists
     int* mark = nullptr;
     TriCtl* ctl = nullptr;
     TriCtl* ctl_host = nullptr;
-    TriCtl* ctl_pipe = nullptr;   // pinned [2]: control block after each batch of rounds
-    hipEvent_t ev[2] = {nullptr, nullptr};
     int* par = nullptr;
     int4* pnode = nullptr;        // weighted parents a, b (-1: none)
     float4* pa = nullptr;         // alpha_a, alpha_b, best, root_self
@@ -101,27 +115,32 @@ void tri_free(gbp_tri_plan p) {
                     p->T,     p->troot, p->q[0],   p->q[1],   p->mark,   p->ctl,    p->par,
                     p->pnode, p->pa,    p->crange, p->cfill,  p->cchild, p->calpha, p->lam,
                     p->g,     p->dsbar, p->done,   p->rec,    p->over,
-                    p->ready[0], p->ready[1], p->team};
+                    p->ready[0], p->ready[1], p->team, p->info, p->tpos, p->inc, p->q0, p->now[0], p->now[1], p->gain[0],
+                    p->gain[1]};
     for (void* q : ptrs)
         if (q) (void)hipFree(q);
     if (p->ctl_host) (void)hipHostFree(p->ctl_host);
-    if (p->ctl_pipe) (void)hipHostFree(p->ctl_pipe);
-    for (hipEvent_t e : p->ev)
-        if (e) (void)hipEventDestroy(e);
     delete p;
 }
 
 __device__ __forceinline__ bool fin(float x) { return x - x == 0.f; }
 
+// Floats as integers of the same order.
+__device__ __forceinline__ int ordered(float x) {
+    const int b = __float_as_int(x);
+    return b < 0 ? b ^ 0x7fffffff : b;
+}
+__device__ __forceinline__ float from_ordered(int b) { return __int_as_float(b < 0 ? b ^ 0x7fffffff : b); }
+
 // block reductions (one atomic per block instead of one per thread)
 __device__ __forceinline__ unsigned long long tri_block_sum(unsigned long long v) {
-    __shared__ unsigned long long part[TPB / 64];
+    __shared__ unsigned long long part[16];
     for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
     __syncthreads();
     if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = v;
     __syncthreads();
     unsigned long long t = 0;
-    for (int w = 0; w < TPB / 64; ++w) t += part[w];
+    for (int w = 0; w < (int)blockDim.x / 64; ++w) t += part[w];
     return t;
 }
 
@@ -135,13 +154,14 @@ __device__ __forceinline__ void tri_face(int4 t, int k, int& i, int& a, int& b) 
 
 // d = 2 local solve in precision R: vertex a, vertex b, interior (first wins on
 // ties); unreached vertices leave the other vertex's candidate.
+// sa, sb: the roots of qaa and qbb.
 template <typename R>
-__device__ __forceinline__ R tri_local(R qaa, R qbb, R qab, R pa, R pb, R* alpha_a = nullptr) {
+__device__ __forceinline__ R tri_local(R qaa, R qbb, R qab, R sa, R sb, R pa, R pb, R* alpha_a = nullptr) {
     const R INF = gbp_inf<R>();
     const bool fa = pa < INF, fb = pb < INF;
-    R best = fa ? pa + gbp_sqrt(qaa) : INF;
+    R best = fa ? pa + sa : INF;
     R al = fa ? R(1) : R(0);
-    const R vb = fb ? pb + gbp_sqrt(qbb) : INF;
+    const R vb = fb ? pb + sb : INF;
     if (vb < best) { best = vb; al = R(0); }
     if (fa && fb) {
         const R m = fmin(pa, pb);
@@ -153,9 +173,11 @@ __device__ __forceinline__ R tri_local(R qaa, R qbb, R qab, R pa, R pb, R* alpha
     return best;
 }
 
+// inc (or null): the record of each of the triangle's incidences, at tpos.
 __global__ void k_tri_metric(const float* __restrict__ D, const float* __restrict__ vscale,
                              const int4* __restrict__ tri, int n_t, float4* __restrict__ minv,
-                             TriCtl* ctl) {
+                             const float2* __restrict__ xy, const int* __restrict__ tpos,
+                             TriInc* __restrict__ inc, TriCtl* ctl) {
     const int t = blockIdx.x * blockDim.x + threadIdx.x;
     if (t >= n_t) return;
     const int4 v = tri[t];
@@ -166,17 +188,36 @@ __global__ void k_tri_metric(const float* __restrict__ D, const float* __restric
             atomicOr(&ctl->err, ERRBIT_VSCALE);
         sbar = (s0 + s1 + s2) * (1.f / 3.f);
     }
-    const float xx = D[3 * (size_t)t], yy = D[3 * (size_t)t + 1], xy = D[3 * (size_t)t + 2];
-    const float det = xx * yy - xy * xy;
-    if (!(fin(xx) && fin(yy) && fin(xy))) atomicOr(&ctl->err, ERRBIT_D_NONFINITE);
+    const float xx = D[3 * (size_t)t], yy = D[3 * (size_t)t + 1], dxy = D[3 * (size_t)t + 2];
+    const float det = xx * yy - dxy * dxy;
+    if (!(fin(xx) && fin(yy) && fin(dxy))) atomicOr(&ctl->err, ERRBIT_D_NONFINITE);
     else if (!(xx > 0.f && det > 0.f)) atomicOr(&ctl->err, ERRBIT_D_NOT_SPD);
     const float s = 1.f / (det * sbar * sbar);
-    minv[t] = make_float4(yy * s, xx * s, -xy * s, sbar);
+    const float4 m = make_float4(yy * s, xx * s, -dxy * s, sbar);
+    minv[t] = m;
+    if (!inc) return;
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+        int i, a, b;
+        tri_face(v, k, i, a, b);
+        const float2 xi = xy[i], xa = xy[a], xb = xy[b];
+        const float ax = xa.x - xi.x, ay = xa.y - xi.y, bx = xb.x - xi.x, by = xb.y - xi.y;
+        TriInc r;
+        r.a = a;
+        r.b = b;
+        r.qaa = ax * (m.x * ax + m.z * ay) + ay * (m.z * ax + m.y * ay);
+        r.qbb = bx * (m.x * bx + m.z * by) + by * (m.z * bx + m.y * by);
+        r.qab = ax * (m.x * bx + m.z * by) + ay * (m.z * bx + m.y * by);
+        r.sa = gbp_sqrt(r.qaa);
+        r.sb = gbp_sqrt(r.qbb);
+        r.pad = 0;
+        inc[tpos[3 * (size_t)t + k]] = r;
+    }
 }
 
 __global__ void k_tri_roots(const int* __restrict__ root_node, const float* __restrict__ root_t,
                             int n_roots, int n_v, float* __restrict__ troot, float* __restrict__ T,
-                            int cold, const int* __restrict__ nbp, const int* __restrict__ nb,
+                            int* __restrict__ now0, int* __restrict__ now1, int cold, const int* __restrict__ nbp, const int* __restrict__ nb,
                             int* __restrict__ q0, int* __restrict__ mark, int stamp, TriCtl* ctl) {
     if (threadIdx.x == 0) {
         for (int r = 0; r < n_roots; ++r) {
@@ -186,6 +227,7 @@ __global__ void k_tri_roots(const int* __restrict__ root_node, const float* __re
             if (!fin(t)) { atomicOr(&ctl->err, ERRBIT_ROOT_NONFINITE); continue; }
             troot[u] = fminf(troot[u], t);
             if (cold) T[u] = fminf(T[u], t);
+            if (now0) now0[u] = now1[u] = ordered(T[u]);
         }
     }
     __syncthreads();
@@ -195,108 +237,220 @@ __global__ void k_tri_roots(const int* __restrict__ root_node, const float* __re
         if (u < 0 || u >= n_v) continue;
         for (int a = nbp[u]; a < nbp[u + 1]; ++a) {
             const int w = nb[a];
-            if (atomicMax(&mark[w], stamp) < stamp) q0[atomicAdd(&ctl->count[0], 1)] = w;
+            if (atomicMax(&mark[w], stamp) < stamp) q0[atomicAdd(&ctl->count, 1)] = w;
         }
     }
 }
 
-// Lanes per queued vertex in a relaxation round: the lanes of a group take the
-// vertex's triangles (and then its neighbours) in turn, so a round's chain of
-// dependent loads is one triangle's, not the sum over the vertex's triangles.
-// Narrow fronts (at most kNarrowFront queued vertices) take 8 lanes per vertex,
-// wider ones 4: the round is latency-bound when the front is narrow and bound by
-// the waves it issues when it is wide.
-constexpr int kNarrowFront = 1024;
+// ------------------------------------------------------------------ relaxation rounds
+// One queued vertex by a group of 8 lanes, which take its triangles (and then its
+// neighbours) in turn: a round is a chain of dependent loads, one triangle's and not the
+// sum over the vertex's.  The chain is queue -> info -> records (the two other
+// vertices and their Q, computed with the metric) -> T -> solve -> marks; the neighbours
+// are read with the records.  (4 lanes: 6% slower at 2,700 nodes, 3% at 250,000.)
+constexpr int kTriLanes = 8;
 
-template <int L>
-__device__ __forceinline__ void tri_relax(const float2* __restrict__ xy, const int4* __restrict__ tri,
-                                          const float4* __restrict__ minv, const int* __restrict__ vptr,
-                                          const int* __restrict__ vent, const int* __restrict__ nbp,
-                                          const int* __restrict__ nb, float* T, const int* __restrict__ qin,
-                                          int n, int* __restrict__ qout, int* __restrict__ mark,
-                                          int* cnt_next, int stamp_next, float eps_rel, int* pbuf,
-                                          int* pn, int cap, unsigned long long& solves,
-                                          unsigned long long& upd) {
-    const int lane = threadIdx.x & (L - 1);
-    // k is the same in every lane of a group, so a group runs its passes together
-    for (int k = (blockIdx.x * TPB + threadIdx.x) / L; k < n; k += gridDim.x * (TPB / L)) {
-        const int i = qin[k];
-        const float told = T[i];
-        float best = told;
-        const float2 xi = xy[i];
-        for (int e = vptr[i] + lane; e < vptr[i + 1]; e += L) {
-            const int code = vent[e];
-            const int t = code >> 2;
-            int ii, a, b;
-            tri_face(tri[t], code & 3, ii, a, b);
-            const float4 m = minv[t];
-            const float2 xa = xy[a], xb = xy[b];
-            const float ax = xa.x - xi.x, ay = xa.y - xi.y, bx = xb.x - xi.x, by = xb.y - xi.y;
-            const float qaa = ax * (m.x * ax + m.z * ay) + ay * (m.z * ax + m.y * ay);
-            const float qbb = bx * (m.x * bx + m.z * by) + by * (m.z * bx + m.y * by);
-            const float qab = ax * (m.x * bx + m.z * by) + ay * (m.z * bx + m.y * by);
-            best = fminf(best, tri_local<float>(qaa, qbb, qab, T[a], T[b]));
-            ++solves;
-        }
+struct TriRelax {
+    const int4* info;     // per vertex: its incidences [x, y), its neighbours [z, w)
+    const TriInc* inc;
+    const int* nb;
+    float eps_rel;
+};
+
+// A round is a Jacobi step: all its vertices see the times of the round before, so that
+// times and the parents chosen by them do not depend on which vertex was first.
+template <typename Load, typename Done, typename Push>
+__device__ __forceinline__ void tri_vertex(const TriRelax& g, int i, Load load, Done done, Push push,
+                                           unsigned& solves, unsigned& upd) {
+    const int lane = threadIdx.x & (kTriLanes - 1);
+    const int4 at = g.info[i];
+    const int w0 = at.z + lane < at.w ? g.nb[at.z + lane] : -1;
+    const float told = load(i);
+    float best = told;
+    for (int e = at.x + lane; e < at.y; e += kTriLanes) {
+        const int4* r = reinterpret_cast<const int4*>(g.inc + e);
+        const int4 r0 = r[0], r1 = r[1];
+        best = fminf(best, tri_local<float>(__int_as_float(r0.z), __int_as_float(r0.w), __int_as_float(r1.x),
+                                            __int_as_float(r1.y), __int_as_float(r1.z), load(r0.x), load(r0.y)));
+        ++solves;
+    }
 #pragma unroll
-        for (int o = 1; o < L; o <<= 1) best = fminf(best, __shfl_xor(best, o));
-        const bool changed = (told < GBP_INF) ? (best < told - eps_rel * fmaxf(1.f, fabsf(told)))
-                                              : (best < GBP_INF);
-        if (lane == 0 && best < told) T[i] = best;
-        if (changed) {
-            if (lane == 0) ++upd;
-            for (int a = nbp[i] + lane; a < nbp[i + 1]; a += L) {
-                const int w = nb[a];
-                if (atomicMax(&mark[w], stamp_next) < stamp_next) {
-                    const int pos = atomicAdd(pn, 1);
-                    if (pos < cap) pbuf[pos] = w;
-                    else qout[atomicAdd(cnt_next, 1)] = w;     // buffer full: straight to the queue
-                }
-            }
-        }
+    for (int o = 1; o < kTriLanes; o <<= 1) best = fminf(best, __shfl_xor(best, o));
+    if (lane == 0) done(best, best < told);
+    const bool changed = (told < GBP_INF) ? (best < told - g.eps_rel * fmaxf(1.f, fabsf(told)))
+                                          : (best < GBP_INF);
+    if (!changed) return;
+    if (lane == 0) ++upd;
+    if (w0 >= 0) push(w0);
+    for (int a = at.z + lane + kTriLanes; a < at.w; a += kTriLanes) push(g.nb[a]);
+}
+
+// Narrow fronts: all rounds by one block, with T, the queues and their marks in LDS and a
+// block barrier between rounds.  Bound by the solves of one CU (2,704 nodes, 240 queued
+// vertices a round: 3.6 us a round; as a launch a round 5.3 us and the gap to the next).
+// An iteration by one block and by a team takes 666 and 755 us at 2,700 nodes, 798 and
+// 770 at 4,000, 1237 and 1010 at 8,000.
+constexpr int kTriBlockVerts = 4096;
+constexpr int kTriThreads = 1024;
+
+constexpr size_t tri_block_lds(int n_v) { return (size_t)n_v * 12 + 2 * (((size_t)n_v + 31) / 32) * 4 + 16; }
+
+__global__ void __launch_bounds__(kTriThreads)
+    k_tri_rounds_block(TriRelax g, int n_v, float* __restrict__ T, const int* __restrict__ q0, TriCtl* ctl, int rounds) {
+    extern __shared__ float lds[];
+    const int words = (n_v + 31) / 32, tid = threadIdx.x;
+    float* Ts = lds;
+    float* Tn = Ts + n_v;                                                            // by queue position
+    unsigned* queued = reinterpret_cast<unsigned*>(Tn + n_v);                        // [2][words]
+    unsigned short* q = reinterpret_cast<unsigned short*>(queued + 2 * words);       // [2][n_v]
+    __shared__ int count[3];
+    if (ctl->err) return;
+    for (int i = tid; i < n_v; i += kTriThreads) Ts[i] = T[i];
+    for (int i = tid; i < 2 * words; i += kTriThreads) queued[i] = 0;
+    const int n0 = ctl->count;
+    for (int i = tid; i < n0; i += kTriThreads) q[i] = (unsigned short)q0[i];
+    if (tid < 3) count[tid] = tid == 0 ? n0 : 0;
+    __syncthreads();
+    unsigned solves = 0, upd = 0;
+    unsigned long long all_solves = 0, all_upd = 0;
+    int r = 0, n = n0;
+    while (n > 0 && r < rounds) {
+        const unsigned short* in = q + (size_t)(r & 1) * n_v;
+        unsigned short* out = q + (size_t)((r + 1) & 1) * n_v;
+        unsigned* mark = queued + ((r + 1) & 1) * words;
+        int* n_out = &count[(r + 1) % 3];
+        if (tid == 0) count[(r + 2) % 3] = 0;
+        for (int i = tid; i < words; i += kTriThreads) queued[(r & 1) * words + i] = 0;
+        for (int k = tid / kTriLanes; k < n; k += kTriThreads / kTriLanes)
+            tri_vertex(g, in[k], [&](int x) { return Ts[x]; }, [&](float t, bool) { Tn[k] = t; },
+                       [&](int x) {
+                           const unsigned bit = 1u << (x & 31);
+                           if (!(atomicOr(mark + (x >> 5), bit) & bit)) out[atomicAdd(n_out, 1)] = (unsigned short)x;
+                       },
+                       solves, upd);
+        __syncthreads();
+        for (int k = tid; k < n; k += kTriThreads) Ts[in[k]] = Tn[k];
+        all_solves += solves;
+        all_upd += upd;
+        solves = upd = 0;
+        __syncthreads();
+        ++r;
+        n = count[r % 3];
+    }
+    for (int i = tid; i < n_v; i += kTriThreads) T[i] = Ts[i];
+    all_solves = tri_block_sum(all_solves);
+    all_upd = tri_block_sum(all_upd);
+    if (tid == 0) {
+        ctl->solves = all_solves;
+        ctl->updates = all_upd;
+        ctl->rounds = r;
+        ctl->left = n;
     }
 }
 
-// one relaxation round over the queue qin; the grid covers kNarrowFront vertices
-// at 8 lanes each or the mesh, whichever is less
-__global__ void __launch_bounds__(TPB)
-    k_tri_sweep(const float2* __restrict__ xy, const int4* __restrict__ tri,
-                const float4* __restrict__ minv, const int* __restrict__ vptr,
-                const int* __restrict__ vent, const int* __restrict__ nbp,
-                const int* __restrict__ nb, float* T, const int* __restrict__ qin,
-                int* __restrict__ qout, int* __restrict__ mark, TriCtl* ctl, int s, int stamp_next,
-                float eps_rel) {
-    const int n = ctl->count[s % 3];
-    if (blockIdx.x == 0 && threadIdx.x == 0) {
-        ctl->count[(s + 2) % 3] = 0;
-        if (n > 0) atomicMax(&ctl->rounds, s + 1);
+// Wider ones: all rounds by a team of blocks; member b writes its pushes to
+// list[cap * b ...], read with the prefix of the members' counts.  A member's share of n
+// vertices pushes at most as many times their largest number of neighbours.
+// Round r reads the times of `now[r & 1]` and lowers those of the other array, which holds
+// the improvements of all rounds but the last; a member repeats its own of that one
+// (gain, by position in the round's queue) before it adds its new ones.
+// Bound by the chain of agent-scope accesses and, with many thousand vertices a round, by
+// their number: 250,000 nodes (12,000 vertices a round), 8.3 us a round and 12.8 us as a
+// launch a round; an iteration takes 7.6 ms with 128 blocks, 7.9 with 64, 8.1 with 256;
+// at 60,000 nodes 2.99, 2.88 and 3.4; at 8,000 1011 us with 32 blocks, 1031 with 64.
+// (Blocks of one XCD only: 11.6 ms at 250,000, 1087 us at 8,000.)
+int tri_team_blocks(int n_v) { return n_v < 24576 ? 32 : n_v < 163840 ? 64 : 128; }
+
+__host__ __device__ inline size_t tri_list_cap(int n_v, int max_deg, int size) {
+    const size_t most = ((size_t)n_v / size + 1) * max_deg;
+    return most < (size_t)n_v ? most : (size_t)n_v;
+}
+
+// Room for a team of any number of blocks.
+size_t tri_list_size(int n_v, int max_deg) {
+    size_t most = 0;
+    for (int size = 1; size <= kTeamMax; ++size) most = std::max(most, size * tri_list_cap(n_v, max_deg, size));
+    return most;
+}
+
+struct TriLists {
+    int *now0, *now1;                    // [n_v] times, as ordered integers
+    unsigned long long *gain0, *gain1;   // [n_v] vertex << 32 | its time, or all ones
+    int *list0, *list1;
+    const int* q0;
+    int* mark;
+};
+
+__global__ void __launch_bounds__(kTriThreads)
+    k_tri_rounds_team(TriRelax g, int n_v, int max_deg, TriLists q, int stamp, TeamCtl* team, TriCtl* ctl, int rounds,
+                      float* __restrict__ T) {
+    __shared__ int before[kTeamMax + 1], count[3];
+    if (ctl->err) return;
+    if (threadIdx.x < 3) count[threadIdx.x] = 0;
+    Team t;
+    if (!team_join(team, false, t)) return;
+    const size_t cap = tri_list_cap(n_v, max_deg, t.size);
+    int n = ctl->count, r = 0, m = 0, p0 = 0, p1 = 0;
+    unsigned long long all_solves = 0, all_upd = 0;
+    while (n > 0 && r < rounds) {
+        const bool odd = r & 1;
+        const int* in = odd ? q.list1 : q.list0;
+        int* out = (odd ? q.list0 : q.list1) + cap * t.rank;
+        int* n_out = &count[(r + 1) % 3];
+        const int* T0 = odd ? q.now1 : q.now0;
+        int* T1 = odd ? q.now0 : q.now1;
+        const unsigned long long* last = odd ? q.gain0 : q.gain1;
+        unsigned long long* gain = odd ? q.gain1 : q.gain0;
+        for (int k = p0 + (int)threadIdx.x; k < p1; k += kTriThreads) {
+            const unsigned long long v = agent_load(last + k);
+            if (v != ~0ull)
+                (void)__hip_atomic_fetch_min(T1 + (int)(v >> 32), (int)(unsigned)v, __ATOMIC_RELAXED,
+                                             __HIP_MEMORY_SCOPE_AGENT);
+        }
+        const int next = stamp + r + 1;
+        unsigned solves = 0, upd = 0;
+        team_share(t, n, p0, p1);
+        for (int k = p0 + threadIdx.x / kTriLanes; k < p1; k += kTriThreads / kTriLanes) {
+            int i;
+            if (r == 0) {
+                i = q.q0[k];
+            } else {
+                while (before[m + 1] <= k) ++m;
+                i = agent_load(in + cap * m + (k - before[m]));
+            }
+            tri_vertex(g, i, [&](int x) { return from_ordered(agent_load(T0 + x)); },
+                       [&](float best, bool lower) {
+                           const int b = ordered(best);
+                           const unsigned long long v = lower ? ((unsigned long long)(unsigned)i << 32) | (unsigned)b : ~0ull;
+                           __hip_atomic_store(gain + k, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                           if (lower)
+                               (void)__hip_atomic_fetch_min(T1 + i, b, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                       },
+                       [&](int x) {
+                           if (__hip_atomic_fetch_max(q.mark + x, next, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < next)
+                               agent_store(out + atomicAdd(n_out, 1), x);
+                       },
+                       solves, upd);
+        }
+        all_solves += solves;
+        all_upd += upd;
+        ++r;
+        n = team_sync(t, r, n_out, before, m);
+        if (threadIdx.x == 0) count[(r + 2) % 3] = 0;   // read by all before the sync, used after the next
     }
-    const bool narrow = n <= kNarrowFront;
-    if ((int)(blockIdx.x * (narrow ? TPB / 8 : TPB / 4)) >= n) return;   // uniform over the block
-    // pushes collect in LDS; one atomic per block reserves their room in the queue
-    constexpr int kCap = 4096;
-    __shared__ int pbuf[kCap];
-    __shared__ int pn, pbase;
-    int* cnt_next = &ctl->count[(s + 1) % 3];
-    if (threadIdx.x == 0) pn = 0;
-    __syncthreads();
-    unsigned long long solves = 0, upd = 0;
-    if (narrow)
-        tri_relax<8>(xy, tri, minv, vptr, vent, nbp, nb, T, qin, n, qout, mark, cnt_next, stamp_next, eps_rel,
-                     pbuf, &pn, kCap, solves, upd);
-    else
-        tri_relax<4>(xy, tri, minv, vptr, vent, nbp, nb, T, qin, n, qout, mark, cnt_next, stamp_next, eps_rel,
-                     pbuf, &pn, kCap, solves, upd);
-    __syncthreads();
-    const int m = min(pn, kCap);
-    if (threadIdx.x == 0) pbase = m > 0 ? atomicAdd(cnt_next, m) : 0;
-    __syncthreads();
-    for (int k = threadIdx.x; k < m; k += blockDim.x) qout[pbase + k] = pbuf[k];
-    solves = tri_block_sum(solves);
-    upd = tri_block_sum(upd);
+    const int* T0 = r & 1 ? q.now1 : q.now0;
+    int i0, i1;
+    team_share(t, n_v, i0, i1);
+    for (int i = i0 + (int)threadIdx.x; i < i1; i += kTriThreads) T[i] = from_ordered(agent_load(T0 + i));
+    all_solves = tri_block_sum(all_solves);
+    all_upd = tri_block_sum(all_upd);
     if (threadIdx.x == 0) {
-        if (solves) atomicAdd(&ctl->solves, solves);
-        if (upd) atomicAdd(&ctl->updates, upd);
+        atomicAdd(&ctl->solves, all_solves);
+        atomicAdd(&ctl->updates, all_upd);
+        if (t.rank == 0) {
+            ctl->rounds = r;
+            ctl->left = n;
+        }
     }
 }
 
@@ -309,6 +463,16 @@ __global__ void k_tri_ctl_reset(TriCtl* ctl, TeamCtl* team) {
 __global__ void k_tri_fill(float* __restrict__ x, float v, int n) {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i < n) x[i] = v;
+}
+
+// No onset and, for a cold start, no time anywhere (now0, now1: a team's, or null).
+__global__ void k_tri_unreached(float* __restrict__ troot, float* __restrict__ T, int* __restrict__ now0,
+                                int* __restrict__ now1, int n_v) {
+    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= n_v) return;
+    troot[i] = GBP_INF;
+    if (T) T[i] = GBP_INF;
+    if (now0) now0[i] = now1[i] = __float_as_int(GBP_INF);
 }
 
 __global__ void k_tri_fill_i(int* __restrict__ x, int v, int n) {
@@ -360,7 +524,7 @@ __global__ void k_tri_parent(const float2* __restrict__ xy, const int4* __restri
             const double ta = T[a] < GBP_INF ? (double)T[a] : gbp_inf<double>();
             const double tb = T[b] < GBP_INF ? (double)T[b] : gbp_inf<double>();
             double al;
-            const double v = tri_local<double>(qaa, qbb, qab, ta, tb, &al);
+            const double v = tri_local<double>(qaa, qbb, qab, gbp_sqrt(qaa), gbp_sqrt(qbb), ta, tb, &al);
             if (pass == 0) {
                 best = fmin(best, v);
             } else if (v <= best + tol && v < gbp_inf<double>()) {
@@ -475,11 +639,12 @@ int tri_prepare(gbp_tri_plan p, const float* D, const float* vscale, const int32
         k_tri_fill_i<<<gbp_blocks(n_v, TPB), TPB, 0, s>>>(p->mark, 0, n_v);
         p->stamp = 1;
     }
-    k_tri_metric<<<gbp_blocks(p->n_t, TPB), TPB, 0, s>>>(D, vscale, p->tri, p->n_t, p->minv, p->ctl);
-    k_tri_fill<<<gbp_blocks(n_v, TPB), TPB, 0, s>>>(p->troot, GBP_INF, n_v);
-    if (cold) k_tri_fill<<<gbp_blocks(n_v, TPB), TPB, 0, s>>>(p->T, GBP_INF, n_v);
-    k_tri_roots<<<1, TPB, 0, s>>>(root_node, root_t, n_roots, n_v, p->troot, p->T, cold ? 1 : 0,
-                                  p->nbp, p->nb, p->q[0], p->mark, p->stamp, p->ctl);
+    k_tri_metric<<<gbp_blocks(p->n_t, TPB), TPB, 0, s>>>(D, vscale, p->tri, p->n_t, p->minv, p->xy, p->tpos,
+                                                       cold ? p->inc : nullptr, p->ctl);
+    k_tri_unreached<<<gbp_blocks(n_v, TPB), TPB, 0, s>>>(p->troot, cold ? p->T : nullptr,
+                                                         cold ? p->now[0] : nullptr, p->now[1], n_v);
+    k_tri_roots<<<1, TPB, 0, s>>>(root_node, root_t, n_roots, n_v, p->troot, p->T, cold ? p->now[0] : nullptr,
+                                  p->now[1], cold ? 1 : 0, p->nbp, p->nb, p->q0, p->mark, p->stamp, p->ctl);
     GBP_LAUNCH_CHECK();
     return GBP_OK;
 }
@@ -519,14 +684,18 @@ extern "C" int gbp_tri_plan_create(const float* xy, int n_v, const int32_t* tris
         }
     }
     // incidence (sorted by triangle within a vertex) and unique neighbours
-    std::vector<int> vptr(n_v + 1, 0), vent((size_t)3 * n_t);
+    std::vector<int> vptr(n_v + 1, 0), vent((size_t)3 * n_t), tpos((size_t)3 * n_t);
     for (int t = 0; t < n_t; ++t)
         for (int k = 0; k < 3; ++k) vptr[tris[3 * (size_t)t + k] + 1]++;
     for (int i = 0; i < n_v; ++i) vptr[i + 1] += vptr[i];
     {
         std::vector<int> cur(vptr.begin(), vptr.end() - 1);
         for (int t = 0; t < n_t; ++t)
-            for (int k = 0; k < 3; ++k) vent[cur[tris[3 * (size_t)t + k]]++] = (t << 2) | k;
+            for (int k = 0; k < 3; ++k) {
+                const int e = cur[tris[3 * (size_t)t + k]]++;
+                vent[e] = (t << 2) | k;
+                tpos[3 * (size_t)t + k] = e;
+            }
     }
     std::vector<int> nbp(n_v + 1, 0), nb;
     nb.reserve((size_t)6 * n_v);
@@ -543,6 +712,12 @@ extern "C" int gbp_tri_plan_create(const float* xy, int n_v, const int32_t* tris
         nb.insert(nb.end(), tmp.begin(), tmp.end());
         nbp[i + 1] = (int)nb.size();
     }
+    std::vector<int4> info(n_v);
+    int max_deg = 0;
+    for (int i = 0; i < n_v; ++i) {
+        info[i] = make_int4(vptr[i], vptr[i + 1], nbp[i], nbp[i + 1]);
+        max_deg = std::max(max_deg, nbp[i + 1] - nbp[i]);
+    }
     std::vector<float2> xy2(n_v);
     for (int i = 0; i < n_v; ++i) xy2[i] = make_float2(xy[2 * i], xy[2 * i + 1]);
     std::vector<int4> t4(n_t);
@@ -553,6 +728,7 @@ extern "C" int gbp_tri_plan_create(const float* xy, int n_v, const int32_t* tris
     (void)hipGetDevice(&p->device);
     p->n_v = n_v;
     p->n_t = n_t;
+    p->max_deg = max_deg;
     int rc = GBP_OK;
 #define TRI_TRY(x)                  \
     if ((rc = (x)) != GBP_OK) {     \
@@ -575,8 +751,18 @@ extern "C" int gbp_tri_plan_create(const float* xy, int n_v, const int32_t* tris
     TRI_TRY(tri_alloc(&p->minv, n_t));
     TRI_TRY(tri_alloc(&p->T, n_v));
     TRI_TRY(tri_alloc(&p->troot, n_v));
-    TRI_TRY(tri_alloc(&p->q[0], n_v));
-    TRI_TRY(tri_alloc(&p->q[1], n_v));
+    TRI_UP(p->info, info.data(), (size_t)n_v);
+    TRI_UP(p->tpos, tpos.data(), (size_t)3 * n_t);
+    TRI_TRY(tri_alloc(&p->inc, (size_t)3 * n_t));
+    TRI_TRY(tri_alloc(&p->q0, n_v));
+    if (n_v > kTriBlockVerts) {
+        TRI_TRY(tri_alloc(&p->q[0], tri_list_size(n_v, max_deg)));
+        TRI_TRY(tri_alloc(&p->q[1], tri_list_size(n_v, max_deg)));
+        for (int k = 0; k < 2; ++k) {
+            TRI_TRY(tri_alloc(&p->now[k], n_v));
+            TRI_TRY(tri_alloc(&p->gain[k], n_v));
+        }
+    }
     TRI_TRY(tri_alloc(&p->mark, n_v));
     TRI_TRY(tri_alloc(&p->ctl, 1));
     TRI_TRY(tri_alloc(&p->par, n_v));
@@ -598,9 +784,6 @@ extern "C" int gbp_tri_plan_create(const float* xy, int n_v, const int32_t* tris
 #undef TRI_UP
 #undef TRI_TRY
     if (hipHostMalloc((void**)&p->ctl_host, sizeof(TriCtl)) != hipSuccess ||
-        hipHostMalloc((void**)&p->ctl_pipe, 2 * sizeof(TriCtl)) != hipSuccess ||
-        hipEventCreateWithFlags(&p->ev[0], hipEventDisableTiming) != hipSuccess ||
-        hipEventCreateWithFlags(&p->ev[1], hipEventDisableTiming) != hipSuccess ||
         hipMemset(p->mark, 0, (size_t)n_v * sizeof(int)) != hipSuccess) {
         gbp_set_error("pinned control block or mark reset failed");
         tri_free(p);
@@ -635,41 +818,22 @@ extern "C" int gbp_tri_forward(gbp_tri_plan p, const float* D, const float* vsca
     hipStream_t s = (hipStream_t)stream;
     const int n_v = p->n_v;
     if ((rc = tri_prepare(p, D, vscale, root_node, root_t, n_roots, true, s))) return rc;
-    // enough blocks for the widest narrow front at 8 lanes or for a wide front at 4
-    const size_t lanes_max = std::max<size_t>((size_t)std::min(n_v, kNarrowFront) * 8, (size_t)n_v * 4);
-    const int grid = (int)std::max<size_t>(1, std::min<size_t>((lanes_max + TPB - 1) / TPB, 1024));
-    // batches of 8 rounds; the host checks batch k's queue length (copied into
-    // pinned memory behind it, with an event) only once batch k + 1 is queued, so
-    // the device never waits for the check; a finished solve costs one batch of
-    // empty rounds (each returns at once)
-    int r = 0, batch = 0, r_prev = 0;
-    bool converged = false;
-    while (r < p->max_rounds) {
-        for (int b = 0; b < 8; ++b, ++r)
-            k_tri_sweep<<<grid, TPB, 0, s>>>(p->xy, p->tri, p->minv, p->vptr, p->vent, p->nbp, p->nb,
-                                              p->T, p->q[r & 1], p->q[(r + 1) & 1], p->mark, p->ctl, r,
-                                              p->stamp + r + 1, p->eps_rel);
-        GBP_LAUNCH_CHECK();
-        GBP_HIP(hipMemcpyAsync(p->ctl_pipe + (batch & 1), p->ctl, sizeof(TriCtl), hipMemcpyDeviceToHost, s));
-        GBP_HIP(hipEventRecord(p->ev[batch & 1], s));
-        if (batch > 0) {
-            GBP_HIP(hipEventSynchronize(p->ev[(batch - 1) & 1]));
-            const TriCtl& c = p->ctl_pipe[(batch - 1) & 1];
-            if (c.err) break;
-            if (c.count[r_prev % 3] == 0) {
-                converged = true;
-                break;
-            }
-        }
-        r_prev = r;
-        ++batch;
+    const TriRelax g{p->info, p->inc, p->nb, p->eps_rel};
+    const int cap = (p->max_rounds + 7) / 8 * 8;
+    if (n_v <= kTriBlockVerts) {
+        k_tri_rounds_block<<<1, kTriThreads, tri_block_lds(n_v), s>>>(g, n_v, p->T, p->q0, p->ctl, cap);
+    } else {
+        const TriLists q{p->now[0], p->now[1], p->gain[0], p->gain[1], p->q[0], p->q[1], p->q0, p->mark};
+        k_tri_rounds_team<<<tri_team_blocks(n_v), kTriThreads, 0, s>>>(g, n_v, p->max_deg, q, p->stamp, p->team, p->ctl,
+                                                                       cap, p->T);
     }
-    p->stamp += r + 2;
+    GBP_LAUNCH_CHECK();
     k_tri_count_inf<<<gbp_blocks(n_v, TPB), TPB, 0, s>>>(p->T, n_v, p->ctl);
     GBP_HIP(hipMemcpyAsync(T_out, p->T, (size_t)n_v * sizeof(float), hipMemcpyDeviceToDevice, s));
     if ((rc = tri_read(p, s))) return rc;
     const TriCtl& c = *p->ctl_host;
-    if (!converged && !c.err && c.count[r % 3] == 0) converged = true;   // the cap's last batch finished it
+    p->stamp += c.rounds + 2;
+    const bool converged = !c.err && c.left == 0;
     if (stats) {
         stats->rounds = c.rounds;
         stats->converged = converged ? 1 : 0;
@@ -679,7 +843,7 @@ extern "C" int gbp_tri_forward(gbp_tri_plan p, const float* D, const float* vsca
     }
     if (c.err) return gbp_err_from_bits(c.err);
     if (!converged) {
-        gbp_set_error("triangle forward did not converge in %d rounds", r);
+        gbp_set_error("triangle forward did not converge in %d rounds", cap);
         return GBP_ERR_NOT_CONVERGED;
     }
     return GBP_OK;
@@ -716,7 +880,7 @@ extern "C" int gbp_tri_backward(gbp_tri_plan p, const float* D, const float* vsc
     a.calpha = p->calpha;
     a.rec = p->rec;
     a.over = p->over;
-    a.leaf = p->q[0];
+    a.leaf = p->q0;
     a.ready[0] = p->ready[0];
     a.ready[1] = p->ready[1];
     a.team = p->team;
