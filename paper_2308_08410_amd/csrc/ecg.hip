@@ -707,8 +707,9 @@ extern "C" int gbp_ecg_forward_batched(gbp_batch b, const float* T, const float*
         gbp_set_error("ecg is NULL");
         return GBP_ERR_ARG;
     }
-    return ecg_forward_launch(EcgLaunch{b->off, b->n_inst, b->max_verts, b->work, ecg_work_floats(b->max_steps)}, T, b->total, W,
-                              L, ap, ecg, (hipStream_t)stream);
+    return ecg_forward_launch(
+        EcgLaunch{b->off, b->n_inst, b->max_verts, b->work, ecg_work_floats(b->max_steps)}, T, b->total, W, L, ap, ecg,
+        (hipStream_t)stream);
 }
 
 extern "C" int gbp_ecg_backward_batched(gbp_batch b, const float* T, const float* W, int L,

@@ -28,6 +28,7 @@
 #include "local_solve.h"
 #include "fista.h"
 #include "profile.h"
+#include "team.h"
 #include "walk.h"
 
 namespace {
@@ -428,10 +429,10 @@ __device__ __forceinline__ void relax_slot(int& e, int cnt, const int* __restric
 // the Hopf-Lax minimum, and on a change the lanes push the unique neighbours.
 // SOLVER 0: the exact predicated solve; 1: Alg. 1 with the face's step constant
 // lip[4 t + K], n_f iterations (tau = 0) or the face's count for tolerance tau.
-template <int SOLVER>
+template <int SOLVER, typename Times>
 __device__ __forceinline__ float face_value(const int* __restrict__ nent,
                                             const int4* __restrict__ tetv,
-                                            const float4* __restrict__ tetg, const float* T,
+                                            const float4* __restrict__ tetg, Times T,
                                             int e, int K, const float* __restrict__ lip, int n_f,
                                             float tau) {
     const int t = nent[e];
@@ -443,6 +444,158 @@ __device__ __forceinline__ float face_value(const int* __restrict__ nent,
     else {
         const float L = lip[4 * (size_t)t + K];
         return local_fista<false>(face_q_rt(g0, g1, K), T[a], T[b], T[cc], L, fista_iters(L, tau, n_f));
+    }
+}
+
+// ------------------------------------------------------------------ rounds in one launch
+// All rounds of a plain cold solve by a team of blocks, L lanes a vertex; member b writes
+// its pushes to list[cap * b ...], read with the prefix of the members' counts, and a
+// member's share of n vertices pushes at most as many times their largest number of
+// neighbours.  A round is a Jacobi step: round r reads the times of now[r & 1] and lowers
+// those of the other array, which holds the improvements of all rounds but the last; a
+// member repeats its own of that one (gain, by position in the round's queue) before it
+// adds its new ones.  The times do not depend on which vertex was first.
+// Bound by a round's chain (queue, vertex, patch, element, times, solve, marks, barrier),
+// about 5 us, where a launch a round is 6.6 us and its gap.  A forward takes, as launches
+// and with 64 / 128 / 256 blocks: at 2,000 vertices 306 us and 239 / 259 / 310, at 9,000
+// 432 and 369 / 383 / 462, at 32,000 830 and 913 / 794 / 867, at 120,000 1586 and 2317 /
+// 1556 / 1360, at 200,000 1852 and 1732 (256); at 350,000 both 2.9 ms, at 500,000 4.3 and
+// 4.9, so larger meshes take launches.  (8 and 32 lanes a vertex: 30% and 3% slower at 9,000.)
+struct TeamTimes {
+    const int* now;
+    __device__ float operator[](int x) const { return from_ordered(agent_load(now + x)); }
+};
+
+struct TeamLists {
+    int* now[2];                  // [n_v] times, as ordered integers
+    unsigned long long* gain[2];  // [n_v] vertex << 32 | its time, or all ones
+    int* list[2];
+    int max_deg;
+};
+
+constexpr int kRoundThreads = 1024;
+constexpr int kRoundLanes = 16;
+int round_blocks(int n_v) { return n_v < 12288 ? 64 : n_v < 49152 ? 128 : 256; }
+
+__global__ void __launch_bounds__(kRoundThreads)
+    k_rounds_team(const int2* __restrict__ nptr, const int* __restrict__ nent, const int4* __restrict__ tetv,
+                  const float4* __restrict__ tetg, float* __restrict__ T, const int* __restrict__ q0,
+                  const int* __restrict__ adj_ptr, const int* __restrict__ adj, int* mark, GbpCtl* ctl, TeamCtl* team,
+                  unsigned long long* __restrict__ blk, int rounds, float eps_rel, int n_v, XcdQueues xq, TeamLists q,
+                  int stop_on_error) {
+    __shared__ int before[kTeamMax + 1], count[3], seg[9];
+    __shared__ unsigned long long sums[2];
+    if (stop_on_error && ctl->err) {
+        if (blockIdx.x == 0 && threadIdx.x == 0) ctl->stamp += 2;   // the roots' marks stay retired
+        return;
+    }
+    const int stamp = ctl->stamp;
+    if (threadIdx.x < 3) count[threadIdx.x] = 0;
+    if (threadIdx.x < 2) sums[threadIdx.x] = 0;
+    if (threadIdx.x == 0) {
+        seg[0] = 0;
+        for (int x = 0; x < 8; ++x) seg[x + 1] = seg[x] + ctl->qcnt[0][x];
+    }
+    Team t;
+    if (!team_join(team, false, t)) return;
+    const size_t cap = team_list_cap(n_v, q.max_deg, t.size);
+    int v0, v1, m = 0;
+    team_share(t, n_v, v0, v1);
+    for (int i = v0 + (int)threadIdx.x; i < v1; i += kRoundThreads) {
+        const int b = ordered(T[i]);
+        agent_store(q.now[0] + i, b);
+        agent_store(q.now[1] + i, b);
+    }
+    team_sync(t, 1, &count[0], before, m);
+    int n = seg[8], r = 0, p0 = 0, p1 = 0;
+    unsigned solves = 0, upd = 0;
+    const int lane = threadIdx.x & (kRoundLanes - 1);
+    while (n > 0 && r < rounds) {
+        const int odd = r & 1;
+        const int* in = odd ? q.list[1] : q.list[0];
+        int* out = (odd ? q.list[0] : q.list[1]) + cap * t.rank;
+        int* n_out = &count[(r + 1) % 3];
+        const int* T0 = odd ? q.now[1] : q.now[0];
+        int* T1 = odd ? q.now[0] : q.now[1];
+        const unsigned long long* last = odd ? q.gain[0] : q.gain[1];
+        unsigned long long* gain = odd ? q.gain[1] : q.gain[0];
+        // (the last waves, which have the fewest vertices)
+        for (int k = p0 + kRoundThreads - 1 - (int)threadIdx.x; k < p1; k += kRoundThreads) {
+            const unsigned long long v = agent_load(last + k);
+            if (v != ~0ull)
+                (void)__hip_atomic_fetch_min(T1 + (int)(v >> 32), (int)(unsigned)v, __ATOMIC_RELAXED,
+                                             __HIP_MEMORY_SCOPE_AGENT);
+        }
+        const int next = stamp + r + 1;
+        const TeamTimes time{T0};
+        team_share(t, n, p0, p1);
+        for (int k = p0 + (int)threadIdx.x / kRoundLanes; k < p1; k += kRoundThreads / kRoundLanes) {
+            int i;
+            if (r == 0) {
+                int x = 0;
+                while (seg[x + 1] <= k) ++x;
+                i = q0[xq.off[x] + k - seg[x]];
+            } else {
+                while (before[m + 1] <= k) ++m;
+                i = agent_load(in + cap * m + (k - before[m]));
+            }
+            const int2 p = nptr[i];
+            const int a0 = adj_ptr[i], a1 = adj_ptr[i + 1];
+            const float told = time[i];
+            const int c0 = p.y & 255, e01 = c0 + ((p.y >> 8) & 255), e012 = e01 + ((p.y >> 16) & 255),
+                      tot = e012 + ((p.y >> 24) & 255);
+            const int w0 = a0 + lane < a1 ? adj[a0 + lane] : -1;
+            const int w1 = a0 + lane + kRoundLanes < a1 ? adj[a0 + lane + kRoundLanes] : -1;
+            float best = told;
+            for (int c = lane; c < tot; c += 2 * kRoundLanes) {
+                const int d = c + kRoundLanes;       // second local problem of this lane
+                const bool okd = d < tot;
+                const int Kc = (c < c0) ? 0 : (c < e01) ? 1 : (c < e012) ? 2 : 3;
+                const int Kd = (d < c0) ? 0 : (d < e01) ? 1 : (d < e012) ? 2 : 3;
+                const float vc = face_value<0>(nent, tetv, tetg, time, p.x + c, Kc, nullptr, 0, 0.f);
+                const float vd =
+                    face_value<0>(nent, tetv, tetg, time, p.x + (okd ? d : c), okd ? Kd : Kc, nullptr, 0, 0.f);
+                best = fminf(best, okd ? fminf(vc, vd) : vc);
+                solves += okd ? 2 : 1;
+            }
+#pragma unroll
+            for (int o = kRoundLanes / 2; o > 0; o >>= 1) best = fminf(best, __shfl_xor(best, o));
+            if (lane == 0) {
+                const bool lower = best < told;
+                const int b = ordered(best);
+                __hip_atomic_store(gain + k, lower ? ((unsigned long long)(unsigned)i << 32) | (unsigned)b : ~0ull,
+                                   __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                if (lower) (void)__hip_atomic_fetch_min(T1 + i, b, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            }
+            const bool changed = (told < GBP_INF) ? (best < told - eps_rel * fmaxf(1.f, fabsf(told)))
+                                                  : (best < GBP_INF);
+            if (!changed) continue;
+            if (lane == 0) ++upd;
+            const auto push = [&](int x) {
+                if (__hip_atomic_fetch_max(mark + x, next, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < next)
+                    agent_store(out + atomicAdd(n_out, 1), x);
+            };
+            if (w0 >= 0) push(w0);
+            if (w1 >= 0) push(w1);
+            for (int a = a0 + lane + 2 * kRoundLanes; a < a1; a += kRoundLanes) push(adj[a]);
+        }
+        ++r;
+        n = team_sync(t, r + 1, n_out, before, m);
+        if (threadIdx.x == 0) count[(r + 2) % 3] = 0;   // read by all before the sync, used after the next
+    }
+    const int* T0 = r & 1 ? q.now[1] : q.now[0];
+    for (int i = v0 + (int)threadIdx.x; i < v1; i += kRoundThreads) T[i] = from_ordered(agent_load(T0 + i));
+    atomicAdd(&sums[0], (unsigned long long)solves);
+    atomicAdd(&sums[1], (unsigned long long)upd);
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        blk[2 * t.rank] = sums[0];
+        blk[2 * t.rank + 1] = sums[1];
+        if (t.rank == 0) {
+            ctl->rounds = r;
+            ctl->stamp = stamp + r + 2;
+            if (n > 0) ctl->status |= 1;
+        }
     }
 }
 
@@ -1411,8 +1564,8 @@ static void launch_round(gbp_plan p, bool cold, bool ordered, int r, hipStream_t
 }
 
 // Forward.  budget <= 0: synchronous, rounds until the queue empties (checked every
-// sync_batch rounds).  budget > 0: exactly `budget` rounds, no host synchronisation
-// (graph-capturable); empty rounds return at once and status bit 0 reports a queue
+// sync_batch rounds; one launch and one check where a team runs them).  budget > 0: at most
+// `budget` rounds, no host synchronisation (graph-capturable); empty rounds return at once and status bit 0 reports a queue
 // left non-empty.
 int gbp_forward_impl(gbp_plan p, const float* D, const float* vscale, const int32_t* root_node,
                      const float* root_t, int n_roots, const float* T_init, float* T_out,
@@ -1436,7 +1589,16 @@ int gbp_forward_impl(gbp_plan p, const float* D, const float* vscale, const int3
     GBP_LAUNCH_CHECK();
     int r = 0;
     bool converged = true;
-    if (budget > 0) {
+    const bool team = cold && p->hold_delta <= 0.f && p->solver == 0 && p->n_v <= kRoundsTeamVerts;
+    if (team) {
+        ProfScope ps(GBP_PROF_FIM_SWEEP, s);
+        r = budget > 0 ? budget : p->max_rounds;
+        k_rounds_team<<<round_blocks(n_v), kRoundThreads, 0, s>>>(
+            p->nptr, p->nent, p->tetv, p->tetg, p->T, p->q[0], p->adj_ptr, p->adj, p->mark, p->ctl, p->team, p->blk, r,
+            p->eps_rel, n_v, p->xq,
+            TeamLists{{p->now[0], p->now[1]}, {p->gain[0], p->gain[1]}, {p->list[0], p->list[1]}, p->max_deg},
+            budget > 0 ? 0 : 1);
+    } else if (budget > 0) {
         for (; r < budget; ++r) launch_round(p, cold, ordered, r, s);
     } else {
         rc = run_pipelined(
@@ -1447,13 +1609,17 @@ int gbp_forward_impl(gbp_plan p, const float* D, const float* vscale, const int3
             return rc;
         }
     }
-    k_forward_end<<<1, 64, 0, s>>>(p->ctl, r);
+    if (!team) k_forward_end<<<1, 64, 0, s>>>(p->ctl, r);
     k_reduce_stats<<<1, TPB, 0, s>>>(p->blk, p->ctl);
     k_count_inf<<<gbp_blocks(n_v, TPB), TPB, 0, s>>>(p->T, n_v, p->ctl);
     k_scatter_out<<<gbp_blocks(n_v, TPB), TPB, 0, s>>>(p->T, p->node_int, T_out, n_v);
     GBP_LAUNCH_CHECK();
     if (budget > 0) return GBP_OK;
     if ((rc = read_ctl(p, s))) return rc;
+    if (team) {
+        if (p->ctl_host->err) return gbp_err_from_bits(p->ctl_host->err);
+        converged = (p->ctl_host->status & 1) == 0;
+    }
     p->last_rounds = p->ctl_host->rounds;
     if (stats) {
         std::memset(stats, 0, sizeof(*stats));

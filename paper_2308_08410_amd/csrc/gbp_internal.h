@@ -52,6 +52,21 @@ struct TeamCtl {
     unsigned long long flag[2][kTeamMax];   // per round parity and block: round << 32 | the block's count
 };
 
+// Members' lists of a relaxation round: a member's share of the round's vertices pushes at
+// most as many times their largest number of neighbours.
+__host__ __device__ inline size_t team_list_cap(int n_v, int max_deg, int size) {
+    const size_t most = ((size_t)n_v / size + 1) * max_deg;
+    return most < (size_t)n_v ? most : (size_t)n_v;
+}
+inline size_t team_list_size(int n_v, int max_deg) {   // for a team of any number of blocks
+    size_t most = 0;
+    for (int size = 1; size <= kTeamMax; ++size) {
+        const size_t all = size * team_list_cap(n_v, max_deg, size);
+        if (all > most) most = all;
+    }
+    return most;
+}
+
 // State of one adjoint walk (walk.h), zeroed before it.
 struct AdjCtl {
     int nleaf;     // vertices that wait for no child
@@ -127,6 +142,9 @@ __host__ __device__ inline size_t walk_list_cap(int n_v, int size) {
 inline size_t walk_list_size(int n_v) { return 4 * ((size_t)n_v + (size_t)kWalkGroups * kTeamMax); }
 static_assert(sizeof(AdjParent) == 16 && offsetof(AdjRec, entry) == 64, "pieces 0-2 parents, 4 and 5 entries");
 
+// Plain cold solves of meshes up to this size run their rounds in one launch.
+constexpr int kRoundsTeamVerts = 1 << 18;
+
 struct gbp_plan_s {
     int device = 0;
     int n_v = 0, n_e = 0;
@@ -157,6 +175,11 @@ struct gbp_plan_s {
     int* q[2] = {nullptr, nullptr};  // work queues
     int* mark = nullptr;          // [n_v] queue stamps
     XcdQueues xq{};               // sub-queue layout of q[0], q[1]
+    // a team's rounds (n_v <= kRoundsTeamVerts): times, each round's improvements, lists
+    int* now[2] = {nullptr, nullptr};
+    unsigned long long* gain[2] = {nullptr, nullptr};
+    int* list[2] = {nullptr, nullptr};
+    int max_deg = 0;              // most neighbours of a vertex
     // launch configuration (autotunable)
     int lanes = 16;               // lanes per vertex in a relaxation round (8, 16 or 32)
     int sweep_blocks = 2048;      // grid of a relaxation round (<= kStatBlocks)

@@ -78,7 +78,7 @@ static void plan_free(gbp_plan p) {
                     p->mark, p->ctl, p->team, p->blk, p->par, p->pa, p->crange, p->cfill, p->rec, p->cchild,
                     p->calpha, p->lam, p->over, p->ready[0], p->ready[1], p->g, p->dsbar, p->done, p->lip,
                     p->pnode, p->hold, p->blist, p->guess, p->comp,
-                    p->comp_root};
+                    p->comp_root, p->now[0], p->now[1], p->gain[0], p->gain[1], p->list[0], p->list[1]};
     for (void* q : ptrs)
         if (q) (void)hipFree(q);
     if (p->ctl_host) (void)hipHostFree(p->ctl_host);
@@ -335,6 +335,12 @@ extern "C" int gbp_plan_create(const float* xyz, int n_v, const int32_t* tets, i
     TRY(dalloc(&p->q[0], n_v));
     TRY(dalloc(&p->q[1], n_v));
     TRY(dalloc(&p->mark, n_v));
+    for (int i = 0; i < n_v; ++i) p->max_deg = std::max(p->max_deg, adj_ptr[i + 1] - adj_ptr[i]);
+    for (int k = 0; k < 2 && n_v <= kRoundsTeamVerts; ++k) {
+        TRY(dalloc(&p->now[k], n_v));
+        TRY(dalloc(&p->gain[k], n_v));
+        TRY(dalloc(&p->list[k], team_list_size(n_v, p->max_deg)));
+    }
     TRY(dalloc(&p->ctl, 1));
     TRY(dalloc(&p->team, 1));
     TRY(dalloc(&p->blk, 2 * (size_t)kStatBlocks));

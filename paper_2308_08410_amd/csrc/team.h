@@ -44,6 +44,13 @@ __device__ __forceinline__ int agent_add(int* p, int v) {
     return __hip_atomic_fetch_add(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
+// Floats as integers of the same order.
+__device__ __forceinline__ int ordered(float x) {
+    const int b = __float_as_int(x);
+    return b < 0 ? b ^ 0x7fffffff : b;
+}
+__device__ __forceinline__ float from_ordered(int b) { return __int_as_float(b < 0 ? b ^ 0x7fffffff : b); }
+
 // Joins the block to the launch's team (false: it is not a member and returns).
 // one_xcd: the blocks of one XCD, whichever the first block runs on.
 __device__ __forceinline__ bool team_join(TeamCtl* ctl, bool one_xcd, Team& t) {

@@ -115,8 +115,8 @@ void tri_free(gbp_tri_plan p) {
                     p->T,     p->troot, p->q[0],   p->q[1],   p->mark,   p->ctl,    p->par,
                     p->pnode, p->pa,    p->crange, p->cfill,  p->cchild, p->calpha, p->lam,
                     p->g,     p->dsbar, p->done,   p->rec,    p->over,
-                    p->ready[0], p->ready[1], p->team, p->info, p->tpos, p->inc, p->q0, p->now[0], p->now[1], p->gain[0],
-                    p->gain[1]};
+                    p->ready[0], p->ready[1], p->team, p->info, p->tpos, p->inc, p->q0,
+                    p->now[0], p->now[1], p->gain[0], p->gain[1]};
     for (void* q : ptrs)
         if (q) (void)hipFree(q);
     if (p->ctl_host) (void)hipHostFree(p->ctl_host);
@@ -124,13 +124,6 @@ void tri_free(gbp_tri_plan p) {
 }
 
 __device__ __forceinline__ bool fin(float x) { return x - x == 0.f; }
-
-// Floats as integers of the same order.
-__device__ __forceinline__ int ordered(float x) {
-    const int b = __float_as_int(x);
-    return b < 0 ? b ^ 0x7fffffff : b;
-}
-__device__ __forceinline__ float from_ordered(int b) { return __int_as_float(b < 0 ? b ^ 0x7fffffff : b); }
 
 // block reductions (one atomic per block instead of one per thread)
 __device__ __forceinline__ unsigned long long tri_block_sum(unsigned long long v) {
@@ -217,7 +210,8 @@ __global__ void k_tri_metric(const float* __restrict__ D, const float* __restric
 
 __global__ void k_tri_roots(const int* __restrict__ root_node, const float* __restrict__ root_t,
                             int n_roots, int n_v, float* __restrict__ troot, float* __restrict__ T,
-                            int* __restrict__ now0, int* __restrict__ now1, int cold, const int* __restrict__ nbp, const int* __restrict__ nb,
+                            int* __restrict__ now0, int* __restrict__ now1, int cold,
+                            const int* __restrict__ nbp, const int* __restrict__ nb,
                             int* __restrict__ q0, int* __restrict__ mark, int stamp, TriCtl* ctl) {
     if (threadIdx.x == 0) {
         for (int r = 0; r < n_roots; ++r) {
@@ -361,18 +355,6 @@ __global__ void __launch_bounds__(kTriThreads)
 // (Blocks of one XCD only: 11.6 ms at 250,000, 1087 us at 8,000.)
 int tri_team_blocks(int n_v) { return n_v < 24576 ? 32 : n_v < 163840 ? 64 : 128; }
 
-__host__ __device__ inline size_t tri_list_cap(int n_v, int max_deg, int size) {
-    const size_t most = ((size_t)n_v / size + 1) * max_deg;
-    return most < (size_t)n_v ? most : (size_t)n_v;
-}
-
-// Room for a team of any number of blocks.
-size_t tri_list_size(int n_v, int max_deg) {
-    size_t most = 0;
-    for (int size = 1; size <= kTeamMax; ++size) most = std::max(most, size * tri_list_cap(n_v, max_deg, size));
-    return most;
-}
-
 struct TriLists {
     int *now0, *now1;                    // [n_v] times, as ordered integers
     unsigned long long *gain0, *gain1;   // [n_v] vertex << 32 | its time, or all ones
@@ -389,7 +371,7 @@ __global__ void __launch_bounds__(kTriThreads)
     if (threadIdx.x < 3) count[threadIdx.x] = 0;
     Team t;
     if (!team_join(team, false, t)) return;
-    const size_t cap = tri_list_cap(n_v, max_deg, t.size);
+    const size_t cap = team_list_cap(n_v, max_deg, t.size);
     int n = ctl->count, r = 0, m = 0, p0 = 0, p1 = 0;
     unsigned long long all_solves = 0, all_upd = 0;
     while (n > 0 && r < rounds) {
@@ -401,7 +383,8 @@ __global__ void __launch_bounds__(kTriThreads)
         int* T1 = odd ? q.now0 : q.now1;
         const unsigned long long* last = odd ? q.gain0 : q.gain1;
         unsigned long long* gain = odd ? q.gain1 : q.gain0;
-        for (int k = p0 + (int)threadIdx.x; k < p1; k += kTriThreads) {
+        // (the last waves, which have the fewest vertices)
+        for (int k = p0 + kTriThreads - 1 - (int)threadIdx.x; k < p1; k += kTriThreads) {
             const unsigned long long v = agent_load(last + k);
             if (v != ~0ull)
                 (void)__hip_atomic_fetch_min(T1 + (int)(v >> 32), (int)(unsigned)v, __ATOMIC_RELAXED,
@@ -756,8 +739,8 @@ extern "C" int gbp_tri_plan_create(const float* xy, int n_v, const int32_t* tris
     TRI_TRY(tri_alloc(&p->inc, (size_t)3 * n_t));
     TRI_TRY(tri_alloc(&p->q0, n_v));
     if (n_v > kTriBlockVerts) {
-        TRI_TRY(tri_alloc(&p->q[0], tri_list_size(n_v, max_deg)));
-        TRI_TRY(tri_alloc(&p->q[1], tri_list_size(n_v, max_deg)));
+        TRI_TRY(tri_alloc(&p->q[0], team_list_size(n_v, max_deg)));
+        TRI_TRY(tri_alloc(&p->q[1], team_list_size(n_v, max_deg)));
         for (int k = 0; k < 2; ++k) {
             TRI_TRY(tri_alloc(&p->now[k], n_v));
             TRI_TRY(tri_alloc(&p->gain[k], n_v));
