@@ -213,8 +213,9 @@ struct gbp_plan_s {
     int* st_dev = nullptr;        //   the first launch of a batch (st_dev: its device address)
     hipEvent_t ev[2] = {nullptr, nullptr};   // completion of the pipelined status copies
 
-    // backward workspace (allocated on first use)
+    // backward workspace (one allocation, on first use)
     bool bwd_ready = false;
+    char* bwd_mem = nullptr;
     int bwd_levels = 0, bwd_cyclic = 0, bwd_gs_sweeps = 0;   // last backward
     int* par = nullptr;           // [n_v] (element << 2 | local slot) or -1
     float4* pa = nullptr;         // [n_v] (alpha0, alpha1, alpha2, best)

@@ -15,6 +15,7 @@
 #include <algorithm>
 #include <cstdlib>
 #include <numeric>
+#include <type_traits>
 #include <vector>
 
 #include <climits>
@@ -75,9 +76,7 @@ static void plan_free(gbp_plan p) {
     if (!p) return;
     void* ptrs[] = {p->xyz, p->tetv, p->tet_user, p->tet_int, p->node_user, p->node_int, p->nptr, p->nent,
                     p->adj_ptr, p->adj, p->tetg, p->vs, p->T, p->troot, p->q[0], p->q[1],
-                    p->mark, p->ctl, p->team, p->blk, p->par, p->pa, p->crange, p->cfill, p->rec, p->cchild,
-                    p->calpha, p->lam, p->over, p->ready[0], p->ready[1], p->g, p->dsbar, p->done, p->lip,
-                    p->pnode, p->hold, p->blist, p->guess, p->comp,
+                    p->mark, p->ctl, p->team, p->blk, p->bwd_mem, p->lip, p->hold, p->blist, p->guess, p->comp,
                     p->comp_root, p->now[0], p->now[1], p->gain[0], p->gain[1], p->list[0], p->list[1]};
     for (void* q : ptrs)
         if (q) (void)hipFree(q);
@@ -381,15 +380,33 @@ int gbp_alloc_backward(gbp_plan p) {
                       INT_MAX / (kAdjEntries + 3));
         return GBP_ERR_ARG;
     }
-    int rc;
-    if ((rc = dalloc(&p->par, n_v)) || (rc = dalloc(&p->pa, n_v)) || (rc = dalloc(&p->pnode, n_v)) ||
-        (rc = dalloc(&p->crange, n_v)) || (rc = dalloc(&p->cfill, n_v)) ||
-        (rc = dalloc(&p->cchild, (size_t)3 * n_v)) || (rc = dalloc(&p->calpha, (size_t)3 * n_v)) ||
-        (rc = dalloc(&p->rec, n_v)) || (rc = dalloc(&p->over, (size_t)3 * n_v)) ||
-        (rc = dalloc(&p->ready[0], walk_list_size(n_v))) || (rc = dalloc(&p->ready[1], walk_list_size(n_v))) ||
-        (rc = dalloc(&p->lam, n_v)) || (rc = dalloc(&p->g, n_v)) || (rc = dalloc(&p->done, n_v)) ||
-        (rc = dalloc(&p->dsbar, n_e)))
-        return rc;
+    // one allocation: 16 of their own took longer than a backward
+    size_t size = 0;
+    const auto carve = [&](auto** dst, size_t n) {
+        if (p->bwd_mem) *dst = reinterpret_cast<std::remove_reference_t<decltype(*dst)>>(p->bwd_mem + size);
+        size += (std::max<size_t>(n, 1) * sizeof(**dst) + 255) / 256 * 256;
+    };
+    const auto layout = [&] {
+        size = 0;
+        carve(&p->rec, n_v);
+        carve(&p->par, n_v);
+        carve(&p->pa, n_v);
+        carve(&p->pnode, n_v);
+        carve(&p->crange, n_v);
+        carve(&p->cfill, n_v);
+        carve(&p->cchild, (size_t)3 * n_v);
+        carve(&p->calpha, (size_t)3 * n_v);
+        carve(&p->over, (size_t)3 * n_v);
+        carve(&p->ready[0], walk_list_size(n_v));
+        carve(&p->ready[1], walk_list_size(n_v));
+        carve(&p->lam, n_v);
+        carve(&p->g, n_v);
+        carve(&p->done, n_v);
+        carve(&p->dsbar, n_e);
+    };
+    layout();
+    if (int rc = dalloc(&p->bwd_mem, size)) return rc;
+    layout();
     p->bwd_ready = true;
     return GBP_OK;
 }
