@@ -42,20 +42,6 @@ __device__ __forceinline__ bf16 to_bf16(float x) {
 }
 __device__ __forceinline__ float from_bf16(bf16 h) { return __uint_as_float((unsigned)h << 16); }
 
-// ---------------------------------------------------------------- loss
-__global__ void k_sum_parts(const float* __restrict__ part, int n, float scale, float* __restrict__ out) {
-    __shared__ float sh[256];
-    float s = 0.f;
-    for (int i = threadIdx.x; i < n; i += 256) s += part[i];
-    sh[threadIdx.x] = s;
-    __syncthreads();
-    for (int o = 128; o > 0; o >>= 1) {
-        if ((int)threadIdx.x < o) sh[threadIdx.x] += sh[threadIdx.x + o];
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) *out = sh[0] * scale;
-}
-
 // ---------------------------------------------------------------- fused row-tile kernels
 // A block of 4 waves owns a tile of 16 TR rows and runs the network's 256-wide layers
 // on it with the tile in LDS (16 TR x 256 bf16 per layer).  Wave w
@@ -526,32 +512,6 @@ __global__ void __launch_bounds__(256) k_mlp_wgrad(MlpWgrad a) {
         wgrad_tile<16>(a, blockIdx.x - 4 * (NLAYER - 1), As, reinterpret_cast<bf16(*)[16][KP]>(&Bs[0][0][0]));
 }
 
-// weight gradients: the splits' partials of each W1..W4 entry, summed in split order
-__global__ void k_mlp_reduce_w(const float* __restrict__ pw, int splits, int n_params, float* __restrict__ g) {
-    const int e = blockIdx.x * blockDim.x + threadIdx.x;
-    if (e >= n_params) return;
-    bool weight = false;
-    for (int l = 1; l <= NLAYER; ++l) weight |= e >= off_W_dev(l) && e < off_b_dev(l);
-    if (!weight) return;
-    float s = 0.f;
-#pragma unroll 8
-    for (int z = 0; z < splits; ++z) s += pw[(size_t)z * n_params + e];
-    g[e] = s;
-}
-
-// b1..b4, w5, b5: one wave per entry; lane k sums the backward blocks k, k + 64, ... in
-// order, then a fixed butterfly adds the lanes (the same order on every call)
-__global__ void k_mlp_reduce_b(const float* __restrict__ pb, int blocks, float* __restrict__ g) {
-    const int col = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
-    if (col >= kBwdPart) return;
-    float s = 0.f;
-    for (int b = lane; b < blocks; b += 64) s += pb[(size_t)b * kBwdPart + col];
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o);
-    if (lane == 0)
-        g[col < NLAYER * HID ? off_b_dev(col / HID + 1) + col % HID : off_w5_dev() + (col - NLAYER * HID)] = s;
-}
-
 // Rows per block (16 TR) of the row-tile kernels: a larger tile fetches the weights
 // fewer times per row, more blocks hide more latency; the steps are where the
 // measured forward and training times cross (128 rows from 65536 rows, 64 from
@@ -586,19 +546,78 @@ __global__ void k_refresh_copies(const float* __restrict__ p, int n, MlpCopies c
     if (t < n) write_copies(c, t, p[t]);
 }
 
-// one Adam step on the fp32 masters, refreshing their bf16 copies
-__global__ void k_adam_flat(float* __restrict__ p, const float* __restrict__ g, float* __restrict__ m,
-                            float* __restrict__ v, int n, float lr, float c1, float c2, MlpCopies c) {
-    const int t = blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= n) return;
-    const float gi = g[t];
-    const float mi = 0.9f * m[t] + 0.1f * gi;
-    const float vi = 0.999f * v[t] + 0.001f * gi * gi;
-    m[t] = mi;
-    v[t] = vi;
-    const float pi = p[t] - lr * (mi * c1) / (sqrtf(vi * c2) + 1e-8f);
-    p[t] = pi;
-    write_copies(c, t, pi);
+// End of a training pass, every entry by one thread, wave or block in a fixed order (the
+// same on every call): block 0 the misfit; the next kBiasBlocks a wave per entry of
+// b1..b4, w5, b5 (lane k sums the blocks' partials k, k + 64, ..., a butterfly adds the
+// lanes); the others the splits' partials of the W1..W4 entries, in split order.  With p
+// given, an Adam step on the fp32 masters follows at once, refreshing their bf16 copies.
+// Bound by the splits' partials (16,384 rows: 52 MB, in the last-level cache): 11.5 us;
+// the misfit, the two reductions, the step and the copy of the misfit as launches of their
+// own took 22 us and four gaps (a 16,384-row step 122 us, now 113).
+struct MlpFinish {
+    const float* loss_part;
+    const float* pb;
+    const float* pw;
+    float* loss;
+    float* loss_out;   // the caller's, or null
+    float* g;
+    float *p, *m, *v;  // p == nullptr: gradients only
+    int blocks, splits, n_params;
+    float loss_scale, lr, c1, c2;
+    MlpCopies c;
+};
+constexpr int kBiasBlocks = (kBwdPart + 3) / 4;
+
+__device__ __forceinline__ void finish_entry(const MlpFinish& a, int e, float gi) {
+    a.g[e] = gi;
+    if (!a.p) return;
+    const float mi = 0.9f * a.m[e] + 0.1f * gi;
+    const float vi = 0.999f * a.v[e] + 0.001f * gi * gi;
+    a.m[e] = mi;
+    a.v[e] = vi;
+    const float pi = a.p[e] - a.lr * (mi * a.c1) / (sqrtf(vi * a.c2) + 1e-8f);
+    a.p[e] = pi;
+    write_copies(a.c, e, pi);
+}
+
+__global__ void __launch_bounds__(256) k_mlp_finish(MlpFinish a) {
+    if (blockIdx.x == 0) {
+        __shared__ float sh[256];
+        float s = 0.f;
+        for (int i = threadIdx.x; i < a.blocks; i += 256) s += a.loss_part[i];
+        sh[threadIdx.x] = s;
+        __syncthreads();
+        for (int o = 128; o > 0; o >>= 1) {
+            if ((int)threadIdx.x < o) sh[threadIdx.x] += sh[threadIdx.x + o];
+            __syncthreads();
+        }
+        if (threadIdx.x == 0) {
+            *a.loss = sh[0] * a.loss_scale;
+            if (a.loss_out) *a.loss_out = sh[0] * a.loss_scale;
+        }
+        return;
+    }
+    if (blockIdx.x <= kBiasBlocks) {
+        const int col = (blockIdx.x - 1) * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
+        if (col >= kBwdPart) return;
+        float s = 0.f;
+        for (int b = lane; b < a.blocks; b += 64) s += a.pb[(size_t)b * kBwdPart + col];
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o);
+        if (lane == 0)
+            finish_entry(a, col < NLAYER * HID ? off_b_dev(col / HID + 1) + col % HID
+                                               : off_w5_dev() + (col - NLAYER * HID), s);
+        return;
+    }
+    const int e = (blockIdx.x - 1 - kBiasBlocks) * 256 + threadIdx.x;
+    if (e >= a.n_params) return;
+    bool weight = false;
+    for (int l = 1; l <= NLAYER; ++l) weight |= e >= off_W_dev(l) && e < off_b_dev(l);
+    if (!weight) return;
+    float s = 0.f;
+#pragma unroll 8
+    for (int z = 0; z < a.splits; ++z) s += a.pw[(size_t)z * a.n_params + e];
+    finish_entry(a, e, s);
 }
 
 // ---------------------------------------------------------------- features
@@ -724,8 +743,9 @@ void launch_infer(gbp_mlp p, const bf16* X, int m, float out_scale, float* y, hi
 }
 
 // training pass (forward, misfit, backward chain), weight gradients, reductions into
-// p->grads and p->loss
-void launch_train(gbp_mlp p, const bf16* X, int m, const float* target, hipStream_t s) {
+// p->grads, p->loss and the caller's `loss`; step > 0: the step-th Adam step with rate lr
+void launch_train(gbp_mlp p, const bf16* X, int m, const float* target, float* loss, int step, float lr,
+                  hipStream_t s) {
     MlpTrain a{};
     a.X = X;
     a.target = target;
@@ -742,7 +762,6 @@ void launch_train(gbp_mlp p, const bf16* X, int m, const float* target, hipStrea
     const int ib = train_rows(m), blocks = (m + ib - 1) / ib;
     if (ib == 64) k_mlp_train<4><<<blocks, 256, 0, s>>>(a);
     else k_mlp_train<2><<<blocks, 256, 0, s>>>(a);
-    k_sum_parts<<<1, 256, 0, s>>>(p->part, blocks, 1.f / (float)m, p->loss);
     MlpWgrad w{};
     for (int l = 0; l < NLAYER; ++l) {
         w.dZT[l] = a.dZT[l];
@@ -755,8 +774,27 @@ void launch_train(gbp_mlp p, const bf16* X, int m, const float* target, hipStrea
     w.n_params = p->n_params;
     const int splits = (w.kend + w.kchunk - 1) / w.kchunk;
     k_mlp_wgrad<<<dim3(kWgradTiles, splits), 256, 0, s>>>(w);
-    k_mlp_reduce_w<<<gbp_blocks(p->n_params, 256), 256, 0, s>>>(p->part_w, splits, p->n_params, p->grads);
-    k_mlp_reduce_b<<<(kBwdPart + 3) / 4, 256, 0, s>>>(p->part_b, blocks, p->grads);
+    MlpFinish f{};
+    f.loss_part = p->part;
+    f.pb = p->part_b;
+    f.pw = p->part_w;
+    f.loss = p->loss;
+    f.loss_out = loss;
+    f.g = p->grads;
+    f.blocks = blocks;
+    f.splits = splits;
+    f.n_params = p->n_params;
+    f.loss_scale = 1.f / (float)m;
+    if (step > 0) {
+        f.p = p->params;
+        f.m = p->m;
+        f.v = p->v;
+        f.lr = lr;
+        f.c1 = (float)(1.0 / (1.0 - std::pow(0.9, step)));
+        f.c2 = (float)(1.0 / (1.0 - std::pow(0.999, step)));
+        f.c = copies_of(p);
+    }
+    k_mlp_finish<<<1 + kBiasBlocks + gbp_blocks(p->n_params, 256), 256, 0, s>>>(f);
 }
 
 int check_rows(gbp_mlp p, int m) {
@@ -914,8 +952,9 @@ extern "C" int gbp_mlp_forward(gbp_mlp p, const uint16_t* X, int m, float out_sc
     return GBP_OK;
 }
 
-extern "C" int gbp_mlp_gradient(gbp_mlp p, const uint16_t* X, int m, const float* target,
-                                float* loss, void* stream) {
+// adam: followed by one step of it
+static int mlp_train(gbp_mlp p, const uint16_t* X, int m, const float* target, bool adam, float lr, float* loss,
+                     void* stream) {
     int rc = check_rows(p, m);
     if (rc) return rc;
     if (!X || !target) {
@@ -926,23 +965,18 @@ extern "C" int gbp_mlp_gradient(gbp_mlp p, const uint16_t* X, int m, const float
         gbp_set_error("mlp_gradient: X must be 16-byte aligned");
         return GBP_ERR_ARG;
     }
-    hipStream_t s = (hipStream_t)stream;
-    launch_train(p, (const bf16*)X, m, target, s);
+    if (adam) p->step += 1;
+    launch_train(p, (const bf16*)X, m, target, loss, adam ? p->step : 0, lr, (hipStream_t)stream);
     GBP_LAUNCH_CHECK();
-    if (loss) GBP_HIP(hipMemcpyAsync(loss, p->loss, sizeof(float), hipMemcpyDeviceToDevice, s));
     return GBP_OK;
+}
+
+extern "C" int gbp_mlp_gradient(gbp_mlp p, const uint16_t* X, int m, const float* target,
+                                float* loss, void* stream) {
+    return mlp_train(p, X, m, target, false, 0.f, loss, stream);
 }
 
 extern "C" int gbp_mlp_train_step(gbp_mlp p, const uint16_t* X, int m, const float* target,
                                   float lr, float* loss, void* stream) {
-    int rc = gbp_mlp_gradient(p, X, m, target, loss, stream);
-    if (rc) return rc;
-    hipStream_t s = (hipStream_t)stream;
-    p->step += 1;
-    const float c1 = (float)(1.0 / (1.0 - std::pow(0.9, p->step)));
-    const float c2 = (float)(1.0 / (1.0 - std::pow(0.999, p->step)));
-    k_adam_flat<<<gbp_blocks(p->n_params, 256), 256, 0, s>>>(p->params, p->grads, p->m, p->v,
-                                                             p->n_params, lr, c1, c2, copies_of(p));
-    GBP_LAUNCH_CHECK();
-    return GBP_OK;
+    return mlp_train(p, X, m, target, true, lr, loss, stream);
 }
