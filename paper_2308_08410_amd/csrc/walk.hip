@@ -185,8 +185,20 @@ __global__ void __launch_bounds__(TPB) k_child_sort(AdjGraph a) {
     }
 }
 
+// Data that the walk's blocks hand to one another, at the scope that holds them all: the
+// block (its loads may hit the CU's cache) or the device.
+template <int SCOPE, typename V>
+__device__ __forceinline__ V scoped_load(const V* p) {
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, SCOPE);
+}
+template <int SCOPE, typename V>
+__device__ __forceinline__ void scoped_store(V* p, V v) {
+    __hip_atomic_store(p, v, __ATOMIC_RELAXED, SCOPE);
+}
+
 // Sum of a pair member's right-hand side and entries but its partner's, whose weight
 // comes back in wo.
+template <int SCOPE>
 __device__ __forceinline__ float pair_sum(const AdjGraph& a, int v, int partner, float& wo) {
     const AdjRec* r = a.rec + v;
     float s = r->up[0].g;
@@ -194,21 +206,29 @@ __device__ __forceinline__ float pair_sum(const AdjGraph& a, int v, int partner,
     for (int k = 0; k < r->up[1].nchild; ++k) {
         const int at = r->first + k;
         if (a.cchild[at] == partner) wo = a.calpha[at];
-        else s += agent_load(k < kAdjEntries ? r->entry + k : a.over + at);
+        else s += scoped_load<SCOPE>(k < kAdjEntries ? r->entry + k : a.over + at);
     }
     return s;
 }
 
 constexpr int kWalkThreads = 8 * kWalkGroups;
 
-// One vertex x of the level, by the 8 lanes of a group: lane j loads piece j of its
-// record (one line, one request; lanes 0-2 a parent each, 4 and 5 the entries).
-// ready(p): parent p's last child is finished.
-template <class Ready>
-__device__ __forceinline__ void walk_vertex(const AdjGraph& a, int x, Ready ready) {
+// A vertex's record, by the 8 lanes of a group: lane j holds piece j (one line, one
+// request; lanes 0-2 a parent each, 4 and 5 the entries).
+struct RecPiece {
+    unsigned long long u0, u1;
+};
+template <int SCOPE>
+__device__ __forceinline__ RecPiece walk_record(const AdjGraph& a, int x) {
+    const unsigned long long* rp = reinterpret_cast<const unsigned long long*>(a.rec + x) + 2 * min(threadIdx.x & 7, 5u);
+    return {scoped_load<SCOPE>(rp), scoped_load<SCOPE>(rp + 1)};
+}
+
+// One vertex x of the level.  ready(p): parent p's last child is finished.
+template <int SCOPE, typename Ready>
+__device__ __forceinline__ void walk_vertex(const AdjGraph& a, int x, RecPiece piece, Ready ready) {
     const int j = threadIdx.x & 7, g0 = threadIdx.x & 56;   // lane in the group, the group's first lane
-    const unsigned long long* rp = reinterpret_cast<const unsigned long long*>(a.rec + x) + 2 * min(j, 5);
-    const unsigned long long u0 = agent_load(rp), u1 = agent_load(rp + 1);
+    const unsigned long long u0 = piece.u0, u1 = piece.u1;
     const float v0 = __uint_as_float((unsigned)u0), v1 = __uint_as_float((unsigned)(u0 >> 32)),
                 v2 = __uint_as_float((unsigned)u1), v3 = __uint_as_float((unsigned)(u1 >> 32));
     const float rhs = __shfl(v3, g0);
@@ -222,7 +242,7 @@ __device__ __forceinline__ void walk_vertex(const AdjGraph& a, int x, Ready read
             // entries past the record's, each lane every eighth
             float o = 0.f;
             const int first = a.rec[x].first;
-            for (int k = kAdjEntries + j; k < nchild; k += 8) o += agent_load(a.over + first + k);
+            for (int k = kAdjEntries + j; k < nchild; k += 8) o += scoped_load<SCOPE>(a.over + first + k);
             o += __shfl_xor(o, 1);
             o += __shfl_xor(o, 2);
             o += __shfl_xor(o, 4);
@@ -233,10 +253,10 @@ __device__ __forceinline__ void walk_vertex(const AdjGraph& a, int x, Ready read
         // a two-cycle: the second member to become ready solves the pair
         //   lam_a = S_a + w_ca lam_c,  lam_c = S_c + w_ac lam_a   (a < c)
         int second = 0;
-        if (j == 0) second = agent_add(&a.rec[min(x, q)].pair, -1) == 1;
+        if (j == 0) second = __hip_atomic_fetch_add(&a.rec[min(x, q)].pair, -1, __ATOMIC_RELAXED, SCOPE) == 1;
         if (!__shfl(second, g0)) return;
         float wx, wq;   // wx: weight of x in q's parent face
-        const float sx = pair_sum(a, x, q, wx), sq = pair_sum(a, q, x, wq);
+        const float sx = pair_sum<SCOPE>(a, x, q, wx), sq = pair_sum<SCOPE>(a, q, x, wq);
         if (x < q) {
             l = (sx + wx * sq) / (1.f - wx * wq);
             lq = sq + wq * l;
@@ -247,8 +267,8 @@ __device__ __forceinline__ void walk_vertex(const AdjGraph& a, int x, Ready read
     }
     auto hand_on = [&](int self, float lam, int p, int rk, float w, int skip) {
         if (p >= 0) {
-            const int left = p != skip ? agent_add(&a.rec[p].rem, -1) : 0;
-            agent_store(rk < kAdjEntries ? a.rec[p].entry + rk : a.over + (rk - kAdjEntries), w * lam);
+            const int left = p != skip ? __hip_atomic_fetch_add(&a.rec[p].rem, -1, __ATOMIC_RELAXED, SCOPE) : 0;
+            scoped_store<SCOPE>(rk < kAdjEntries ? a.rec[p].entry + rk : a.over + (rk - kAdjEntries), w * lam);
             if (left == 1) ready(p);
         }
         if (j == 3) {
@@ -266,10 +286,13 @@ __device__ __forceinline__ void walk_vertex(const AdjGraph& a, int x, Ready read
 // The walk by one block, for narrow levels: the level's list is in LDS (what does not
 // fit in memory), a level ends with a block barrier.  Bound by the chain list, record,
 // parents' counts, barrier, and from some 150 vertices a level on by what one CU can
-// request.  Triangle slice of 250k vertices (1,131 levels): 4.3 ms, 3.8 us a level
-// (5.6 ms by one thread per vertex over child lists).
+// request, so the next vertex's record is on its way while one is worked on, and what
+// the waves hand on goes by the CU's own cache.  An iteration on a triangle slice of
+// 250k vertices (1,416 levels): 7.0 ms, of which the walk 3.4 (7.8 ms with accesses at
+// the device's scope and each record loaded in its turn); 60,000: 2.71 and 2.92 ms.
 constexpr int kWalkList = 8192;
 
+constexpr int kBlock = __HIP_MEMORY_SCOPE_WORKGROUP;
 __global__ void __launch_bounds__(kWalkThreads) k_adj_walk_block(AdjGraph a, int levels) {
     __shared__ int list[2][kWalkList], count[3];
     if (threadIdx.x < 3) count[threadIdx.x] = 0;
@@ -278,13 +301,25 @@ __global__ void __launch_bounds__(kWalkThreads) k_adj_walk_block(AdjGraph a, int
     while (n > 0 && level < levels) {
         const int out = (level + 1) & 1;
         int* const n_out = &count[(level + 1) % 3];
-        for (int i = threadIdx.x >> 3; i < n; i += kWalkGroups) {
-            const int x = level == 0 ? a.leaf[i] : i < kWalkList ? list[level & 1][i] : agent_load(a.ready[level & 1] + i);
-            walk_vertex(a, x, [&](int p) {
+        const auto item = [&](int i) {
+            return level == 0 ? a.leaf[i] : i < kWalkList ? list[level & 1][i] : scoped_load<kBlock>(a.ready[level & 1] + i);
+        };
+        int i = threadIdx.x >> 3, x = i < n ? item(i) : -1;
+        RecPiece piece{};
+        if (x >= 0) piece = walk_record<kBlock>(a, x);
+        while (x >= 0) {
+            // the next vertex's record loads while this one is worked on
+            i += kWalkGroups;
+            const int x_next = i < n ? item(i) : -1;
+            RecPiece next{};
+            if (x_next >= 0) next = walk_record<kBlock>(a, x_next);
+            walk_vertex<kBlock>(a, x, piece, [&](int p) {
                 const int at = atomicAdd(n_out, 1);
                 if (at < kWalkList) list[out][at] = p;
-                else agent_store(a.ready[out] + at, p);
+                else scoped_store<kBlock>(a.ready[out] + at, p);
             });
+            x = x_next;
+            piece = next;
         }
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
         __builtin_amdgcn_s_waitcnt(0);   // this wave's entries are where the next level reads them
@@ -304,6 +339,7 @@ __global__ void __launch_bounds__(kWalkThreads) k_adj_walk_block(AdjGraph a, int
 // vertices, 299 levels: 1.27 ms, 4.3 us a level (1.45 ms as launches over a stamp per
 // vertex, and 1 us between them).  one_xcd: the team is one XCD's blocks, so that the
 // chain's accesses end in one L2.
+constexpr int kDevice = __HIP_MEMORY_SCOPE_AGENT;
 __global__ void __launch_bounds__(kWalkThreads) k_adj_walk_team(AdjGraph a, int levels, int one_xcd) {
     __shared__ int before[kTeamMax + 1], count[3];
     if (threadIdx.x < 3) count[threadIdx.x] = 0;
@@ -325,7 +361,8 @@ __global__ void __launch_bounds__(kWalkThreads) k_adj_walk_team(AdjGraph a, int 
                 while (before[m + 1] <= i) ++m;
                 x = agent_load(in + cap * m + (i - before[m]));
             }
-            walk_vertex(a, x, [&](int p) { agent_store(out + atomicAdd(n_out, 1), p); });
+            walk_vertex<kDevice>(a, x, walk_record<kDevice>(a, x),
+                                 [&](int p) { agent_store(out + atomicAdd(n_out, 1), p); });
         }
         ++level;
         n = team_sync(t, level, n_out, before, m);
