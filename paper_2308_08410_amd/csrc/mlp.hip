@@ -551,7 +551,7 @@ __global__ void k_refresh_copies(const float* __restrict__ p, int n, MlpCopies c
 // b1..b4, w5, b5 (lane k sums the blocks' partials k, k + 64, ..., a butterfly adds the
 // lanes); the others the splits' partials of the W1..W4 entries, in split order.  With p
 // given, an Adam step on the fp32 masters follows at once, refreshing their bf16 copies.
-// Bound by the splits' partials (16,384 rows: 52 MB, in the last-level cache): 11.5 us;
+// Bound by the splits' partials (16,384 rows: 26 MB, in the last-level cache): 11.5 us;
 // the misfit, the two reductions, the step and the copy of the misfit as launches of their
 // own took 22 us and four gaps (a 16,384-row step 122 us, now 113).
 struct MlpFinish {
