@@ -52,8 +52,9 @@ __device__ __forceinline__ int ordered(float x) {
 __device__ __forceinline__ float from_ordered(int b) { return __int_as_float(b < 0 ? b ^ 0x7fffffff : b); }
 
 // Joins the block to the launch's team (false: it is not a member and returns).
-// one_xcd: the blocks of one XCD, whichever the first block runs on.
-__device__ __forceinline__ bool team_join(TeamCtl* ctl, bool one_xcd, Team& t) {
+// one_xcd: the blocks of one XCD, whichever the first block runs on.  blocks: those of the
+// launch that ask to join (the same on all of them).
+__device__ __forceinline__ bool team_join(TeamCtl* ctl, bool one_xcd, Team& t, int blocks) {
     __shared__ int rank_sh, size_sh;
     if (threadIdx.x == 0) {
         bool mine = true;
@@ -69,7 +70,7 @@ __device__ __forceinline__ bool team_join(TeamCtl* ctl, bool one_xcd, Team& t) {
             r = agent_add(&ctl->joined, 1);
             if (r == 0) {
                 // blocks go to the 8 XCDs in turn
-                const int want = min(kTeamMax, one_xcd ? ((int)gridDim.x + 7) / 8 : (int)gridDim.x);
+                const int want = min(kTeamMax, one_xcd ? (blocks + 7) / 8 : blocks);
                 const long long t0 = wall_clock64();
                 while (agent_load(&ctl->joined) < want && wall_clock64() - t0 < kTeamWait) {}
                 n = min(kTeamMax, agent_add(&ctl->joined, kTeamClosed));
@@ -86,6 +87,10 @@ __device__ __forceinline__ bool team_join(TeamCtl* ctl, bool one_xcd, Team& t) {
     t.rank = rank_sh;
     t.size = size_sh;
     return t.rank >= 0 && t.rank < t.size;
+}
+
+__device__ __forceinline__ bool team_join(TeamCtl* ctl, bool one_xcd, Team& t) {
+    return team_join(ctl, one_xcd, t, gridDim.x);
 }
 
 // The block's share [i0, i1) of n items.

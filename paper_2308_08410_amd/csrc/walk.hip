@@ -454,10 +454,12 @@ __global__ void k_adj_swept(AdjCtl* ctl, int from, int count, float tol) {
 // XCD's, longer ones 64 blocks of all.
 // A sweep costs ~4 us on short lists (5-6 us and the gap to the next as a launch) and
 // 7-8 us on lists of 10-20 thousand, where it saves the host's looks (5.7 us and the gap
-// as a launch); beyond, the launches' requests by every CU win (600 thousand: 31 against
-// 70 us).
+// as a launch); beyond, the launches' plain requests by every CU win (170 thousand: 14
+// against 21 us by 256 blocks and 39 by 64; 600 thousand: 31 against 70 us), so a caller that
+// reads the length sweeps long lists that way.
 constexpr int kSweepThreads = 1024;
-constexpr int kSweepBlocks = 64;
+constexpr int kSweepFewBlocks = 64, kSweepBlocks = 256;
+constexpr int kSweepFewList = 32768;
 constexpr int kSweepOneXcd = 2048;
 constexpr int kSweepTeamVerts = 1 << 18;   // mesh size, which bounds the list, up to which a team sweeps
 
@@ -466,10 +468,12 @@ __global__ void __launch_bounds__(kSweepThreads) k_adj_sweeps(AdjGraph a, const 
     __shared__ int before[kTeamMax + 1], zero;
     __shared__ float red[2][kSweepThreads / 64];
     const int n = a.ctl->remaining;
-    if (n == 0) return;
+    const int blocks = n <= kSweepFewList ? kSweepFewBlocks : kSweepBlocks;
+    if (n == 0 || (int)blockIdx.x >= blocks) return;
+    if (!exhaust && n > kSweepFewList) return;   // the caller sees the length and sweeps by launches
     if (threadIdx.x == 0) zero = 0;
     Team t;
-    if (!team_join(a.team, n <= kSweepOneXcd, t)) return;   // uniform over the launch
+    if (!team_join(a.team, n <= kSweepOneXcd, t, blocks)) return;   // uniform over the launch
     int first, it = 0, slot = 0;
     bool settled = false, stop = false;
     while (it < max_sweeps && !stop) {
@@ -555,10 +559,10 @@ int gbp_adj_walk(const AdjGraph& a, int levels, bool narrow, int grid, hipStream
 }
 
 int gbp_adj_sweeps(const AdjGraph& a, int* list, bool build, int from, int count, float tol, bool exhaust,
-                   hipStream_t s) {
+                   hipStream_t s, int remaining) {
     ProfScope ps(GBP_PROF_AUX, s);
     if (build) k_adj_remaining<<<gbp_blocks(a.n_v, kLinkThreads), kLinkThreads, 0, s>>>(a, list);
-    if (a.n_v <= kSweepTeamVerts) {
+    if (a.n_v <= kSweepTeamVerts && remaining <= kSweepFewList) {
         k_sweeps_reset<<<1, 256, 0, s>>>(a.team, a.ctl);
         if (count > 0) k_adj_sweeps<<<kSweepBlocks, kSweepThreads, 0, s>>>(a, list, count, tol, exhaust);
     } else {
@@ -570,4 +574,6 @@ int gbp_adj_sweeps(const AdjGraph& a, int* list, bool build, int from, int count
     return GBP_OK;
 }
 
-int gbp_adj_sweep_batch(const AdjGraph& a) { return a.n_v <= kSweepTeamVerts ? 1024 : 16; }
+int gbp_adj_sweep_batch(const AdjGraph& a, int remaining) {
+    return a.n_v > kSweepTeamVerts ? 16 : remaining > kSweepFewList ? 32 : 1024;
+}

@@ -85,7 +85,7 @@ def _mean_of(d, substr):
     return sum(vals) / len(vals), len(vals)
 
 
-def traffic(fetch_path, write_path, kernel="k_sweep", copy_substr="neg", copy_mib=256, match=None):
+def traffic(fetch_path, write_path, kernel="k_sweep", copy_substr="neg", copy_mib=256, match=None, source="eikonal.hip"):
     """match: the substring that selects the kernel's dispatches (default: its
     name; e.g. one template instance)."""
     fetch = per_kernel(fetch_path, "FETCH_SIZE")
@@ -100,7 +100,7 @@ def traffic(fetch_path, write_path, kernel="k_sweep", copy_substr="neg", copy_mi
                 copy_fetch_kib_raw=f_c, copy_write_kib_raw=w_c, copy_mib=copy_mib,
                 fetch_scale=sf, write_scale=sw,
                 bytes_per_launch=1024.0 * (f_k * sf + w_k * sw),
-                source_hash=source_hash(kernel))
+                source_hash=source_hash(kernel, source))
 
 
 def mfma(path, kernel, source="ecg.hip", peak_tflops=2500.0, match=None):
@@ -261,7 +261,8 @@ def main(argv=None):
         return
     if not (args.fetch and args.write):
         ap.error("--fetch and --write are required without --mfma or --valu")
-    t = traffic(args.fetch, args.write, args.kernel, args.copy, args.copy_mib, match=args.match)
+    t = traffic(args.fetch, args.write, args.kernel, args.copy, args.copy_mib, match=args.match,
+                source=args.source or "eikonal.hip")
     with open(args.out, "w") as f:
         f.write(f"# HBM traffic per launch: {args.kernel}\n\n")
         f.write("Two rocprofv3 counter runs of the same command, FETCH_SIZE then WRITE_SIZE (KiB per\n"
