@@ -73,3 +73,27 @@ def test_triangle_walk_launches(target):
     assert abs(float(drt.double().sum()) - want) <= 1e-4 * want, info
     assert info["levels"] >= 1 and (info["sweeps"] > 0) == (info["cyclic"] > 0)
     plan.close()
+
+
+def test_long_list_of_cycles():
+    """Uniform scales on a fine slice: a cycle near a root leaves most vertices to the
+    sweeps, a list that launches sweep (the sweeps end at 1e-7 of the largest lambda and
+    contract in some 560, 35 times that in the sum)."""
+    import torch
+    from paper_2308_08410_amd import binding as B
+
+    dev = torch.device("cuda", 0)
+    p = gi.annulus_problem(250_000)
+    f32 = lambda x: torch.as_tensor(np.ascontiguousarray(x, np.float32), device=dev)
+    rn = torch.as_tensor(p.root_node, device=dev)
+    D, vs, rt = f32(p.D), f32(np.ones(p.n_v)), f32(p.root_t + 2.0)
+    g = f32(np.random.Generator(np.random.PCG64(4)).uniform(0, 1, p.n_v))
+    plan = B.TriPlan(p.xyz, p.tets)
+    T, _ = B.tri_forward(plan, D, vs, rn, rt)
+    _, _, drt = B.tri_backward(plan, D, vs, rn, rt, T, g, want_D=False)
+    info = B.tri_backward_info(plan)
+    print(f"[sweeps] {info}", flush=True)
+    want = float(g.double().sum())
+    assert abs(float(drt.double().sum()) - want) <= 1e-4 * want, info
+    assert info["cyclic"] > 32768 and info["sweeps"] % 32 == 0
+    plan.close()
