@@ -141,13 +141,13 @@ def stored_valu(kernel):
     return t
 
 
-def stored_traffic(kernel="k_sweep"):
+def stored_traffic(kernel="k_sweep", source="eikonal.hip"):
     """Measured HBM bytes per launch of a kernel on this workload, from the
     committed counter summary, while the kernel's source is unchanged since the
     counters were taken (else None)."""
     from paper_2308_08410_amd import profiling
     t = profiling.read_summary(os.path.join(PROFILES, f"{kernel}_shell500k_traffic.md"))
-    if not t or t.get("source_hash") != profiling.source_hash(kernel):
+    if not t or t.get("source_hash") != profiling.source_hash(kernel, source):
         return None
     return t["bytes_per_launch"]
 
@@ -867,7 +867,7 @@ def main():
         ab = adjoint_bytes(prob.n_v, prob.n_e)
         n_lv, ms_lv = prof["adj_level"]
         lv_ms = ms_lv / max(n_lv, 1)
-        lv_bytes = stored_traffic("k_adj_walk_team")
+        lv_bytes = stored_traffic("k_adj_walk_team", "walk.hip")
         detail["adjoint"] = dict(
             kernels="+".join(bwd_fams), ms_per_step=bwd_ms, algorithmic_bytes=ab,
             achieved_GBps=ab / (bwd_ms * 1e-3) / 1e9, frac=ab / (bwd_ms * 1e-3) / 1e9 / PEAK_HBM_GBS,
