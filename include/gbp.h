@@ -18,7 +18,7 @@
  *     only on the device, so the host reads the device's convergence flag (one
  *     batch of launches behind, so that the device does not idle) and returns
  *     when the solve is done, with its statistics and error code.  Their _async
- *     variants enqueue a fixed budget of launches and return at once (for graph
+ *     variants enqueue at most a budget of work and return at once (for graph
  *     capture and streams the caller does not want to block on); the ECG, loss
  *     and Adam calls are fully asynchronous.
  *   - Outputs are overwritten, never accumulated into.
