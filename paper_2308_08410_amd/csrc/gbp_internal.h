@@ -112,13 +112,13 @@ struct XcdQueues {
 void gbp_set_queue_layout(gbp_plan p, int split);
 
 // Adjoint: a vertex's record, one 128-byte line in pieces of 16 bytes.  Its children
-// hand over their alpha * lambda in the entries (child k of the sorted list in entry
-// k, later ones in an array beside the records).
+// hand over their lambda in the entries (child k of the sorted list in entry k, later
+// ones in an array beside the records), whose weights stand beside them.
 constexpr int kAdjEntries = 8;
 struct AdjParent {
     int vertex;        // a weighted parent or -1
     int rank;          // the entry in its list (from kAdjEntries on: child-list position + kAdjEntries)
-    float w;           // its weight
+    int pad;
     union {
         float g;       // [0] right-hand side
         int nchild;    // [1] children
@@ -132,6 +132,7 @@ struct alignas(128) AdjRec {
     int first;         // its child list's first position
     int pad;
     float entry[kAdjEntries];
+    float weight[kAdjEntries];
 };
 // A member's list of the vertices it made ready in a level holds at most 4 for each
 // vertex of its share of the level (a pair's two members release up to 2 each).
@@ -140,7 +141,8 @@ __host__ __device__ inline size_t walk_list_cap(int n_v, int size) {
     return 4 * ((size_t)n_v / size + kWalkGroups);
 }
 inline size_t walk_list_size(int n_v) { return 4 * ((size_t)n_v + (size_t)kWalkGroups * kTeamMax); }
-static_assert(sizeof(AdjParent) == 16 && offsetof(AdjRec, entry) == 64, "pieces 0-2 parents, 4 and 5 entries");
+static_assert(sizeof(AdjParent) == 16 && offsetof(AdjRec, entry) == 64 && sizeof(AdjRec) == 128,
+              "pieces 0-2 parents, 4 and 5 entries, 6 and 7 their weights");
 
 // Plain cold solves of meshes up to this size run their rounds in one launch.
 constexpr int kRoundsTeamVerts = 1 << 18;

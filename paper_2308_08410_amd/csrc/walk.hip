@@ -2,10 +2,13 @@
 //
 // Every vertex sums alpha_c lambda_c over its children c in a fixed order, so the
 // result does not depend on the order in which vertices finish.  The walk goes in
-// levels: a vertex is finished in the level after its last child, hands alpha lambda
+// levels: a vertex is finished in the level after its last child, hands its lambda
 // to its parents' entries and takes one off each parent's count of unfinished
 // children; the parents whose count that brought to zero are the next level.  One
 // launch walks all levels (team.h).
+//
+// A sum's products are exact and added in FP64, and a lambda is rounded once: with FP32
+// products and sums the largest relative error over 2,704 nodes was 1.2-1.3e-7.
 #include <algorithm>
 #include <climits>
 
@@ -55,11 +58,10 @@ __global__ void __launch_bounds__(kLinkThreads) k_adj_link(AdjGraph a, const flo
         const int wait = c - (pair ? 1 : 0);   // all its children but its partner, which is one of them
         leaf = wait == 0 && reached;
         const int4 pn = a.pnode[x];
-        const float4 w = a.pa[x];
-        float4* r = reinterpret_cast<float4*>(a.rec + x);   // rank: k_child_sort
-        r[0] = make_float4(__int_as_float(pn.x), 0.f, w.x, g);
-        r[1] = make_float4(__int_as_float(pn.y), 0.f, w.y, __int_as_float(c));
-        r[2] = make_float4(__int_as_float(pn.z), 0.f, w.z, __int_as_float(pair ? p : -1));
+        float4* r = reinterpret_cast<float4*>(a.rec + x);   // ranks and weights: k_child_sort
+        r[0] = make_float4(__int_as_float(pn.x), 0.f, 0.f, g);
+        r[1] = make_float4(__int_as_float(pn.y), 0.f, 0.f, __int_as_float(c));
+        r[2] = make_float4(__int_as_float(pn.z), 0.f, 0.f, __int_as_float(pair ? p : -1));
         r[4] = r[5] = make_float4(0.f, 0.f, 0.f, 0.f);
         a.rec[x].rem = wait;
         a.rec[x].pair = pair && x < p ? 2 : 0;
@@ -117,7 +119,8 @@ __global__ void k_child_fill(AdjGraph a) {
 }
 
 // Sort each child list by child id (fixed summation order -> deterministic), then
-// tell each child where its entry sits: its rank in the parent's list.  The entries
+// tell each child where its entry sits, its rank in the parent's list, and put the
+// first entries' weights in the parent's record (0 where there is no entry).  The entries
 // arrive as (child << 2 | which of the child's parents this is) from k_child_fill;
 // child ids are distinct within a list, so the packed keys sort in child order, and
 // the ids are written back unpacked.
@@ -163,6 +166,9 @@ __global__ void __launch_bounds__(TPB) k_child_sort(AdjGraph a) {
                 calpha[b + k] = al[k];
                 a.rec[c].up[ch[k] & 3].rank = k < kAdjEntries ? k : b + k + kAdjEntries;
             }
+        float4* w = reinterpret_cast<float4*>(a.rec[p].weight);
+        w[0] = make_float4(al[0], al[1], al[2], al[3]);
+        w[1] = make_float4(al[4], al[5], al[6], al[7]);
         return;
     }
     for (int x = b + 1; x < e; ++x) {
@@ -182,6 +188,7 @@ __global__ void __launch_bounds__(TPB) k_child_sort(AdjGraph a) {
         const int c = v >> 2;
         cchild[x] = c;
         a.rec[c].up[v & 3].rank = x - b < kAdjEntries ? x - b : x + kAdjEntries;
+        if (x - b < kAdjEntries) a.rec[p].weight[x - b] = calpha[x];
     }
 }
 
@@ -199,14 +206,15 @@ __device__ __forceinline__ void scoped_store(V* p, V v) {
 // Sum of a pair member's right-hand side and entries but its partner's, whose weight
 // comes back in wo.
 template <int SCOPE>
-__device__ __forceinline__ float pair_sum(const AdjGraph& a, int v, int partner, float& wo) {
+__device__ __forceinline__ double pair_sum(const AdjGraph& a, int v, int partner, double& wo) {
     const AdjRec* r = a.rec + v;
-    float s = r->up[0].g;
-    wo = 0.f;
+    double s = r->up[0].g;
+    wo = 0.0;
     for (int k = 0; k < r->up[1].nchild; ++k) {
         const int at = r->first + k;
-        if (a.cchild[at] == partner) wo = a.calpha[at];
-        else s += scoped_load<SCOPE>(k < kAdjEntries ? r->entry + k : a.over + at);
+        const double w = a.calpha[at];
+        if (a.cchild[at] == partner) wo = w;
+        else s += w * scoped_load<SCOPE>(k < kAdjEntries ? r->entry + k : a.over + at);
     }
     return s;
 }
@@ -214,14 +222,28 @@ __device__ __forceinline__ float pair_sum(const AdjGraph& a, int v, int partner,
 constexpr int kWalkThreads = 8 * kWalkGroups;
 
 // A vertex's record, by the 8 lanes of a group: lane j holds piece j (one line, one
-// request; lanes 0-2 a parent each, 4 and 5 the entries).
+// request; lanes 0-2 a parent each, 4 and 5 the entries, 6 and 7 their weights).
 struct RecPiece {
     unsigned long long u0, u1;
 };
 template <int SCOPE>
 __device__ __forceinline__ RecPiece walk_record(const AdjGraph& a, int x) {
-    const unsigned long long* rp = reinterpret_cast<const unsigned long long*>(a.rec + x) + 2 * min(threadIdx.x & 7, 5u);
+    const unsigned long long* rp = reinterpret_cast<const unsigned long long*>(a.rec + x) + 2 * (threadIdx.x & 7);
     return {scoped_load<SCOPE>(rp), scoped_load<SCOPE>(rp + 1)};
+}
+
+// The value N lanes on in the row of 16 (a vector move, no trip through LDS).
+template <int N>
+__device__ __forceinline__ int lane_ahead(int v) {
+    return __builtin_amdgcn_update_dpp(0, v, 0x100 + N, 0xf, 0xf, true);
+}
+template <int N>
+__device__ __forceinline__ float lane_ahead(float v) {
+    return __int_as_float(lane_ahead<N>(__float_as_int(v)));
+}
+template <int N>
+__device__ __forceinline__ double lane_ahead(double v) {
+    return __hiloint2double(lane_ahead<N>(__double2hiint(v)), lane_ahead<N>(__double2loint(v)));
 }
 
 // One vertex x of the level.  ready(p): parent p's last child is finished.
@@ -236,39 +258,37 @@ __device__ __forceinline__ void walk_vertex(const AdjGraph& a, int x, RecPiece p
     const int parent = j < 3 ? __float_as_int(v0) : -1, rank = __float_as_int(v1);
     float l, lq = 0.f;
     if (q < 0) {
-        float s = (v0 + v1) + (v2 + v3);
-        s = __shfl(s, g0 + 4) + __shfl(s, g0 + 5);
+        // lanes 4 and 5, the sum in lane 4
+        double s = (double)v0 * lane_ahead<2>(v0) + (double)v1 * lane_ahead<2>(v1) +
+                   (double)v2 * lane_ahead<2>(v2) + (double)v3 * lane_ahead<2>(v3);
+        s += lane_ahead<1>(s);
         if (nchild > kAdjEntries) {
             // entries past the record's, each lane every eighth
-            float o = 0.f;
+            double o = 0.0;
             const int first = a.rec[x].first;
-            for (int k = kAdjEntries + j; k < nchild; k += 8) o += scoped_load<SCOPE>(a.over + first + k);
+            for (int k = kAdjEntries + j; k < nchild; k += 8)
+                o += (double)a.calpha[first + k] * scoped_load<SCOPE>(a.over + first + k);
             o += __shfl_xor(o, 1);
             o += __shfl_xor(o, 2);
             o += __shfl_xor(o, 4);
             s += o;
         }
-        l = rhs + s;
+        l = __shfl((float)(rhs + s), g0 + 4);
     } else {
         // a two-cycle: the second member to become ready solves the pair
         //   lam_a = S_a + w_ca lam_c,  lam_c = S_c + w_ac lam_a   (a < c)
         int second = 0;
         if (j == 0) second = __hip_atomic_fetch_add(&a.rec[min(x, q)].pair, -1, __ATOMIC_RELAXED, SCOPE) == 1;
         if (!__shfl(second, g0)) return;
-        float wx, wq;   // wx: weight of x in q's parent face
-        const float sx = pair_sum<SCOPE>(a, x, q, wx), sq = pair_sum<SCOPE>(a, q, x, wq);
-        if (x < q) {
-            l = (sx + wx * sq) / (1.f - wx * wq);
-            lq = sq + wq * l;
-        } else {
-            lq = (sq + wq * sx) / (1.f - wq * wx);
-            l = sx + wx * lq;
-        }
+        double wx, wq;   // wx: weight of x in q's parent face
+        const double sx = pair_sum<SCOPE>(a, x, q, wx), sq = pair_sum<SCOPE>(a, q, x, wq);
+        l = (float)((sx + wx * sq) / (1.0 - wx * wq));
+        lq = (float)((sq + wq * sx) / (1.0 - wq * wx));
     }
-    auto hand_on = [&](int self, float lam, int p, int rk, float w, int skip) {
+    auto hand_on = [&](int self, float lam, int p, int rk, int skip) {
         if (p >= 0) {
             const int left = p != skip ? __hip_atomic_fetch_add(&a.rec[p].rem, -1, __ATOMIC_RELAXED, SCOPE) : 0;
-            scoped_store<SCOPE>(rk < kAdjEntries ? a.rec[p].entry + rk : a.over + (rk - kAdjEntries), w * lam);
+            scoped_store<SCOPE>(rk < kAdjEntries ? a.rec[p].entry + rk : a.over + (rk - kAdjEntries), lam);
             if (left == 1) ready(p);
         }
         if (j == 3) {
@@ -276,10 +296,10 @@ __device__ __forceinline__ void walk_vertex(const AdjGraph& a, int x, RecPiece p
             a.done[self] = 1;
         }
     };
-    hand_on(x, l, parent, rank, v2, q);
+    hand_on(x, l, parent, rank, q);
     if (q >= 0) {
         const AdjParent* up = a.rec[q].up + min(j, 2);
-        hand_on(q, lq, j < 3 ? up->vertex : -1, up->rank, up->w, x);
+        hand_on(q, lq, j < 3 ? up->vertex : -1, up->rank, x);
     }
 }
 
