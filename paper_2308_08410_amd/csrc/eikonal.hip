@@ -457,9 +457,7 @@ __device__ __forceinline__ float face_value(const int* __restrict__ nent,
 
 // ------------------------------------------------------------------ rounds in one launch
 // All rounds of a plain cold solve by a team of blocks, L lanes a vertex; member b writes
-// its pushes to list[cap * b ...], read with the prefix of the members' counts, and a
-// member's share of n vertices pushes at most as many times their largest number of
-// neighbours.  A round is a Jacobi step: round r reads the times of now[r & 1] and lowers
+// its pushes to list[cap * b ...], read with the prefix of the members' counts.  A round is a Jacobi step: round r reads the times of now[r & 1] and lowers
 // those of the other array, which holds the improvements of all rounds but the last; a
 // member repeats its own of that one (gain, by position in the round's queue) before it
 // adds its new ones.  The times do not depend on which vertex was first.
@@ -478,12 +476,11 @@ struct TeamLists {
     int* now[2];                  // [n_v] times, as ordered integers
     unsigned long long* gain[2];  // [n_v] vertex << 32 | its time, or all ones
     int* list[2];
-    int max_deg;
+    TeamListCap cap;
 };
 
 constexpr int kRoundThreads = 1024;
 constexpr int kRoundLanes = 16;
-int round_blocks(int n_v) { return n_v < 12288 ? 64 : n_v < 49152 ? 128 : 256; }
 
 __global__ void __launch_bounds__(kRoundThreads)
     k_rounds_team(const int2* __restrict__ nptr, const int* __restrict__ nent, const int4* __restrict__ tetv,
@@ -506,7 +503,7 @@ __global__ void __launch_bounds__(kRoundThreads)
     }
     Team t;
     if (!team_join(team, false, t)) return;
-    const size_t cap = team_list_cap(n_v, q.max_deg, t.size);
+    const size_t cap = q.cap(t.size);
     int v0, v1, m = 0;
     team_share(t, n_v, v0, v1);
     for (int i = v0 + (int)threadIdx.x; i < v1; i += kRoundThreads) {
@@ -1593,10 +1590,10 @@ int gbp_forward_impl(gbp_plan p, const float* D, const float* vscale, const int3
     if (team) {
         ProfScope ps(GBP_PROF_FIM_SWEEP, s);
         r = budget > 0 ? budget : p->max_rounds;
-        k_rounds_team<<<round_blocks(n_v), kRoundThreads, 0, s>>>(
+        k_rounds_team<<<p->team_blocks, kRoundThreads, 0, s>>>(
             p->nptr, p->nent, p->tetv, p->tetg, p->T, p->q[0], p->adj_ptr, p->adj, p->mark, p->ctl, p->team, p->blk, r,
             p->eps_rel, n_v, p->xq,
-            TeamLists{{p->now[0], p->now[1]}, {p->gain[0], p->gain[1]}, {p->list[0], p->list[1]}, p->max_deg},
+            TeamLists{{p->now[0], p->now[1]}, {p->gain[0], p->gain[1]}, {p->list[0], p->list[1]}, p->list_cap},
             budget > 0 ? 0 : 1);
     } else if (budget > 0) {
         for (; r < budget; ++r) launch_round(p, cold, ordered, r, s);

@@ -52,20 +52,21 @@ struct TeamCtl {
     unsigned long long flag[2][kTeamMax];   // per round parity and block: round << 32 | the block's count
 };
 
-// Members' lists of a relaxation round: a member's share of the round's vertices pushes at
-// most as many times their largest number of neighbours.
-__host__ __device__ inline size_t team_list_cap(int n_v, int max_deg, int size) {
-    const size_t most = ((size_t)n_v / size + 1) * max_deg;
-    return most < (size_t)n_v ? most : (size_t)n_v;
-}
-inline size_t team_list_size(int n_v, int max_deg) {   // for a team of any number of blocks
-    size_t most = 0;
-    for (int size = 1; size <= kTeamMax; ++size) {
-        const size_t all = size * team_list_cap(n_v, max_deg, size);
-        if (all > most) most = all;
+// Members' lists of a relaxation round: a member's share of the round's vertices, at most
+// n_v / size + 1, pushes no more than the most neighbours that so many vertices have, and
+// nothing twice in a round.  That sum over the k largest degrees is concave in k, so a
+// tangent bounds it for every size.
+struct TeamListCap {
+    int n_v, base, slope;   // the sum over k vertices is at most base + slope k
+    __host__ __device__ size_t operator()(int size) const {
+        const long long most = base + (long long)slope * (n_v / size + 1);
+        return (size_t)(most < n_v ? most : n_v);
     }
-    return most;
-}
+};
+// For teams of up to `blocks`, which is halved (to 32 at least) where the lists would be
+// longer than 64 entries a vertex: meshes with many vertices of very many neighbours.
+TeamListCap team_list_cap(int n_v, const int* degree, int& blocks);
+size_t team_list_size(const TeamListCap& cap, int blocks);
 
 // State of one adjoint walk (walk.h), zeroed before it.
 struct AdjCtl {
@@ -146,6 +147,8 @@ static_assert(sizeof(AdjParent) == 16 && offsetof(AdjRec, entry) == 64 && sizeof
 
 // Plain cold solves of meshes up to this size run their rounds in one launch.
 constexpr int kRoundsTeamVerts = 1 << 18;
+// Blocks of that launch; measured at k_rounds_team.
+inline int rounds_team_blocks(int n_v) { return n_v < 12288 ? 64 : n_v < 49152 ? 128 : 256; }
 
 struct gbp_plan_s {
     int device = 0;
@@ -181,7 +184,8 @@ struct gbp_plan_s {
     int* now[2] = {nullptr, nullptr};
     unsigned long long* gain[2] = {nullptr, nullptr};
     int* list[2] = {nullptr, nullptr};
-    int max_deg = 0;              // most neighbours of a vertex
+    TeamListCap list_cap{};       // entries of a member's list
+    int team_blocks = 0;          // most members
     // launch configuration (autotunable)
     int lanes = 16;               // lanes per vertex in a relaxation round (8, 16 or 32)
     int sweep_blocks = 2048;      // grid of a relaxation round (<= kStatBlocks)

@@ -14,6 +14,7 @@
 
 #include <algorithm>
 #include <cstdlib>
+#include <functional>
 #include <numeric>
 #include <type_traits>
 #include <vector>
@@ -70,6 +71,24 @@ static int upload(T** dst, const T* src, size_t n) {
 template <typename T>
 static int dalloc(T** dst, size_t n) {
     return upload<T>(dst, nullptr, n);
+}
+
+size_t team_list_size(const TeamListCap& cap, int blocks) {
+    size_t most = 0;
+    for (int size = 1; size <= blocks; ++size) most = std::max(most, size * cap(size));
+    return most;
+}
+
+TeamListCap team_list_cap(int n_v, const int* degree, int& blocks) {
+    std::vector<int> d(degree, degree + n_v);
+    std::sort(d.begin(), d.end(), std::greater<int>());
+    for (;; blocks /= 2) {
+        const int k = std::min(n_v, n_v / blocks + 1);   // a full team's share
+        const long long sum = std::accumulate(d.begin(), d.begin() + k, 0LL);
+        const int slope = d[k - 1];
+        const TeamListCap cap{n_v, (int)std::min<long long>(sum - (long long)k * slope, n_v), slope};
+        if (blocks <= 32 || team_list_size(cap, blocks) <= (size_t)64 * n_v) return cap;
+    }
 }
 
 static void plan_free(gbp_plan p) {
@@ -334,11 +353,16 @@ extern "C" int gbp_plan_create(const float* xyz, int n_v, const int32_t* tets, i
     TRY(dalloc(&p->q[0], n_v));
     TRY(dalloc(&p->q[1], n_v));
     TRY(dalloc(&p->mark, n_v));
-    for (int i = 0; i < n_v; ++i) p->max_deg = std::max(p->max_deg, adj_ptr[i + 1] - adj_ptr[i]);
-    for (int k = 0; k < 2 && n_v <= kRoundsTeamVerts; ++k) {
-        TRY(dalloc(&p->now[k], n_v));
-        TRY(dalloc(&p->gain[k], n_v));
-        TRY(dalloc(&p->list[k], team_list_size(n_v, p->max_deg)));
+    if (n_v <= kRoundsTeamVerts) {
+        std::vector<int> degree(n_v);
+        for (int i = 0; i < n_v; ++i) degree[i] = adj_ptr[i + 1] - adj_ptr[i];
+        p->team_blocks = rounds_team_blocks(n_v);
+        p->list_cap = team_list_cap(n_v, degree.data(), p->team_blocks);
+        for (int k = 0; k < 2; ++k) {
+            TRY(dalloc(&p->now[k], n_v));
+            TRY(dalloc(&p->gain[k], n_v));
+            TRY(dalloc(&p->list[k], team_list_size(p->list_cap, p->team_blocks)));
+        }
     }
     TRY(dalloc(&p->ctl, 1));
     TRY(dalloc(&p->team, 1));

@@ -60,7 +60,8 @@ struct gbp_tri_plan_s {
     int4* info = nullptr;         // incidence and neighbour ranges of a vertex
     int* tpos = nullptr;          // [3 n_t] position of a triangle's incidences
     TriInc* inc = nullptr;        // [3 n_t] as vent; of the forward's metric
-    int max_deg = 0;              // most neighbours of a vertex
+    TeamListCap list_cap{};       // a team's lists
+    int team_blocks = 0;          // its most members
     float* T = nullptr;
     int* now[2] = {nullptr, nullptr};   // a team's times, and each round's improvements
     unsigned long long* gain[2] = {nullptr, nullptr};
@@ -343,8 +344,7 @@ __global__ void __launch_bounds__(kTriThreads)
 }
 
 // Wider ones: all rounds by a team of blocks; member b writes its pushes to
-// list[cap * b ...], read with the prefix of the members' counts.  A member's share of n
-// vertices pushes at most as many times their largest number of neighbours.
+// list[cap * b ...], read with the prefix of the members' counts.
 // Round r reads the times of `now[r & 1]` and lowers those of the other array, which holds
 // the improvements of all rounds but the last; a member repeats its own of that one
 // (gain, by position in the round's queue) before it adds its new ones.
@@ -364,14 +364,14 @@ struct TriLists {
 };
 
 __global__ void __launch_bounds__(kTriThreads)
-    k_tri_rounds_team(TriRelax g, int n_v, int max_deg, TriLists q, int stamp, TeamCtl* team, TriCtl* ctl, int rounds,
+    k_tri_rounds_team(TriRelax g, int n_v, TeamListCap list_cap, TriLists q, int stamp, TeamCtl* team, TriCtl* ctl, int rounds,
                       float* __restrict__ T) {
     __shared__ int before[kTeamMax + 1], count[3];
     if (ctl->err) return;
     if (threadIdx.x < 3) count[threadIdx.x] = 0;
     Team t;
     if (!team_join(team, false, t)) return;
-    const size_t cap = team_list_cap(n_v, max_deg, t.size);
+    const size_t cap = list_cap(t.size);
     int n = ctl->count, r = 0, m = 0, p0 = 0, p1 = 0;
     unsigned long long all_solves = 0, all_upd = 0;
     while (n > 0 && r < rounds) {
@@ -696,10 +696,10 @@ extern "C" int gbp_tri_plan_create(const float* xy, int n_v, const int32_t* tris
         nbp[i + 1] = (int)nb.size();
     }
     std::vector<int4> info(n_v);
-    int max_deg = 0;
+    std::vector<int> degree(n_v);
     for (int i = 0; i < n_v; ++i) {
         info[i] = make_int4(vptr[i], vptr[i + 1], nbp[i], nbp[i + 1]);
-        max_deg = std::max(max_deg, nbp[i + 1] - nbp[i]);
+        degree[i] = nbp[i + 1] - nbp[i];
     }
     std::vector<float2> xy2(n_v);
     for (int i = 0; i < n_v; ++i) xy2[i] = make_float2(xy[2 * i], xy[2 * i + 1]);
@@ -711,7 +711,6 @@ extern "C" int gbp_tri_plan_create(const float* xy, int n_v, const int32_t* tris
     (void)hipGetDevice(&p->device);
     p->n_v = n_v;
     p->n_t = n_t;
-    p->max_deg = max_deg;
     int rc = GBP_OK;
 #define TRI_TRY(x)                  \
     if ((rc = (x)) != GBP_OK) {     \
@@ -739,9 +738,10 @@ extern "C" int gbp_tri_plan_create(const float* xy, int n_v, const int32_t* tris
     TRI_TRY(tri_alloc(&p->inc, (size_t)3 * n_t));
     TRI_TRY(tri_alloc(&p->q0, n_v));
     if (n_v > kTriBlockVerts) {
-        TRI_TRY(tri_alloc(&p->q[0], team_list_size(n_v, max_deg)));
-        TRI_TRY(tri_alloc(&p->q[1], team_list_size(n_v, max_deg)));
+        p->team_blocks = tri_team_blocks(n_v);
+        p->list_cap = team_list_cap(n_v, degree.data(), p->team_blocks);
         for (int k = 0; k < 2; ++k) {
+            TRI_TRY(tri_alloc(&p->q[k], team_list_size(p->list_cap, p->team_blocks)));
             TRI_TRY(tri_alloc(&p->now[k], n_v));
             TRI_TRY(tri_alloc(&p->gain[k], n_v));
         }
@@ -807,7 +807,7 @@ extern "C" int gbp_tri_forward(gbp_tri_plan p, const float* D, const float* vsca
         k_tri_rounds_block<<<1, kTriThreads, tri_block_lds(n_v), s>>>(g, n_v, p->T, p->q0, p->ctl, cap);
     } else {
         const TriLists q{p->now[0], p->now[1], p->gain[0], p->gain[1], p->q[0], p->q[1], p->q0, p->mark};
-        k_tri_rounds_team<<<tri_team_blocks(n_v), kTriThreads, 0, s>>>(g, n_v, p->max_deg, q, p->stamp, p->team, p->ctl,
+        k_tri_rounds_team<<<p->team_blocks, kTriThreads, 0, s>>>(g, n_v, p->list_cap, q, p->stamp, p->team, p->ctl,
                                                                        cap, p->T);
     }
     GBP_LAUNCH_CHECK();
