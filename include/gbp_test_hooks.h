@@ -21,6 +21,23 @@ extern "C" {
  */
 int gbp_plan_set_stamp_base(gbp_plan plan, int stamp);
 
+/*
+ * gbp_plan_set_team, gbp_tri_plan_set_team -- bounds on the teams of blocks that run a
+ * solve's rounds, the adjoint's levels and its sweeps in one launch (0: none): the
+ * blocks that found a team (the others join at the ends of rounds) and its blocks in
+ * all.  Otherwise a small or growing team needs a device that other work fills.
+ * Results do not depend on them.  Errors: GBP_ERR_ARG for negative bounds.
+ */
+int gbp_plan_set_team(gbp_plan plan, int founders, int most);
+int gbp_tri_plan_set_team(gbp_tri_plan plan, int founders, int most);
+
+/*
+ * gbp_plan_team, gbp_tri_plan_team -- blocks that founded the last launch's team and
+ * its blocks at the end.  Synchronises the device.  Errors: GBP_ERR_HIP.
+ */
+int gbp_plan_team(gbp_plan plan, int *founders, int *members);
+int gbp_tri_plan_team(gbp_tri_plan plan, int *founders, int *members);
+
 #ifdef __cplusplus
 }
 #endif

@@ -146,6 +146,10 @@ _tri_forward = _sig("gbp_tri_forward", [c_void_p, c_void_p, c_void_p, c_void_p, 
 _tri_backward = _sig("gbp_tri_backward", [c_void_p, c_void_p, c_void_p, c_void_p, c_void_p, c_int, c_void_p,
                                           c_void_p, c_void_p, c_void_p, c_void_p, c_void_p])
 _tri_backward_info = _sig("gbp_tri_backward_info", [c_void_p] + [ctypes.POINTER(c_int)] * 3)
+_set_team = _sig("gbp_plan_set_team", [c_void_p, c_int, c_int])
+_tri_set_team = _sig("gbp_tri_plan_set_team", [c_void_p, c_int, c_int])
+_team = _sig("gbp_plan_team", [c_void_p] + [ctypes.POINTER(c_int)] * 2)
+_tri_team = _sig("gbp_tri_plan_team", [c_void_p] + [ctypes.POINTER(c_int)] * 2)
 _last_error = _sig("gbp_last_error", [], ctypes.c_char_p)
 _version = _sig("gbp_version", [], ctypes.c_char_p)
 
@@ -582,6 +586,18 @@ def set_local_solver(plan: Plan, solver="exact", n_f=32, lipschitz="tight"):
 def set_stamp_base(plan: Plan, stamp: int):
     """Queue stamp base of the forward (for tests of its restart past 2^30)."""
     _check(_set_stamp(plan.handle, int(stamp)))
+
+
+def set_team(plan, founders: int = 0, most: int = 0):
+    """Bounds on a plan's teams of blocks, 0: none (for tests of small and growing ones)."""
+    _check((_tri_set_team if isinstance(plan, TriPlan) else _set_team)(plan.handle, int(founders), int(most)))
+
+
+def team(plan):
+    """(founders, members at the end) of the last launch's team (for tests)."""
+    a, b = c_int(), c_int()
+    _check((_tri_team if isinstance(plan, TriPlan) else _team)(plan.handle, ctypes.byref(a), ctypes.byref(b)))
+    return a.value, b.value
 
 
 def set_input_reuse(plan: Plan, on=True):

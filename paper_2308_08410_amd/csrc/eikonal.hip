@@ -487,7 +487,7 @@ __global__ void __launch_bounds__(kRoundThreads)
                   const float4* __restrict__ tetg, float* __restrict__ T, const int* __restrict__ q0,
                   const int* __restrict__ adj_ptr, const int* __restrict__ adj, int* mark, GbpCtl* ctl, TeamCtl* team,
                   unsigned long long* __restrict__ blk, int rounds, float eps_rel, int n_v, XcdQueues xq, TeamLists q,
-                  int stop_on_error) {
+                  int stop_on_error, TeamLimits limits) {
     __shared__ int before[kTeamMax + 1], count[3], seg[9];
     __shared__ unsigned long long sums[2];
     if (stop_on_error && ctl->err) {
@@ -502,23 +502,28 @@ __global__ void __launch_bounds__(kRoundThreads)
         for (int x = 0; x < 8; ++x) seg[x + 1] = seg[x] + ctl->qcnt[0][x];
     }
     Team t;
-    if (!team_join(team, false, t)) return;
-    const size_t cap = q.cap(t.size);
-    int v0, v1, m = 0;
-    team_share(t, n_v, v0, v1);
+    if (!team_join(team, false, t, limits)) return;
+    int v0 = 0, v1 = 0, m = 0;
+    if (!t.late) team_share(t, n_v, v0, v1);
     for (int i = v0 + (int)threadIdx.x; i < v1; i += kRoundThreads) {
         const int b = ordered(T[i]);
         agent_store(q.now[0] + i, b);
         agent_store(q.now[1] + i, b);
     }
-    team_sync(t, 1, &count[0], before, m);
     int n = seg[8], r = 0, p0 = 0, p1 = 0;
+    if (t.late < 2) {
+        team_sync(t, 1, &count[0], before, m);
+    } else {
+        r = t.late - 2;
+        n = 1;
+    }
+    size_t cap = q.cap(t.size), cap_out = cap;
     unsigned solves = 0, upd = 0;
     const int lane = threadIdx.x & (kRoundLanes - 1);
     while (n > 0 && r < rounds) {
         const int odd = r & 1;
         const int* in = odd ? q.list[1] : q.list[0];
-        int* out = (odd ? q.list[0] : q.list[1]) + cap * t.rank;
+        int* out = (odd ? q.list[0] : q.list[1]) + cap_out * t.rank;
         int* n_out = &count[(r + 1) % 3];
         const int* T0 = odd ? q.now[1] : q.now[0];
         int* T1 = odd ? q.now[0] : q.now[1];
@@ -533,7 +538,7 @@ __global__ void __launch_bounds__(kRoundThreads)
         }
         const int next = stamp + r + 1;
         const TeamTimes time{T0};
-        team_share(t, n, p0, p1);
+        if (!t.late) team_share(t, n, p0, p1);
         for (int k = p0 + (int)threadIdx.x / kRoundLanes; k < p1; k += kRoundThreads / kRoundLanes) {
             int i;
             if (r == 0) {
@@ -586,9 +591,13 @@ __global__ void __launch_bounds__(kRoundThreads)
         }
         ++r;
         n = team_sync(t, r + 1, n_out, before, m);
+        cap = cap_out;
+        if (t.size != t.was) cap_out = q.cap(t.size);
         if (threadIdx.x == 0) count[(r + 2) % 3] = 0;   // read by all before the sync, used after the next
     }
+    team_leave(t);
     const int* T0 = r & 1 ? q.now[1] : q.now[0];
+    team_share(t, n_v, v0, v1);
     for (int i = v0 + (int)threadIdx.x; i < v1; i += kRoundThreads) T[i] = from_ordered(agent_load(T0 + i));
     atomicAdd(&sums[0], (unsigned long long)solves);
     atomicAdd(&sums[1], (unsigned long long)upd);
@@ -1594,7 +1603,7 @@ int gbp_forward_impl(gbp_plan p, const float* D, const float* vscale, const int3
             p->nptr, p->nent, p->tetv, p->tetg, p->T, p->q[0], p->adj_ptr, p->adj, p->mark, p->ctl, p->team, p->blk, r,
             p->eps_rel, n_v, p->xq,
             TeamLists{{p->now[0], p->now[1]}, {p->gain[0], p->gain[1]}, {p->list[0], p->list[1]}, p->list_cap},
-            budget > 0 ? 0 : 1);
+            budget > 0 ? 0 : 1, p->team_limits);
     } else if (budget > 0) {
         for (; r < budget; ++r) launch_round(p, cold, ordered, r, s);
     } else {
@@ -1724,6 +1733,7 @@ int gbp_backward_impl(gbp_plan p, const float* D, const float* vscale, const int
     a.ready[0] = p->ready[0];
     a.ready[1] = p->ready[1];
     a.team = p->team;
+    a.limits = p->team_limits;
     a.done = p->done;
     a.g = p->g;
     a.lam = p->lam;

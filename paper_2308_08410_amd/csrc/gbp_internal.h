@@ -46,10 +46,17 @@ enum : int {
 constexpr int kTeamMax = 256;          // blocks
 struct TeamCtl {
     int home;      // 1 + the XCD whose blocks may join
-    int joined;    // blocks that asked to join, marked once the team is closed
-    int size;      // blocks in the team (0: open)
+    int joined;    // blocks that asked to join
+    int size;      // blocks that founded it (0: open)
+    int members;   // blocks at its end
+    int taken[2];  // per parity, the last round whose end took blocks in
+    int over;      // 1: the team is done
     int pad;
-    unsigned long long flag[2][kTeamMax];   // per round parity and block: round << 32 | the block's count
+    unsigned long long flag[2][kTeamMax];   // per round parity and member, its word (team_word)
+};
+// Bounds on a team (0: none): blocks that found it, blocks in all.
+struct TeamLimits {
+    int found = 0, most = 0;
 };
 
 // Members' lists of a relaxation round: a member's share of the round's vertices, at most
@@ -186,6 +193,7 @@ struct gbp_plan_s {
     int* list[2] = {nullptr, nullptr};
     TeamListCap list_cap{};       // entries of a member's list
     int team_blocks = 0;          // most members
+    TeamLimits team_limits;       // of every team (tests)
     // launch configuration (autotunable)
     int lanes = 16;               // lanes per vertex in a relaxation round (8, 16 or 32)
     int sweep_blocks = 2048;      // grid of a relaxation round (<= kStatBlocks)
@@ -248,6 +256,8 @@ constexpr int kStatBlocks = 2048;   // max grid of the relaxation kernels
 constexpr int kStWords = 16;
 
 int gbp_plan_check(gbp_plan p);
+int gbp_team_bounds(int founders, int most, TeamLimits& out);
+int gbp_team_read(const TeamCtl* team, int* founders, int* members);
 int gbp_err_from_bits(int bits);
 // budget <= 0: synchronous; > 0: fixed launch counts, graph-capturable
 int gbp_forward_impl(gbp_plan p, const float* D, const float* vscale, const int32_t* root_node,

@@ -592,6 +592,35 @@ extern "C" int gbp_plan_set_stamp_base(gbp_plan p, int stamp) {
     return GBP_OK;
 }
 
+int gbp_team_bounds(int founders, int most, TeamLimits& out) {
+    if (founders < 0 || most < 0) {
+        gbp_set_error("set_team: bounds must be >= 0");
+        return GBP_ERR_ARG;
+    }
+    out.found = founders;
+    out.most = most;
+    return GBP_OK;
+}
+
+int gbp_team_read(const TeamCtl* team, int* founders, int* members) {
+    int head[offsetof(TeamCtl, flag) / sizeof(int)];
+    GBP_HIP(hipDeviceSynchronize());
+    GBP_HIP(hipMemcpy(head, team, sizeof(head), hipMemcpyDeviceToHost));
+    if (founders) *founders = head[offsetof(TeamCtl, size) / sizeof(int)];
+    if (members) *members = head[offsetof(TeamCtl, members) / sizeof(int)];
+    return GBP_OK;
+}
+
+extern "C" int gbp_plan_set_team(gbp_plan p, int founders, int most) {
+    int rc = gbp_plan_check(p);
+    return rc ? rc : gbp_team_bounds(founders, most, p->team_limits);
+}
+
+extern "C" int gbp_plan_team(gbp_plan p, int* founders, int* members) {
+    int rc = gbp_plan_check(p);
+    return rc ? rc : gbp_team_read(p->team, founders, members);
+}
+
 extern "C" int gbp_plan_get_queue_split(gbp_plan p, int* split) {
     if (!p || !split) {
         gbp_set_error("get_queue_split: NULL argument");

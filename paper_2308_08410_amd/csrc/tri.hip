@@ -25,6 +25,7 @@
 #include <vector>
 
 #include "gbp_internal.h"
+#include "gbp_test_hooks.h"
 #include "local_solve.h"
 #include "team.h"
 #include "walk.h"
@@ -62,6 +63,7 @@ struct gbp_tri_plan_s {
     TriInc* inc = nullptr;        // [3 n_t] as vent; of the forward's metric
     TeamListCap list_cap{};       // a team's lists
     int team_blocks = 0;          // its most members
+    TeamLimits team_limits;       // of every team (tests)
     float* T = nullptr;
     int* now[2] = {nullptr, nullptr};   // a team's times, and each round's improvements
     unsigned long long* gain[2] = {nullptr, nullptr};
@@ -365,19 +367,19 @@ struct TriLists {
 
 __global__ void __launch_bounds__(kTriThreads)
     k_tri_rounds_team(TriRelax g, int n_v, TeamListCap list_cap, TriLists q, int stamp, TeamCtl* team, TriCtl* ctl, int rounds,
-                      float* __restrict__ T) {
+                      float* __restrict__ T, TeamLimits limits) {
     __shared__ int before[kTeamMax + 1], count[3];
     if (ctl->err) return;
     if (threadIdx.x < 3) count[threadIdx.x] = 0;
     Team t;
-    if (!team_join(team, false, t)) return;
-    const size_t cap = list_cap(t.size);
-    int n = ctl->count, r = 0, m = 0, p0 = 0, p1 = 0;
+    if (!team_join(team, false, t, limits)) return;
+    int n = t.late ? 1 : ctl->count, r = t.late ? t.late - 1 : 0, m = 0, p0 = 0, p1 = 0;
+    size_t cap = list_cap(t.size), cap_out = cap;
     unsigned long long all_solves = 0, all_upd = 0;
     while (n > 0 && r < rounds) {
         const bool odd = r & 1;
         const int* in = odd ? q.list1 : q.list0;
-        int* out = (odd ? q.list0 : q.list1) + cap * t.rank;
+        int* out = (odd ? q.list0 : q.list1) + cap_out * t.rank;
         int* n_out = &count[(r + 1) % 3];
         const int* T0 = odd ? q.now1 : q.now0;
         int* T1 = odd ? q.now0 : q.now1;
@@ -392,7 +394,7 @@ __global__ void __launch_bounds__(kTriThreads)
         }
         const int next = stamp + r + 1;
         unsigned solves = 0, upd = 0;
-        team_share(t, n, p0, p1);
+        if (!t.late) team_share(t, n, p0, p1);
         for (int k = p0 + threadIdx.x / kTriLanes; k < p1; k += kTriThreads / kTriLanes) {
             int i;
             if (r == 0) {
@@ -419,8 +421,11 @@ __global__ void __launch_bounds__(kTriThreads)
         all_upd += upd;
         ++r;
         n = team_sync(t, r, n_out, before, m);
+        cap = cap_out;
+        if (t.size != t.was) cap_out = list_cap(t.size);
         if (threadIdx.x == 0) count[(r + 2) % 3] = 0;   // read by all before the sync, used after the next
     }
+    team_leave(t);
     const int* T0 = r & 1 ? q.now1 : q.now0;
     int i0, i1;
     team_share(t, n_v, i0, i1);
@@ -778,6 +783,22 @@ extern "C" int gbp_tri_plan_create(const float* xy, int n_v, const int32_t* tris
 
 extern "C" void gbp_tri_plan_destroy(gbp_tri_plan p) { tri_free(p); }
 
+extern "C" int gbp_tri_plan_set_team(gbp_tri_plan p, int founders, int most) {
+    if (!p) {
+        gbp_set_error("null triangle plan");
+        return GBP_ERR_ARG;
+    }
+    return gbp_team_bounds(founders, most, p->team_limits);
+}
+
+extern "C" int gbp_tri_plan_team(gbp_tri_plan p, int* founders, int* members) {
+    if (!p) {
+        gbp_set_error("null triangle plan");
+        return GBP_ERR_ARG;
+    }
+    return gbp_team_read(p->team, founders, members);
+}
+
 extern "C" int gbp_tri_backward_info(gbp_tri_plan p, int* levels, int* cyclic, int* sweeps) {
     if (!p) {
         gbp_set_error("null triangle plan");
@@ -808,7 +829,7 @@ extern "C" int gbp_tri_forward(gbp_tri_plan p, const float* D, const float* vsca
     } else {
         const TriLists q{p->now[0], p->now[1], p->gain[0], p->gain[1], p->q[0], p->q[1], p->q0, p->mark};
         k_tri_rounds_team<<<p->team_blocks, kTriThreads, 0, s>>>(g, n_v, p->list_cap, q, p->stamp, p->team, p->ctl,
-                                                                       cap, p->T);
+                                                                       cap, p->T, p->team_limits);
     }
     GBP_LAUNCH_CHECK();
     k_tri_count_inf<<<gbp_blocks(n_v, TPB), TPB, 0, s>>>(p->T, n_v, p->ctl);
@@ -867,6 +888,7 @@ extern "C" int gbp_tri_backward(gbp_tri_plan p, const float* D, const float* vsc
     a.ready[0] = p->ready[0];
     a.ready[1] = p->ready[1];
     a.team = p->team;
+    a.limits = p->team_limits;
     a.done = p->done;
     a.g = p->g;
     a.lam = p->lam;

@@ -24,6 +24,7 @@ struct AdjGraph {
     float *g, *lam;        // [n_v]
     AdjCtl* ctl;           // zeroed before gbp_adj_lists
     TeamCtl* team;         // zeroed before gbp_adj_lists
+    TeamLimits limits;     // of its teams
 };
 
 // Child lists, two-cycle partners, right-hand side (node_user: internal -> caller

@@ -364,15 +364,15 @@ __global__ void __launch_bounds__(kWalkThreads) k_adj_walk_team(AdjGraph a, int 
     __shared__ int before[kTeamMax + 1], count[3];
     if (threadIdx.x < 3) count[threadIdx.x] = 0;
     Team t;
-    if (!team_join(a.team, one_xcd, t)) return;
-    const size_t cap = walk_list_cap(a.n_v, t.size);
-    int n = a.ctl->nleaf, level = 0, m = 0;
+    if (!team_join(a.team, one_xcd, t, a.limits)) return;
+    int n = t.late ? 1 : a.ctl->nleaf, level = t.late ? t.late - 1 : 0, m = 0;
+    size_t cap = walk_list_cap(a.n_v, t.size), cap_out = cap;
     while (n > 0 && level < levels) {
         const int* in = level == 0 ? a.leaf : a.ready[level & 1];
-        int* out = a.ready[(level + 1) & 1] + cap * t.rank;
+        int* out = a.ready[(level + 1) & 1] + cap_out * t.rank;
         int* const n_out = &count[(level + 1) % 3];
-        int i0, i1;
-        team_share(t, n, i0, i1);
+        int i0 = 0, i1 = 0;
+        if (!t.late) team_share(t, n, i0, i1);
         for (int i = i0 + (threadIdx.x >> 3); i < i1; i += kWalkGroups) {
             int x;
             if (level == 0) {
@@ -386,8 +386,11 @@ __global__ void __launch_bounds__(kWalkThreads) k_adj_walk_team(AdjGraph a, int 
         }
         ++level;
         n = team_sync(t, level, n_out, before, m);
+        cap = cap_out;
+        if (t.size != t.was) cap_out = walk_list_cap(a.n_v, t.size);
         if (threadIdx.x == 0) count[(level + 2) % 3] = 0;   // read by all before the sync, used after the next
     }
+    team_leave(t);
     if (t.rank == 0 && threadIdx.x == 0) a.ctl->levels = level;
 }
 
@@ -493,12 +496,12 @@ __global__ void __launch_bounds__(kSweepThreads) k_adj_sweeps(AdjGraph a, const 
     if (!exhaust && n > kSweepFewList) return;   // the caller sees the length and sweeps by launches
     if (threadIdx.x == 0) zero = 0;
     Team t;
-    if (!team_join(a.team, n <= kSweepOneXcd, t, blocks)) return;   // uniform over the launch
-    int first, it = 0, slot = 0;
+    if (!team_join(a.team, n <= kSweepOneXcd, t, blocks, a.limits)) return;   // uniform over the launch
+    int first, it = t.late ? t.late - 1 : 0, slot = it / 16 % 3;   // a check is every 16th sweep's
     bool settled = false, stop = false;
     while (it < max_sweeps && !stop) {
         float d = 0.f, m = 0.f;
-        for (int q = threadIdx.x * t.size + t.rank; q < n; q += t.size * kSweepThreads) {
+        for (int q = t.late ? n : threadIdx.x * t.size + t.rank; q < n; q += t.size * kSweepThreads) {
             const int i = list[q];
             const int2 r = a.crange[i];
             float l = a.g[i];
@@ -540,6 +543,7 @@ __global__ void __launch_bounds__(kSweepThreads) k_adj_sweeps(AdjGraph a, const 
             slot = (slot + 1) % 3;
         }
     }
+    team_leave(t);
     if (t.rank == 0 && threadIdx.x == 0) {
         a.ctl->sweeps += it;
         a.ctl->settled = settled;
