@@ -1752,8 +1752,7 @@ int gbp_backward_impl(gbp_plan p, const float* D, const float* vscale, const int
         if (p->ctl_host->err) return gbp_err_from_bits(p->ctl_host->err);
         const int cap = 4 * p->max_rounds + 1000;
         while (c.remaining > 0 && !c.settled && c.sweeps < cap) {
-            if ((rc = gbp_adj_sweeps(a, p->cfill, false, c.sweeps, gbp_adj_sweep_batch(a, c.remaining), 1e-6f, false, s,
-                                     c.remaining))) return rc;
+            if ((rc = gbp_adj_sweeps(a, p->cfill, false, c.sweeps, batch, 1e-6f, false, s))) return rc;
             if ((rc = read_ctl(p, s))) return rc;
         }
         p->bwd_levels = p->last_levels = c.levels;

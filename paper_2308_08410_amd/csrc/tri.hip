@@ -904,8 +904,7 @@ extern "C" int gbp_tri_backward(gbp_tri_plan p, const float* D, const float* vsc
     const AdjCtl& c = p->ctl_host->adj;
     const int cap = 8 * n_v + 64;
     while (c.remaining > 0 && !c.settled && c.sweeps < cap) {
-        if ((rc = gbp_adj_sweeps(a, p->cfill, false, c.sweeps, gbp_adj_sweep_batch(a, c.remaining), 1e-7f, false, s,
-                                     c.remaining))) return rc;
+        if ((rc = gbp_adj_sweeps(a, p->cfill, false, c.sweeps, batch, 1e-7f, false, s))) return rc;
         if ((rc = tri_read(p, s))) return rc;
     }
     p->last_levels = c.levels;

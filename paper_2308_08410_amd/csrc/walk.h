@@ -41,8 +41,7 @@ int gbp_adj_walk(const AdjGraph& a, int levels, bool narrow, int grid, hipStream
 // that the walk left (ctl->remaining of them in list [n_v], listed if `build`), in place.
 // ctl->sweeps: sweeps so far; ctl->settled: the last moved no lambda by more than tol
 // times the largest.  exhaust: they go on to `count` unless nothing changes any more,
-// else they may end once settled (or, on a long list, not begin).  remaining: the list's
-// length where the host knows it, else 0.
+// else they may end once settled.
 int gbp_adj_sweeps(const AdjGraph& a, int* list, bool build, int from, int count, float tol, bool exhaust,
-                   hipStream_t s, int remaining = 0);
-int gbp_adj_sweep_batch(const AdjGraph& a, int remaining = 0);   // sweeps worth enqueueing between the host's looks
+                   hipStream_t s);
+int gbp_adj_sweep_batch(const AdjGraph& a);   // sweeps worth enqueueing between the host's looks

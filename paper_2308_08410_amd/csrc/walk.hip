@@ -472,17 +472,18 @@ __global__ void k_adj_swept(AdjCtl* ctl, int from, int count, float tol) {
     ctl->settled = count > 0 && __int_as_float(ctl->diff[slot]) <= tol * __int_as_float(ctl->lmax[slot]);
 }
 
-// All sweeps in one launch, by a team: the change is looked at after every 16th and the
-// last; lambdas pass between the blocks as the walk's entries do.  Short lists are one
-// XCD's, longer ones 64 blocks of all.
-// A sweep costs ~4 us on short lists (5-6 us and the gap to the next as a launch) and
-// 7-8 us on lists of 10-20 thousand, where it saves the host's looks (5.7 us and the gap
-// as a launch); beyond, the launches' plain requests by every CU win (170 thousand: 14
-// against 21 us by 256 blocks and 39 by 64; 600 thousand: 31 against 70 us), so a caller that
-// reads the length sweeps long lists that way.
+// All sweeps in one launch, by a team: the change is looked at after every 16th (every
+// 32nd of a long list) and the last; lambdas pass between the blocks as the walk's entries
+// do.  A wave takes 64 neighbours in the list, most of which share lines, and the waves are
+// dealt out over the blocks (one entry a block in turn: 21 us a sweep of 170 thousand).
+// Short lists are one XCD's, longer ones 64 blocks of all, the longest 256.  Us a sweep by
+// 8 / 64 / 256 blocks: 3 thousand 2.8 / 2.6 / 4.0, 17 thousand 8.5 / 4.7 / 6.2, 51 thousand
+// 24 / 6.9 / 9.0, 77 thousand 32 / 7.8 / 8.0, 112 thousand 45 / 9.6 / 8.5, 171 thousand
+// 66 / 12.5 / 8.9; as launches 5.7 at 17 thousand, 12 at 52, 17.7 at 171 (and, past the
+// mesh size below, 31 us for 600 thousand, where the team's scattered requests took 70).
 constexpr int kSweepThreads = 1024;
 constexpr int kSweepFewBlocks = 64, kSweepBlocks = 256;
-constexpr int kSweepFewList = 32768;
+constexpr int kSweepFewList = 65536;
 constexpr int kSweepOneXcd = 2048;
 constexpr int kSweepTeamVerts = 1 << 18;   // mesh size, which bounds the list, up to which a team sweeps
 
@@ -493,15 +494,16 @@ __global__ void __launch_bounds__(kSweepThreads) k_adj_sweeps(AdjGraph a, const 
     const int n = a.ctl->remaining;
     const int blocks = n <= kSweepFewList ? kSweepFewBlocks : kSweepBlocks;
     if (n == 0 || (int)blockIdx.x >= blocks) return;
-    if (!exhaust && n > kSweepFewList) return;   // the caller sees the length and sweeps by launches
+    const int every = n <= kSweepFewList ? 16 : 32;
     if (threadIdx.x == 0) zero = 0;
     Team t;
     if (!team_join(a.team, n <= kSweepOneXcd, t, blocks, a.limits)) return;   // uniform over the launch
-    int first, it = t.late ? t.late - 1 : 0, slot = it / 16 % 3;   // a check is every 16th sweep's
+    int first, it = t.late ? t.late - 1 : 0, slot = it / every % 3;
     bool settled = false, stop = false;
     while (it < max_sweeps && !stop) {
         float d = 0.f, m = 0.f;
-        for (int q = t.late ? n : threadIdx.x * t.size + t.rank; q < n; q += t.size * kSweepThreads) {
+        int q = ((threadIdx.x >> 6) * t.size + t.rank) * 64 + (threadIdx.x & 63);
+        for (q = t.late ? n : q; q < n; q += t.size * kSweepThreads) {
             const int i = list[q];
             const int2 r = a.crange[i];
             float l = a.g[i];
@@ -512,7 +514,7 @@ __global__ void __launch_bounds__(kSweepThreads) k_adj_sweeps(AdjGraph a, const 
             agent_store(a.lam + i, l);
         }
         ++it;
-        const bool check = it % 16 == 0 || it == max_sweeps;
+        const bool check = it % every == 0 || it == max_sweeps;
         if (check) {   // uniform over the team
             for (int o = 32; o > 0; o >>= 1) {
                 d = fmaxf(d, __shfl_xor(d, o));
@@ -583,10 +585,10 @@ int gbp_adj_walk(const AdjGraph& a, int levels, bool narrow, int grid, hipStream
 }
 
 int gbp_adj_sweeps(const AdjGraph& a, int* list, bool build, int from, int count, float tol, bool exhaust,
-                   hipStream_t s, int remaining) {
+                   hipStream_t s) {
     ProfScope ps(GBP_PROF_AUX, s);
     if (build) k_adj_remaining<<<gbp_blocks(a.n_v, kLinkThreads), kLinkThreads, 0, s>>>(a, list);
-    if (a.n_v <= kSweepTeamVerts && remaining <= kSweepFewList) {
+    if (a.n_v <= kSweepTeamVerts) {
         k_sweeps_reset<<<1, 256, 0, s>>>(a.team, a.ctl);
         if (count > 0) k_adj_sweeps<<<kSweepBlocks, kSweepThreads, 0, s>>>(a, list, count, tol, exhaust);
     } else {
@@ -598,6 +600,4 @@ int gbp_adj_sweeps(const AdjGraph& a, int* list, bool build, int from, int count
     return GBP_OK;
 }
 
-int gbp_adj_sweep_batch(const AdjGraph& a, int remaining) {
-    return a.n_v > kSweepTeamVerts ? 16 : remaining > kSweepFewList ? 32 : 1024;
-}
+int gbp_adj_sweep_batch(const AdjGraph& a) { return a.n_v > kSweepTeamVerts ? 16 : 1024; }

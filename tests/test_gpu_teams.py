@@ -135,3 +135,20 @@ def test_two_streams():
                 assert st["forward_converged"] and st["backward_settled"]
                 for x, y in zip(g, w):
                     assert torch.equal(x, y)
+
+
+@pytest.mark.parametrize("cells", [45, 63, 64])   # a team's list on both sides of 65,536; launches
+def test_long_lists(cells):
+    """An enqueue-only backward whose levels end early leaves long lists to the sweeps,
+    which end where the walk does: each is exact once its children are, so as many sweeps
+    as there are levels suffice."""
+    plan, D, vs, rn, rt, g = cube(cells, False)
+    a = (plan, D, vs, rn, rt)
+    T, _ = B().eikonal_forward(*a)
+    G0 = B().eikonal_backward(*a, T, g)
+    info = B().backward_info(plan)
+    for levels in (info["levels"] // 3, 2):
+        G = B().eikonal_backward_async(*a, T, g, levels, 2 * info["levels"] + 64)
+        assert B().plan_status(plan)["backward_settled"]
+        for x, y in zip(G, G0):
+            assert float((x - y).norm()) <= 1e-5 * float(y.norm()), levels
