@@ -521,13 +521,13 @@ int gbp_plan_forward_work(gbp_plan plan, int64_t *face_solves, int64_t *node_upd
 
 /*
  * gbp_plan_set_launch / gbp_plan_get_launch -- launch configuration of the
- * relaxation rounds and adjoint levels (chosen by an autotuner):
+ * relaxation rounds (chosen by an autotuner):
  *   lanes        lanes per vertex in a relaxation round: 8, 16 or 32
  *   sweep_blocks grid of a relaxation round, 64..2048
  *                (both: where rounds are launches of their own; plain cold solves
  *                of up to 2^18 vertices run all rounds in one)
- *   level_blocks most blocks that walk the adjoint's levels, 16..2048 (at most 256 are
- *                used, and one on small meshes)
+ *   level_blocks 16..2048, kept and given back: the adjoint's levels are one launch
+ *                whose blocks go by the mesh's size
  *   sync_batch   rounds between convergence checks in synchronous calls, 1..64
  * Results do not depend on the configuration beyond rounding order.
  * Errors: GBP_ERR_ARG for values outside those ranges.

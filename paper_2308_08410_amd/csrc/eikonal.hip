@@ -1739,7 +1739,7 @@ int gbp_backward_impl(gbp_plan p, const float* D, const float* vscale, const int
     a.lam = p->lam;
     a.ctl = reinterpret_cast<AdjCtl*>(reinterpret_cast<char*>(p->ctl) + offsetof(GbpCtl, adj));
     if ((rc = gbp_adj_lists(a, dL_dT, p->node_user, s))) return rc;
-    if ((rc = gbp_adj_walk(a, sync ? INT_MAX : level_budget, n_v <= kWalkBlockVerts, p->level_blocks, s))) return rc;
+    if ((rc = gbp_adj_walk(a, sync ? INT_MAX : level_budget, n_v <= kWalkBlockVerts, s))) return rc;
     // vertices on or above cycles longer than two: Gauss-Seidel on the remainder
     const int batch = gbp_adj_sweep_batch(a);
     if ((rc = gbp_adj_sweeps(a, p->cfill, true, 0, sync ? (batch > 16 ? batch : 0) : gs_budget, 1e-6f, !sync, s)))

@@ -216,7 +216,7 @@ struct gbp_plan_s {
     const void *prep_D = nullptr, *prep_vs = nullptr, *prep_rn = nullptr, *prep_rt = nullptr;
     int prep_nroots = 0;
     float* lip = nullptr;         // [4 n_e] FISTA step constant per face (allocated on use)
-    int level_blocks = 2048;      // grid of the adjoint walk
+    int level_blocks = 2048;      // kept for the caller
     int sync_batch = 16;          // launches between convergence checks (synchronous mode)
     int last_rounds = 0, last_levels = 0;   // of the last synchronous calls
     GbpCtl* ctl = nullptr;        // device control block

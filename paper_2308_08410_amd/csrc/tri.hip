@@ -894,7 +894,7 @@ extern "C" int gbp_tri_backward(gbp_tri_plan p, const float* D, const float* vsc
     a.lam = p->lam;
     a.ctl = reinterpret_cast<AdjCtl*>(reinterpret_cast<char*>(p->ctl) + offsetof(TriCtl, adj));
     if ((rc = gbp_adj_lists(a, dL_dT, nullptr, s))) return rc;
-    if ((rc = gbp_adj_walk(a, INT_MAX, n_v <= kTriWalkBlockVerts, kTeamMax, s))) return rc;
+    if ((rc = gbp_adj_walk(a, INT_MAX, n_v <= kTriWalkBlockVerts, s))) return rc;
     // vertices on or above parent-graph cycles: Gauss-Seidel sweeps over just those
     // (their children outside the list are final)
     const int batch = gbp_adj_sweep_batch(a);

@@ -34,8 +34,8 @@ int gbp_adj_lists(const AdjGraph& a, const float* dL_dT, const int* node_user, h
 // Finishes every vertex below level `levels` whose children are all finished
 // (done, lam); ctl->levels receives the last level with work + 1.  Vertices on or
 // above cycles longer than two stay unfinished.  narrow: levels of a few hundred
-// vertices, for one block; else at most `grid` blocks (>= 1) share each level.
-int gbp_adj_walk(const AdjGraph& a, int levels, bool narrow, int grid, hipStream_t s);
+// vertices, for one block.
+int gbp_adj_walk(const AdjGraph& a, int levels, bool narrow, hipStream_t s);
 
 // Gauss-Seidel sweeps from, from + 1, ..., at most `count`, over the reached vertices
 // that the walk left (ctl->remaining of them in list [n_v], listed if `build`), in place.

@@ -152,3 +152,20 @@ def test_long_lists(cells):
         assert B().plan_status(plan)["backward_settled"]
         for x, y in zip(G, G0):
             assert float((x - y).norm()) <= 1e-5 * float(y.norm()), levels
+
+
+@pytest.mark.parametrize("cells", [66, 102])     # one XCD's blocks, all
+def test_walk_takes_its_blocks(cells):
+    """Past 2^18 vertices (sweeps are launches, so the walk's team is the last): the least
+    level_blocks leaves the walk as it is."""
+    plan, D, vs, rn, rt, g = cube(cells, False)
+    a = (plan, D, vs, rn, rt)
+    T, _ = B().eikonal_forward(*a)
+    want = []
+    for level_blocks in (2048, 16):
+        B().set_launch(plan, 16, 2048, level_blocks)
+        _, dvs, drt = B().eikonal_backward(*a, T, g, want_D=False)
+        want.append((B().team(plan), dvs, drt))
+    assert want[0][0] == want[1][0] and want[0][0][1] >= 32, want
+    if B().backward_info(plan)["cyclic"] == 0:
+        assert torch.equal(want[0][1], want[1][1]) and torch.equal(want[0][2], want[1][2])
