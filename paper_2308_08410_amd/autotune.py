@@ -10,6 +10,11 @@ that graph-captured iterations can be given launch budgets.  tune_hold searches
 the hold-back alone, also for the ordered warm start (gbp_plan_set_warm_order:
 the forward solves cold, its evaluation order keyed by a guess of the solution).  Results are cached in a JSON file
 keyed by the mesh size class (override the path with GBP_TUNE_CACHE).
+
+On meshes of up to ONE_LAUNCH_VERTS vertices a plain cold forward is one launch, which
+none of the launch settings touch; they act on its hold-back, warm and FISTA rounds.  The
+launch space is searched in hold-back order there, and the hold-back search then sets the
+best of that against the one launch.
 """
 from __future__ import annotations
 
@@ -24,10 +29,10 @@ from . import binding as B
 SPACE = [dict(lanes=lanes, sweep_blocks=sb, level_blocks=2048, sync_batch=bt, split=sp)
          for sp in (1, 0) for lanes in (8, 16, 32) for sb in (256, 512, 768, 1024, 1536, 2048)
          for bt in (16, 32, 64)]
-LEVEL_SPACE = (256, 512, 1024, 2048)   # searched second, with the best of SPACE
+ONE_LAUNCH_VERTS = 1 << 18   # the library's kRoundsTeamVerts
 # a short list for plans of millions of vertices, where every trial costs a
 # forward and backward of the whole union (16 lanes, convergence read every 16
-# launches, 2048 blocks per level: the full search's picks on such plans)
+# launches: the full search's picks on such plans)
 SPACE_LARGE = [dict(lanes=16, sweep_blocks=sb, level_blocks=2048, sync_batch=16, split=sp)
                for sp in (1, 0) for sb in (768, 1024, 2048)]
 # hold-back candidates, searched last: (bucket width / mean front advance per round,
@@ -81,9 +86,9 @@ def tune(plan: B.Plan, D, vscale, root_node, root_t, backward=True, space=None, 
          use_cache=True, save=True, hold=None):
     """Pick and apply the fastest launch configuration; returns its record
     (configuration, ms per forward[+backward], rounds, levels).  Turns the plan's
-    warm order off (see tune_hold for the ordered warm start).  The adjoint's grid
-    and the hold-back are searched after the launch space when `space` is the
-    full one (hold: None) or when hold is True."""
+    warm order off (see tune_hold for the ordered warm start).  The hold-back is
+    searched after the launch space when `space` is the full one (hold: None) or when
+    hold is True."""
     B.set_warm_order(plan, False)
     key = size_key(plan)
     db = _load() if use_cache else {}
@@ -101,25 +106,25 @@ def tune(plan: B.Plan, D, vscale, root_node, root_t, backward=True, space=None, 
         if backward:
             B.eikonal_backward(plan, D, vscale, root_node, root_t, T, gT, want_D=False)
 
+    unit = 0.0
+    if plan.n_v <= ONE_LAUNCH_VERTS and B.get_hold(plan)[0] <= 0 and B.get_local_solver(plan)["solver"] == "exact":
+        unit = _front_advance(plan, D, vscale, root_node, root_t, T)
     best = None
     for cfg in (space or SPACE):
         B.set_launch(plan, cfg["lanes"], cfg["sweep_blocks"], cfg["level_blocks"], cfg["sync_batch"])
         B.set_queue_split(plan, cfg["split"])
+        if unit > 0:
+            B.set_hold(plan, 2 * unit, 0, cfg["sweep_blocks"] * (256 // cfg["lanes"]))
         run()                                    # warm-up
         ms = _time(run, repeats)
         if best is None or ms < best["ms"]:
             best = dict(cfg, ms=ms)
-    if backward and space is None:
-        for lb in LEVEL_SPACE:
-            cfg = dict(best, level_blocks=lb)
-            B.set_launch(plan, cfg["lanes"], cfg["sweep_blocks"], lb, cfg["sync_batch"])
-            B.set_queue_split(plan, cfg["split"])
-            run()
-            ms = _time(run, repeats)
-            if ms < best["ms"]:
-                best = dict(cfg, ms=ms)
     B.set_launch(plan, best["lanes"], best["sweep_blocks"], best["level_blocks"], best["sync_batch"])
     B.set_queue_split(plan, best["split"])
+    if unit > 0:
+        B.set_hold(plan, 0.0)
+        run()
+        best["ms"] = _time(run, repeats)
     best.update(hold_delta=0.0, hold_window=0, hold_open=0)
     if (space is None) if hold is None else hold:
         best.update(tune_hold(plan, D, vscale, root_node, root_t, backward=backward, repeats=repeats))
@@ -130,6 +135,15 @@ def tune(plan: B.Plan, D, vscale, root_node, root_t, backward=True, space=None, 
         db[key] = best
         _save(db)
     return dict(best, cached=False)
+
+
+def _front_advance(plan, D, vscale, root_node, root_t, T):
+    """Mean advance of the front per round of a plain cold solve (0: nothing advances)."""
+    B.eikonal_forward(plan, D, vscale, root_node, root_t, out=T)
+    fin = torch.isfinite(T)
+    rounds = max(B.last_counts(plan)["rounds"], 1)
+    span = float(T[fin].max() - T[fin].min()) if bool(fin.any()) else 0.0
+    return span / rounds
 
 
 def tune_hold(plan: B.Plan, D, vscale, root_node, root_t, guess=None, backward=True, repeats=3):
@@ -149,11 +163,7 @@ def tune_hold(plan: B.Plan, D, vscale, root_node, root_t, guess=None, backward=T
 
     B.set_warm_order(plan, False)
     B.set_hold(plan, 0.0)
-    B.eikonal_forward(plan, D, vscale, root_node, root_t, out=T)
-    fin = torch.isfinite(T)
-    rounds = max(B.last_counts(plan)["rounds"], 1)
-    span = float(T[fin].max() - T[fin].min()) if bool(fin.any()) else 0.0
-    unit = span / rounds                        # mean advance of the front per round
+    unit = _front_advance(plan, D, vscale, root_node, root_t, T)
     cap = sweep_blocks * (256 // lanes)
     B.set_warm_order(plan, ordered)
     best = None
