@@ -57,7 +57,6 @@ struct gbp_tri_plan_s {
     int* vent = nullptr;
     int* nbp = nullptr;           // [n_v+1] unique neighbours
     int* nb = nullptr;
-    float4* minv = nullptr;       // [n_t] D_eff^-1 (xx, yy, xy) and sbar
     int4* info = nullptr;         // incidence and neighbour ranges of a vertex
     int* tpos = nullptr;          // [3 n_t] position of a triangle's incidences
     TriInc* inc = nullptr;        // [3 n_t] as vent; of the forward's metric
@@ -114,7 +113,7 @@ int tri_alloc(T** p, size_t n) {
 
 void tri_free(gbp_tri_plan p) {
     if (!p) return;
-    void* ptrs[] = {p->xy,    p->tri,   p->vptr,   p->vent,   p->nbp,    p->nb,     p->minv,
+    void* ptrs[] = {p->xy,    p->tri,   p->vptr,   p->vent,   p->nbp,    p->nb,
                     p->T,     p->troot, p->q[0],   p->q[1],   p->mark,   p->ctl,    p->par,
                     p->pnode, p->pa,    p->crange, p->cfill,  p->cchild, p->calpha, p->lam,
                     p->g,     p->dsbar, p->done,   p->rec,    p->over,
@@ -169,9 +168,9 @@ __device__ __forceinline__ R tri_local(R qaa, R qbb, R qab, R sa, R sb, R pa, R 
     return best;
 }
 
-// inc (or null): the record of each of the triangle's incidences, at tpos.
+// Checks the inputs; inc (or null): the record of each of the triangle's incidences, at tpos.
 __global__ void k_tri_metric(const float* __restrict__ D, const float* __restrict__ vscale,
-                             const int4* __restrict__ tri, int n_t, float4* __restrict__ minv,
+                             const int4* __restrict__ tri, int n_t,
                              const float2* __restrict__ xy, const int* __restrict__ tpos,
                              TriInc* __restrict__ inc, TriCtl* ctl) {
     const int t = blockIdx.x * blockDim.x + threadIdx.x;
@@ -188,10 +187,9 @@ __global__ void k_tri_metric(const float* __restrict__ D, const float* __restric
     const float det = xx * yy - dxy * dxy;
     if (!(fin(xx) && fin(yy) && fin(dxy))) atomicOr(&ctl->err, ERRBIT_D_NONFINITE);
     else if (!(xx > 0.f && det > 0.f)) atomicOr(&ctl->err, ERRBIT_D_NOT_SPD);
-    const float s = 1.f / (det * sbar * sbar);
-    const float4 m = make_float4(yy * s, xx * s, -dxy * s, sbar);
-    minv[t] = m;
     if (!inc) return;
+    const float s = 1.f / (det * sbar * sbar);
+    const float3 m = make_float3(yy * s, xx * s, -dxy * s);   // D_eff^-1
 #pragma unroll
     for (int k = 0; k < 3; ++k) {
         int i, a, b;
@@ -627,7 +625,7 @@ int tri_prepare(gbp_tri_plan p, const float* D, const float* vscale, const int32
         k_tri_fill_i<<<gbp_blocks(n_v, TPB), TPB, 0, s>>>(p->mark, 0, n_v);
         p->stamp = 1;
     }
-    k_tri_metric<<<gbp_blocks(p->n_t, TPB), TPB, 0, s>>>(D, vscale, p->tri, p->n_t, p->minv, p->xy, p->tpos,
+    k_tri_metric<<<gbp_blocks(p->n_t, TPB), TPB, 0, s>>>(D, vscale, p->tri, p->n_t, p->xy, p->tpos,
                                                        cold ? p->inc : nullptr, p->ctl);
     k_tri_unreached<<<gbp_blocks(n_v, TPB), TPB, 0, s>>>(p->troot, cold ? p->T : nullptr,
                                                          cold ? p->now[0] : nullptr, p->now[1], n_v);
@@ -735,7 +733,6 @@ extern "C" int gbp_tri_plan_create(const float* xy, int n_v, const int32_t* tris
     TRI_UP(p->vent, vent.data(), (size_t)3 * n_t);
     TRI_UP(p->nbp, nbp.data(), (size_t)n_v + 1);
     TRI_UP(p->nb, nb.data(), nb.size());
-    TRI_TRY(tri_alloc(&p->minv, n_t));
     TRI_TRY(tri_alloc(&p->T, n_v));
     TRI_TRY(tri_alloc(&p->troot, n_v));
     TRI_UP(p->info, info.data(), (size_t)n_v);
