@@ -310,9 +310,9 @@ int gbp_lead_field(gbp_plan plan, const float *electrodes, int n_leads, float *W
  * gbp_tri_forward -- activation times (Alg. 2, exact local solves in FP32):
  *   D [n_t*3] velocity tensor per triangle packed (xx, yy, xy), vscale [n_v] or
  *   NULL (D_eff = sbar^2 D, sbar the mean of the three nodal scales), vertex
- *   roots and onsets as gbp_eikonal_forward; T_out [n_v].  Synchronous (the
- *   convergence check reads the queue length every 8 rounds).  Errors: as
- *   gbp_eikonal_forward.
+ *   roots and onsets as gbp_eikonal_forward; T_out [n_v].  Synchronous (all
+ *   rounds are one launch, whose end the host waits for).  Errors: as
+ *   gbp_eikonal_forward; T_out is written then too (onsets and +inf).
  * gbp_tri_backward -- vector-Jacobian product along the FP64 geodesic parents:
  *   dL_dD [n_t*3] (off-diagonal doubled) / dL_dvscale [n_v] / dL_droot_t
  *   [n_roots], each may be NULL; the formulas of gbp_eikonal_backward with

@@ -254,7 +254,7 @@ __global__ void k_ecg_zero(float* __restrict__ work, int n_work, float* __restri
     if (blockIdx.y == 0)
         for (int i = at; i < n_work; i += step) work[i] = 0.f;
     float* ecg = ecg_all + (size_t)blockIdx.y * lt.istride;
-    const int n = S * lt.Lt;   // at most 2^20 * 32
+    const int n = S * lt.Lt;   // at most 8032 * 32 = 16096 * 16
     for (int i = at; i < n; i += step) ecg[(size_t)(i / lt.Lt) * lt.Ls + i % lt.Lt] = 0.f;
 }
 

@@ -6,9 +6,10 @@
 // local problem solved in closed form (local_solve.h).  A vertex whose value
 // drops by more than eps_rel*max(1,|T|) pushes its unique neighbours into the
 // next queue (deduplicated with per-vertex stamps).  This is the change mask of
-// Alg. 2 applied at vertex granularity; updates are in place (chaotic
-// relaxation), which reaches the same fixed point because every value read is an
-// upper bound of the solution and the update is monotone.
+// Alg. 2 applied at vertex granularity.  Where a round is a launch its updates are in
+// place (chaotic relaxation), which reaches the same fixed point because every value
+// read is an upper bound of the solution and the update is monotone; where all rounds
+// are one launch (plain cold solves of up to 2^18 vertices) a round is a Jacobi step.
 //
 // Adjoint.  lambda = g + P^T lambda with P the parent weights.  The parent graph
 // is walked leaves-first (walk.h): a vertex is finished once all of its children

@@ -248,10 +248,9 @@ struct gbp_plan_s {
 };
 
 constexpr int kStatBlocks = 2048;   // max grid of the relaxation kernels
-// Loop status words a relaxation round or adjoint level writes for the host when
-// asked: [0..7] work left (the round's sub-queue lengths; a level: [0] its work
-// flag), [8] device error bits, [9] the launch index that wrote them.  They live
-// in coherent pinned host memory: the host reads them after an event that follows
+// Loop status words a relaxation round writes for the host when asked: [0..7] work left
+// (the round's sub-queue lengths), [8] device error bits, [9] the launch index that
+// wrote them.  They live in coherent pinned host memory: the host reads them after an event that follows
 // the writing launch, when the launch's writes have completed.
 constexpr int kStWords = 16;
 

@@ -96,9 +96,12 @@ struct gbp_tri_plan_s {
 namespace {
 
 constexpr int TPB = 256;
-// Meshes whose adjoint levels (fronts of a planar mesh: some sqrt(n_v) / 2 vertices)
-// are narrow enough for one block: an iteration at 250k vertices takes 10.3 ms by one
-// block and 10.4-11.1 by a team, at 2M 98.7 and 83.0.
+// Meshes whose adjoint levels one block walks.  It depends on their width, which is known
+// only once walked.  Fronts about narrow levels (27 vertices at 10k, 177 at 250k, 209 at
+// 900k), iteration by one block and by a team: 10k 1.20 and 1.95 ms, 60k 2.70 and 3.60,
+// 250k 7.2 and 8.5, 900k 22.8 and 24.7.  About wide ones (121 at 25k, 274 at 60k, 498 at
+// 250k, 1,186 at 1M), backward: 25k 0.53 and 0.77, 60k 0.88 and 0.88, 250k 3.06 and 1.96,
+// 1M 11.9 and 3.5, 2M 28.2 and 10.8.
 constexpr int kTriWalkBlockVerts = 1 << 20;
 
 template <typename T>
@@ -820,7 +823,7 @@ extern "C" int gbp_tri_forward(gbp_tri_plan p, const float* D, const float* vsca
     const int n_v = p->n_v;
     if ((rc = tri_prepare(p, D, vscale, root_node, root_t, n_roots, true, s))) return rc;
     const TriRelax g{p->info, p->inc, p->nb, p->eps_rel};
-    const int cap = (p->max_rounds + 7) / 8 * 8;
+    const int cap = p->max_rounds;
     if (n_v <= kTriBlockVerts) {
         k_tri_rounds_block<<<1, kTriThreads, tri_block_lds(n_v), s>>>(g, n_v, p->T, p->q0, p->ctl, cap);
     } else {

@@ -567,8 +567,8 @@ int gbp_adj_lists(const AdjGraph& a, const float* dL_dT, const int* node_user, h
 // Blocks of the team's launch, an eighth of them on one XCD.  Backward of tetrahedra,
 // 16 / 32 blocks of one XCD / 64 of all: 12k vertices 256 / 275 / 290 us, 100k 887 / 894 /
 // 931 us, 500k 2360 / 2250 / 2250 us; from a million on one XCD's requests bound it
-// (6M: 24.4 ms by one XCD, 23.5 by all).  By 2 blocks of one XCD a later
-// 500k takes 4.8 ms, by 32 1.4.
+// (6M: 24.4 ms by one XCD, 23.5 by all).  Another 500k mesh: 4.8 ms by 2 blocks of one
+// XCD, 1.4 by 32.
 constexpr int kWalkFewBlocks = 128, kWalkManyBlocks = 256;
 constexpr int kWalkFewVerts = 200000;
 constexpr int kWalkOneXcd = 1 << 20;
