@@ -120,8 +120,8 @@ struct XcdQueues {
 void gbp_set_queue_layout(gbp_plan p, int split);
 
 // Adjoint: a vertex's record, one 128-byte line in pieces of 16 bytes.  Its children
-// hand over their lambda in the entries (child k of the sorted list in entry k, later
-// ones in an array beside the records), whose weights stand beside them.
+// hand over their lambda in the entries, beside its weight (child k of the sorted list in
+// entry k; later ones in an array beside the records).
 constexpr int kAdjEntries = 8;
 struct AdjParent {
     int vertex;        // a weighted parent or -1
@@ -139,8 +139,9 @@ struct alignas(128) AdjRec {
     int pair;          // members of the two-cycle not yet ready (at the smaller one)
     int first;         // its child list's first position
     int pad;
-    float entry[kAdjEntries];
-    float weight[kAdjEntries];
+    struct {
+        float lam, weight;
+    } entry[kAdjEntries];
 };
 // A member's list of the vertices it made ready in a level holds at most 4 for each
 // vertex of its share of the level (a pair's two members release up to 2 each).
@@ -150,7 +151,7 @@ __host__ __device__ inline size_t walk_list_cap(int n_v, int size) {
 }
 inline size_t walk_list_size(int n_v) { return 4 * ((size_t)n_v + (size_t)kWalkGroups * kTeamMax); }
 static_assert(sizeof(AdjParent) == 16 && offsetof(AdjRec, entry) == 64 && sizeof(AdjRec) == 128,
-              "pieces 0-2 parents, 4 and 5 entries, 6 and 7 their weights");
+              "pieces 0-2 parents, 4-7 two entries each");
 
 // Plain cold solves of meshes up to this size run their rounds in one launch.
 constexpr int kRoundsTeamVerts = 1 << 18;

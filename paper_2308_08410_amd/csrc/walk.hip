@@ -58,11 +58,10 @@ __global__ void __launch_bounds__(kLinkThreads) k_adj_link(AdjGraph a, const flo
         const int wait = c - (pair ? 1 : 0);   // all its children but its partner, which is one of them
         leaf = wait == 0 && reached;
         const int4 pn = a.pnode[x];
-        float4* r = reinterpret_cast<float4*>(a.rec + x);   // ranks and weights: k_child_sort
+        float4* r = reinterpret_cast<float4*>(a.rec + x);   // ranks and entries: k_child_sort
         r[0] = make_float4(__int_as_float(pn.x), 0.f, 0.f, g);
         r[1] = make_float4(__int_as_float(pn.y), 0.f, 0.f, __int_as_float(c));
         r[2] = make_float4(__int_as_float(pn.z), 0.f, 0.f, __int_as_float(pair ? p : -1));
-        r[4] = r[5] = make_float4(0.f, 0.f, 0.f, 0.f);
         a.rec[x].rem = wait;
         a.rec[x].pair = pair && x < p ? 2 : 0;
         a.cfill[x] = 0;
@@ -120,7 +119,7 @@ __global__ void k_child_fill(AdjGraph a) {
 
 // Sort each child list by child id (fixed summation order -> deterministic), then
 // tell each child where its entry sits, its rank in the parent's list, and put the
-// first entries' weights in the parent's record (0 where there is no entry).  The entries
+// first entries' weights in the parent's record (0 where there is no entry).  They
 // arrive as (child << 2 | which of the child's parents this is) from k_child_fill;
 // child ids are distinct within a list, so the packed keys sort in child order, and
 // the ids are written back unpacked.
@@ -166,9 +165,9 @@ __global__ void __launch_bounds__(TPB) k_child_sort(AdjGraph a) {
                 calpha[b + k] = al[k];
                 a.rec[c].up[ch[k] & 3].rank = k < kAdjEntries ? k : b + k + kAdjEntries;
             }
-        float4* w = reinterpret_cast<float4*>(a.rec[p].weight);
-        w[0] = make_float4(al[0], al[1], al[2], al[3]);
-        w[1] = make_float4(al[4], al[5], al[6], al[7]);
+        float4* r = reinterpret_cast<float4*>(a.rec[p].entry);
+#pragma unroll
+        for (int k = 0; k < kAdjEntries; k += 2) r[k / 2] = make_float4(0.f, al[k], 0.f, al[k + 1]);
         return;
     }
     for (int x = b + 1; x < e; ++x) {
@@ -188,7 +187,7 @@ __global__ void __launch_bounds__(TPB) k_child_sort(AdjGraph a) {
         const int c = v >> 2;
         cchild[x] = c;
         a.rec[c].up[v & 3].rank = x - b < kAdjEntries ? x - b : x + kAdjEntries;
-        if (x - b < kAdjEntries) a.rec[p].weight[x - b] = calpha[x];
+        if (x - b < kAdjEntries) a.rec[p].entry[x - b] = {0.f, calpha[x]};
     }
 }
 
@@ -214,7 +213,7 @@ __device__ __forceinline__ double pair_sum(const AdjGraph& a, int v, int partner
         const int at = r->first + k;
         const double w = a.calpha[at];
         if (a.cchild[at] == partner) wo = w;
-        else s += w * scoped_load<SCOPE>(k < kAdjEntries ? r->entry + k : a.over + at);
+        else s += w * scoped_load<SCOPE>(k < kAdjEntries ? &r->entry[k].lam : a.over + at);
     }
     return s;
 }
@@ -222,7 +221,7 @@ __device__ __forceinline__ double pair_sum(const AdjGraph& a, int v, int partner
 constexpr int kWalkThreads = 8 * kWalkGroups;
 
 // A vertex's record, by the 8 lanes of a group: lane j holds piece j (one line, one
-// request; lanes 0-2 a parent each, 4 and 5 the entries, 6 and 7 their weights).
+// request; lanes 0-2 a parent each, 4-7 two entries each).
 struct RecPiece {
     unsigned long long u0, u1;
 };
@@ -236,10 +235,6 @@ __device__ __forceinline__ RecPiece walk_record(const AdjGraph& a, int x) {
 template <int N>
 __device__ __forceinline__ int lane_ahead(int v) {
     return __builtin_amdgcn_update_dpp(0, v, 0x100 + N, 0xf, 0xf, true);
-}
-template <int N>
-__device__ __forceinline__ float lane_ahead(float v) {
-    return __int_as_float(lane_ahead<N>(__float_as_int(v)));
 }
 template <int N>
 __device__ __forceinline__ double lane_ahead(double v) {
@@ -258,9 +253,8 @@ __device__ __forceinline__ void walk_vertex(const AdjGraph& a, int x, RecPiece p
     const int parent = j < 3 ? __float_as_int(v0) : -1, rank = __float_as_int(v1);
     float l, lq = 0.f;
     if (q < 0) {
-        // lanes 4 and 5, the sum in lane 4
-        double s = (double)v0 * lane_ahead<2>(v0) + (double)v1 * lane_ahead<2>(v1) +
-                   (double)v2 * lane_ahead<2>(v2) + (double)v3 * lane_ahead<2>(v3);
+        double s = (double)v0 * v1 + (double)v2 * v3;   // lanes 4-7; lane 4 gets the sum
+        s += lane_ahead<2>(s);
         s += lane_ahead<1>(s);
         if (nchild > kAdjEntries) {
             // entries past the record's, each lane every eighth
@@ -288,7 +282,7 @@ __device__ __forceinline__ void walk_vertex(const AdjGraph& a, int x, RecPiece p
     auto hand_on = [&](int self, float lam, int p, int rk, int skip) {
         if (p >= 0) {
             const int left = p != skip ? __hip_atomic_fetch_add(&a.rec[p].rem, -1, __ATOMIC_RELAXED, SCOPE) : 0;
-            scoped_store<SCOPE>(rk < kAdjEntries ? a.rec[p].entry + rk : a.over + (rk - kAdjEntries), lam);
+            scoped_store<SCOPE>(rk < kAdjEntries ? &a.rec[p].entry[rk].lam : a.over + (rk - kAdjEntries), lam);
             if (left == 1) ready(p);
         }
         if (j == 3) {
