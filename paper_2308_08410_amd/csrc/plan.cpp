@@ -81,9 +81,9 @@ size_t team_list_size(const TeamListCap& cap, int blocks) {
 
 TeamListCap team_list_cap(int n_v, const int* degree, int& blocks) {
     std::vector<int> d(degree, degree + n_v);
-    std::sort(d.begin(), d.end(), std::greater<int>());
     for (;; blocks /= 2) {
         const int k = std::min(n_v, n_v / blocks + 1);   // a full team's share
+        std::nth_element(d.begin(), d.begin() + (k - 1), d.end(), std::greater<int>());
         const long long sum = std::accumulate(d.begin(), d.begin() + k, 0LL);
         const int slope = d[k - 1];
         const TeamListCap cap{n_v, (int)std::min<long long>(sum - (long long)k * slope, n_v), slope};
